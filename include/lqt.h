@@ -273,10 +273,10 @@ lqt_status lqt_backward(const lqt_dims *dims, const lqt_problem *prob, const voi
  * function (Theorem 6, Lemma 7) the separator returns the problem's terminal value (Sec. IV-D)
  * whatever follows it, and its closed-loop map (Sec. IV-E) sends any state to the next x0, so
  * one scan of each kind solves every problem of the class.  Launches per class: problem
- * constants, elements, clearing of status words, and one launch for both scans, whose waves take
- * tiles (nx <= 4: value tiles in the value scan's order, then trajectory tiles) or tree nodes
- * (nx >= 5: every level of both trees, in dependency order) from a work queue; a wave only waits
- * for work taken before its own, so every wait ends.  The number of launches does not depend on
+ * constants, elements, and then for nx <= 4 the clearing of status words and one launch for both
+ * scans, whose waves take tiles (value tiles in the value scan's order, then trajectory tiles)
+ * from a work queue; a wave only waits for work taken before its own, so every wait ends; for
+ * nx >= 5 a launch per level of the two scan trees.  The number of launches does not depend on
  * the number of problems.
  * ------------------------------------------------------------------------------------------- */
 typedef struct lqt_ragged {
@@ -303,7 +303,7 @@ lqt_status lqt_solve_batched(const lqt_ragged *classes, int32_t nclasses, void *
  * keep them alive until lqt_plan_destroy; launches of one plan must not overlap.
  * flags & LQT_PLAN_AUTOTUNE: time the candidate configurations (per class: the blocks per lane
  * of the value tiles on the per-lane path, two candidates chosen from the class's rows among 1,
- * 4 and 8; 4, 8 or 16 nodes per wave on the wave path; then concurrent or serial classes) by
+ * 4 and 8; 4, 8 or 16 blocks per level-1 node on the wave path; then concurrent or serial classes) by
  * running them on `stream` (outputs are overwritten)
  * and keep the fastest; choices are cached per class signature for the life of the process
  * (thread-safe).  Without the flag the default configuration is used.  flags & LQT_PLAN_GRAPH:

@@ -4,10 +4,10 @@
 //
 // Each class runs the solve over its concatenated horizon in ragged mode (KProb::seg): the element
 // build inserts a separator element after every problem, the control and value kernels look up
-// the owning problem of a boundary.  After the element build, both scans of a class run in one
-// launch whose waves take their tiles (per-lane path) or tree nodes (wave path) from a work queue
-// in dependency order, so a plan is four launches per class (constants, elements, clearing of the
-// queue's status words, the queue launch), whatever the number of problems.
+// the owning problem of a boundary.  After the element build, both scans of a per-lane class run in
+// one launch whose waves take their tiles from a work queue in dependency order; those of a wave-path
+// class take a launch per tree level (tile_kernels.hpp).  The number of launches does not depend on
+// the number of problems.
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -146,11 +146,11 @@ std::vector<int> lane_chunks(long rows) {
   return {8, 4};
 }
 
-// Every class runs its scans in one launch over a work queue (queue_chunk != 0).
+// Per-lane classes run their scans in one launch over a work queue (queue_chunk != 0).
 SolveOpts default_opts(const ClassRun& r) {
   SolveOpts o;
   o.wave_chunk = 8;
-  o.queue_chunk = is_wave(r.d) ? 1 : lane_chunks(r.c.rows)[0];
+  o.queue_chunk = is_wave(r.d) ? 0 : lane_chunks(r.c.rows)[0];
   return o;
 }
 
@@ -366,7 +366,6 @@ lqt_status tune(lqt_plan_s* p, hipStream_t s, Choice* ch) {
       for (int wc : kWaveChunks) {
         SolveOpts o;
         o.wave_chunk = wc;
-        o.queue_chunk = 1;
         cands.push_back(o);
       }
     } else {
@@ -388,8 +387,7 @@ lqt_status tune(lqt_plan_s* p, hipStream_t s, Choice* ch) {
     }
     ch->opts.push_back(bo);
     const std::string choice =
-        is_wave(r.d) ? "wave path, both trees in one queue launch, " +
-                           std::to_string(bo.wave_chunk) + " nodes per wave"
+        is_wave(r.d) ? "wave path, " + std::to_string(bo.wave_chunk) + " blocks per level-1 node"
                      : "lane path, both scans in one queue launch, " +
                            std::to_string(bo.queue_chunk) + " blocks per lane (value scan)";
     snprintf(buf, sizeof(buf), "class %zu (nx=%d nu=%d count=%d rows=%lld): %s, %.3f ms; ", i,

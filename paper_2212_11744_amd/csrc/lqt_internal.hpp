@@ -133,8 +133,6 @@ struct Work {
   void* tpart[kMaxLevels + 1] = {};  // trajectory tree: lane partials above level l
   void* elts = nullptr;              // elements when the caller gives none (lqt_solve)
   void* gsamp = nullptr;             // adjoint with sampled L: G(t) at every sample
-  unsigned* wq_done = nullptr;       // wave path: status words and counter of the queue solve
-  long wq_words = 0;
   void* bmap = nullptr;              // wave path, solve: every block's map ([batch][T][nx^2 + nx])
   // canary mode (lqt_debug_canary): a 256-byte slot after every region, filled by check_ws and
   // checked at the end of the call; canary_res: the index of the first changed slot
@@ -270,27 +268,8 @@ struct WTree {
 // so the serial chain of a wave (wcs[l] combinations or folds) is what they cost.
 constexpr int kWaveUpperChunk = 4;
 WTree wave_tree(long T, int wc);
-// The wave path's solve after the element build in one launch over a work queue: the stages of
-// the two trees (4 levels + 1 of them) and where their items start; done: one status word per
-// item, then the item counter (total + 1 words, zero before the launch).
-constexpr int kWqMaxLevels = 16;
-struct WQueue {
-  int levels = 0, nst = 0;
-  int wcs[kWqMaxLevels + 1] = {};  // branching of every level (WTree::wcs)
-  long total = 0;
-  long n[kWqMaxLevels + 1] = {};      // nodes per problem at level l (n[0] = T)
-  long start[4 * kWqMaxLevels + 1] = {};
-  int kind[4 * kWqMaxLevels + 1] = {};
-  int level[4 * kWqMaxLevels + 1] = {};
-  unsigned* done = nullptr;
-  void* bmap = nullptr;  // per-block maps (Work::bmap)
-  void* vtup[kWqMaxLevels + 1] = {};
-  void* vval[kWqMaxLevels + 1] = {};
-  void* tmap[kWqMaxLevels + 1] = {};
-  void* tx[kWqMaxLevels + 1] = {};
-};
-// The queue of a tree (pointers from w; false if the tree is deeper than kWqMaxLevels).
-bool wave_queue(const WTree& t, long batch, const Work& w, WQueue* q);
+// Levels the wave path's launches have room for (T up to 2^31 with 4 nodes per node).
+constexpr int kTreeMaxLevels = 16;
 // Launchers of one wave-path instantiation (state size, dtype).
 struct WaveFns {
   hipError_t (*build)(const KProb&, void* elts, hipStream_t);
@@ -298,9 +277,6 @@ struct WaveFns {
                       void* maps1, hipStream_t);
   hipError_t (*traj)(const KProb&, const WTree&, const Work&, const void* elts, const void* S,
                      const void* v, void* x, void* u, bool maps_ready, hipStream_t);
-  // both trees in one launch (q.done cleared)
-  hipError_t (*solve_queue)(const KProb&, const WQueue& q, const void* elts, void* S, void* v,
-                            void* x, void* u, hipStream_t);
   hipError_t (*build_fwd)(const KProb&, void* elts, hipStream_t);    // Theorem 9
   hipError_t (*build_split)(const KProb&, void* elts, hipStream_t);  // split blocks
   // Method 2 trajectory (node products in w.vtup, prefix records in w.vpart)
@@ -328,15 +304,12 @@ hipError_t wave_value(const KProb& kp, int dtype, const WTree& t, const Work& w,
 hipError_t wave_traj(const KProb& kp, int dtype, const WTree& t, const Work& w, const void* elts,
                      const void* S, const void* v, void* x, void* u, bool maps_ready,
                      hipStream_t s);
-hipError_t wave_solve_queue(const KProb& kp, int dtype, const WQueue& q, const void* elts, void* S,
-                            void* v, void* x, void* u, hipStream_t s);
 
 // Options of a full solve: the number of nodes per wave of the wave path's trees.
 struct SolveOpts {
   int wave_chunk = 8;
   // Per-lane path: 0 runs the value and trajectory scans as two launches (chunks from
   // scan_chunk); 1, 4 or 8 runs both in one work-queue launch with that value chunk.
-  // Wave path: nonzero runs both trees in one work-queue launch (wave_queue).
   int queue_chunk = 0;
 };
 

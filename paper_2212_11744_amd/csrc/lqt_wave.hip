@@ -14,6 +14,7 @@
 #include "../../include/lqt.h"
 #include "coherent.hpp"
 #include "lqt_internal.hpp"
+#include "tile_kernels.hpp"
 
 namespace lqt {
 namespace {
@@ -309,39 +310,38 @@ WDEV GRef<R> rec_ref(R* rec, int p, long k, long n, int NE) {
   return {rec + ((long)p * n + k) * NE, 1};
 }
 
-// Acc (coherent.hpp): the access policy of the global side.
-template <class Acc = PlainAcc, class R>
+template <class R>
 WDEV void wt_load(WT<R> t, GRef<const R> g, int n) {
   const int ns = n * (n + 1) / 2;
   const int oB = n * n, oC = oB + n, oE = oC + ns, oJ = oE + n;
   for (int e = lane_id(); e < n * n; e += 64) {
     const int i = e / n, j = e % n;
-    t.A[e] = Acc::ld(g.g + e * g.st);
-    t.C[e] = Acc::ld(g.g + (oC + pk(i, j, n)) * g.st);
-    t.J[e] = Acc::ld(g.g + (oJ + pk(i, j, n)) * g.st);
+    t.A[e] = g.g[e * g.st];
+    t.C[e] = g.g[(oC + pk(i, j, n)) * g.st];
+    t.J[e] = g.g[(oJ + pk(i, j, n)) * g.st];
   }
   for (int i = lane_id(); i < n; i += 64) {
-    t.b[i] = Acc::ld(g.g + (oB + i) * g.st);
-    t.e[i] = Acc::ld(g.g + (oE + i) * g.st);
+    t.b[i] = g.g[(oB + i) * g.st];
+    t.e[i] = g.g[(oE + i) * g.st];
   }
   wsync();
 }
 
-template <class Acc = PlainAcc, class R>
+template <class R>
 WDEV void wt_store(WT<R> t, GRef<R> g, int n) {
   const int ns = n * (n + 1) / 2;
   const int oB = n * n, oC = oB + n, oE = oC + ns, oJ = oE + n;
   for (int e = lane_id(); e < n * n; e += 64) {
     const int i = e / n, j = e % n;
-    Acc::st(g.g + e * g.st, t.A[e]);
+    g.g[e * g.st] = t.A[e];
     if (i <= j) {
-      Acc::st(g.g + (oC + pk(i, j, n)) * g.st, t.C[e]);
-      Acc::st(g.g + (oJ + pk(i, j, n)) * g.st, t.J[e]);
+      g.g[(oC + pk(i, j, n)) * g.st] = t.C[e];
+      g.g[(oJ + pk(i, j, n)) * g.st] = t.J[e];
     }
   }
   for (int i = lane_id(); i < n; i += 64) {
-    Acc::st(g.g + (oB + i) * g.st, t.b[i]);
-    Acc::st(g.g + (oE + i) * g.st, t.e[i]);
+    g.g[(oB + i) * g.st] = t.b[i];
+    g.g[(oE + i) * g.st] = t.e[i];
   }
   wsync();
 }
@@ -662,31 +662,6 @@ WDEV WS<R> ws_at(R* base, int* piv, int n) {
   return s;
 }
 
-// ------------------------------------------------------------------------------------------
-// Element build (Theorem 8), one wave per block: RK4 on the full matrices.
-// ------------------------------------------------------------------------------------------
-// Separator element of ragged mode after problem i (see KProb): A - I = -I, b = x0 of problem
-// i + 1 (0 after the last), C = 0, eta = Qf_i rf_i, J = Qf_i.
-template <class R>
-WDEV void w_separator(const KProb& kp, int i, WT<R> y, int n) {
-  const R* Qf = (const R*)kp.Qf + (long)i * n * n;
-  const R* rf = (const R*)kp.rf + (long)i * n;
-  const bool last = i + 1 >= kp.nseg;
-  for (int e = lane_id(); e < n * n; e += 64) {
-    const int a = e / n, b = e % n;
-    y.A[e] = a == b ? R(-1) : R(0);
-    y.C[e] = R(0);
-    y.J[e] = Qf[(a < b ? a : b) * n + (a < b ? b : a)];
-  }
-  for (int a = lane_id(); a < n; a += 64) {
-    y.b[a] = last ? R(0) : ((const R*)kp.x0)[(long)(i + 1) * n + a];
-    R s = R(0);
-    for (int b = 0; b < n; ++b) s = fma(Qf[a * n + b], rf[b], s);
-    y.e[a] = s;
-  }
-  wsync();
-}
-
 // Where block k's data sits: problem p, sample offset s0 (sample j of the block at
 // s0 + 2 n k + j), left end t[tk], constant F of problem pf.
 struct WBlk {
@@ -849,29 +824,6 @@ WDEV void wb_bwd_steps(const KProb& kp, const WBlk& bk, long k, int nsteps, WT<R
     w_copy(y.e, ac.e, n);
     w_copy(y.J, ac.J, n * n);
   }
-}
-
-template <int N, class R>
-__global__ __launch_bounds__(64) void kw_build(const KProb kp, R* __restrict__ elts) {
-  constexpr int kTupW = 3 * N * N + 2 * N;
-  __shared__ R sh[3 * kTupW + kBuildScr<N>];
-  constexpr int n = N;
-  const long T = kp.T;
-  const long k = blockIdx.x;
-  WBlk bk = wblk_plain(kp, blockIdx.y, k);
-  WT<R> y = wt_at(sh, n), ac = wt_at(sh + kTupW, n), st = wt_at(sh + 2 * kTupW, n);
-  if (kp.seg) {
-    const int p = seg_find(kp.seg, kp.nseg, k);
-    if (k == kp.seg[p + 1] - 1 || k == T - 1) {
-      w_separator(kp, p, y, n);
-      wt_store(y, elt_ref(elts, 0, k, T, ne_w(n)), n);
-      return;
-    }
-    bk = {p, (long)p * (1 - 2L * kp.n), k, p};
-  }
-  wt_identity(y, n);
-  wb_bwd_steps<N, R>(kp, bk, k, kp.n, y, ac, st, sh + 3 * kTupW);
-  wt_store(y, elt_ref(elts, kp.seg ? 0 : bk.p, k, T, ne_w(n)), n);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1129,786 +1081,6 @@ __global__ __launch_bounds__(64) void kw_build_split(const KProb kp, R* __restri
 }
 
 // ------------------------------------------------------------------------------------------
-// Element build for nx <= 8 with 8 blocks per wave: lane 8 g + i owns row i of every matrix of
-// block 8 w + g (A - I, C, J rows, b_i, eta_i) in registers, with its rows of G, Q, F and F^T.
-// The products of a stage need other rows of J, K, Lc and A Lc, and the vectors eta and G eta + c;
-// each group publishes them in its own LDS area (rows padded to nx + 1 values, so the 8 rows of a
-// group sit in different banks) and reads them back after a barrier: three barriers per stage
-// for 8 blocks, and each LDS read serves the 8 lanes of a group at once.  Same RK4 recursion of
-// Theorem 8 as the per-lane path; J and C are symmetrised from their upper entries after every
-// step.
-// ------------------------------------------------------------------------------------------
-template <int N, class R>
-__global__ __launch_bounds__(64) void kw_build_rows(const KProb kp, R* __restrict__ elts) {
-  static_assert(N <= 8, "8 lanes per block");
-  constexpr int P = N + 1;  // padded row length in LDS
-  __shared__ R sJ[8][8 * P], sK[8][8 * P], sL[8][8 * P], sAL[8][8 * P], se[8][8], sw[8][8];
-  const int lane = lane_id(), g = lane >> 3, i = lane & 7;
-  const int nu = kp.nu;
-  const long T = kp.T;
-  const int nn = kp.n;
-  const long k = (long)blockIdx.x * 8 + g;
-  const bool row = i < N;
-  bool live = k < T;
-  bool sep = false;
-  int p = blockIdx.y;
-  long s0 = (long)p * (2L * nn * T + 1), tk = (long)p * (T + 1) + k, pf = 0;
-  if (kp.seg && live) {
-    p = seg_find(kp.seg, kp.nseg, k);
-    sep = k == kp.seg[p + 1] - 1 || k == T - 1;
-    s0 = (long)p * (1 - 2L * nn);
-    tk = k;
-    pf = p;
-  }
-  const bool work = live && !sep;  // this group integrates a block
-  const bool act = work && row;    // this lane owns a row of it
-  const R* cs = (const R*)kp.consts + (long)p * consts_count(N, nu);
-  const R* Qp = (const R*)kp.Q + (long)p * N * N;
-  const R* Fc = (const R*)kp.F + pf * N * N;
-  // constant rows: G_i, Q_i, F_i, (F^T)_i, Lc_i
-  R Gr[N], Qr[N], Fr[N], Fk[N], Lr[N];
-#pragma unroll
-  for (int q = 0; q < N; ++q) {
-    Gr[q] = act ? cs[consts_off_G(N, nu) + i * N + q] : R(0);
-    Qr[q] = act ? Qp[i * N + q] : R(0);
-    Fr[q] = act ? Fc[i * N + q] : R(0);
-    Fk[q] = act ? Fc[q * N + i] : R(0);
-    Lr[q] = act && q < nu ? cs[consts_off_Lc(N, nu) + i * nu + q] : R(0);
-  }
-  const R* W = cs + consts_off_W(N, nu);
-  R yA[N], yJ[N], yC[N], aA[N], aJ[N], tA[N], tJ[N];
-  R ye = R(0), yb = R(0), ae = R(0), te = R(0);
-#pragma unroll
-  for (int q = 0; q < N; ++q) yA[q] = yJ[q] = yC[q] = R(0);
-  const R h = work ? (((const R*)kp.t)[tk + 1] - ((const R*)kp.t)[tk]) / R(nn) : R(0);
-  if (!kp.L_sampled) {
-#pragma unroll
-    for (int q = 0; q < N; ++q) sL[g][i * P + q] = Lr[q];
-  }
-  for (int m = 0; m < nn; ++m) {
-    const long j1 = 2L * nn * k + 2L * (nn - m);
-#pragma unroll
-    for (int q = 0; q < N; ++q) {
-      tA[q] = yA[q];
-      tJ[q] = yJ[q];
-    }
-    te = ye;
-    for (int st = 0; st < 4; ++st) {
-      const long j = st == 0 ? j1 : (st == 3 ? j1 - 2 : j1 - 1);
-      const R wk = (st == 0 || st == 3) ? -h / R(6) : -h / R(3);
-      const R cn = st == 2 ? -h : -h / R(2);
-      R rv[N], cv[N];
-#pragma unroll
-      for (int q = 0; q < N; ++q) {
-        rv[q] = act ? ((const R*)kp.r)[(s0 + j) * N + q] : R(0);
-        cv[q] = act && kp.has_c ? ((const R*)kp.c)[(s0 + j) * N + q] : R(0);
-      }
-      if (kp.F_sampled) {
-        const R* Fj = (const R*)kp.F + (s0 + j) * N * N;
-#pragma unroll
-        for (int q = 0; q < N; ++q) {
-          Fr[q] = act ? Fj[i * N + q] : R(0);
-          Fk[q] = act ? Fj[q * N + i] : R(0);
-        }
-      }
-      if (kp.L_sampled) {  // Lc = L(t_j) W, G = Lc Lc^T
-        const R* Lj = (const R*)kp.L + (s0 + j) * N * nu;
-#pragma unroll
-        for (int l = 0; l < N; ++l) {
-          R a = R(0);
-          if (act && l < nu)
-            for (int q = 0; q < nu; ++q) a = fma(Lj[i * nu + q], W[q * nu + l], a);
-          Lr[l] = a;
-          sL[g][i * P + l] = a;
-        }
-        wsync();
-#pragma unroll
-        for (int q = 0; q < N; ++q) {
-          R a = R(0);
-#pragma unroll
-          for (int l = 0; l < N; ++l) a = fma(Lr[l], sL[g][q * P + l], a);
-          Gr[q] = a;
-        }
-      }
-      // publish the stage's J row and eta_i
-#pragma unroll
-      for (int q = 0; q < N; ++q) sJ[g][i * P + q] = tJ[q];
-      se[g][i] = te;
-      wsync();
-      // K_i = G_i J - F_i;  w_i = G_i eta + c_i
-      R K[N];
-#pragma unroll
-      for (int q = 0; q < N; ++q) {
-        R a = -Fr[q];
-#pragma unroll
-        for (int l = 0; l < N; ++l) a = fma(Gr[l], sJ[g][l * P + q], a);
-        K[q] = a;
-      }
-      R w = row ? cv[i] : R(0);
-#pragma unroll
-      for (int l = 0; l < N; ++l) w = fma(Gr[l], se[g][l], w);
-#pragma unroll
-      for (int q = 0; q < N; ++q) sK[g][i * P + q] = K[q];
-      sw[g][i] = w;
-      wsync();
-      // kA_i = K_i + (Ad)_i K;  kb_i = -(w_i + (Ad)_i w);  (A Lc)_i = Lc_i + (Ad)_i Lc
-      R kA[N], AL[N], kJ[N];
-#pragma unroll
-      for (int q = 0; q < N; ++q) {
-        R a = K[q];
-#pragma unroll
-        for (int l = 0; l < N; ++l) a = fma(tA[l], sK[g][l * P + q], a);
-        kA[q] = a;
-      }
-      R kb = w;
-#pragma unroll
-      for (int l = 0; l < N; ++l) kb = fma(tA[l], sw[g][l], kb);
-      kb = -kb;
-#pragma unroll
-      for (int q = 0; q < N; ++q) {
-        R a = Lr[q];
-#pragma unroll
-        for (int l = 0; l < N; ++l) a = fma(tA[l], sL[g][l * P + q], a);
-        AL[q] = q < nu ? a : R(0);
-        sAL[g][i * P + q] = AL[q];
-      }
-      // ke_i = (K^T eta)_i + J_i c - Q_i r;  kJ_i = -Q_i + J_i K - (F^T)_i J
-      R ke = R(0);
-#pragma unroll
-      for (int l = 0; l < N; ++l) {
-        ke = fma(sK[g][l * P + i], se[g][l], ke);
-        if (kp.has_c) ke = fma(tJ[l], cv[l], ke);
-        ke = fma(-Qr[l], rv[l], ke);
-      }
-#pragma unroll
-      for (int q = 0; q < N; ++q) {
-        R a = -Qr[q];
-#pragma unroll
-        for (int l = 0; l < N; ++l) {
-          a = fma(tJ[l], sK[g][l * P + q], a);
-          a = fma(-Fk[l], sJ[g][l * P + q], a);
-        }
-        kJ[q] = a;
-      }
-      wsync();
-      // kC_i = -(A Lc)_i (A Lc)^T
-#pragma unroll
-      for (int q = 0; q < N; ++q) {
-        R a = R(0);
-#pragma unroll
-        for (int l = 0; l < N; ++l) a = fma(AL[l], sAL[g][q * P + l], a);
-        yC[q] = fma(-wk, a, yC[q]);
-      }
-      yb = fma(wk, kb, yb);
-#pragma unroll
-      for (int q = 0; q < N; ++q) {
-        aA[q] = st == 0 ? fma(wk, kA[q], yA[q]) : fma(wk, kA[q], aA[q]);
-        aJ[q] = st == 0 ? fma(wk, kJ[q], yJ[q]) : fma(wk, kJ[q], aJ[q]);
-        if (st < 3) {
-          tA[q] = fma(cn, kA[q], yA[q]);
-          tJ[q] = fma(cn, kJ[q], yJ[q]);
-        }
-      }
-      ae = st == 0 ? fma(wk, ke, ye) : fma(wk, ke, ae);
-      if (st < 3) te = fma(cn, ke, ye);
-    }
-    // end of step: new start value; J and C take their upper entries
-#pragma unroll
-    for (int q = 0; q < N; ++q) {
-      yA[q] = aA[q];
-      sJ[g][i * P + q] = aJ[q];
-      sK[g][i * P + q] = yC[q];
-    }
-    ye = ae;
-    wsync();
-#pragma unroll
-    for (int q = 0; q < N; ++q) {
-      yJ[q] = q < i ? sJ[g][q * P + i] : aJ[q];
-      yC[q] = q < i ? sK[g][q * P + i] : yC[q];
-    }
-    wsync();
-  }
-  if (!live || !row) return;
-  const GRef<R> o = elt_ref(elts, kp.seg ? 0 : p, k, T, ne_w(N));
-  const int ns = N * (N + 1) / 2;
-  const int oB = N * N, oC = oB + N, oE = oC + ns, oJ = oE + N;
-  if (sep) {  // separator after problem p (see KProb): A - I = -I, b = next x0, C = 0
-    const R* Qf = (const R*)kp.Qf + (long)p * N * N;
-    const R* rf = (const R*)kp.rf + (long)p * N;
-    const bool last = p + 1 >= kp.nseg;
-    R e = R(0);
-#pragma unroll
-    for (int q = 0; q < N; ++q) {
-      o.g[(i * N + q) * o.st] = q == i ? R(-1) : R(0);
-      e = fma(Qf[i * N + q], rf[q], e);
-      if (q >= i) {
-        o.g[(oC + pk(i, q, N)) * o.st] = R(0);
-        o.g[(oJ + pk(i, q, N)) * o.st] = Qf[i * N + q];
-      }
-    }
-    o.g[(oB + i) * o.st] = last ? R(0) : ((const R*)kp.x0)[(long)(p + 1) * N + i];
-    o.g[(oE + i) * o.st] = e;
-    return;
-  }
-#pragma unroll
-  for (int q = 0; q < N; ++q) {
-    o.g[(i * N + q) * o.st] = yA[q];
-    if (q >= i) {
-      o.g[(oC + pk(i, q, N)) * o.st] = yC[q];
-      o.g[(oJ + pk(i, q, N)) * o.st] = yJ[q];
-    }
-  }
-  o.g[(oB + i) * o.st] = yb;
-  o.g[(oE + i) * o.st] = ye;
-}
-
-// ------------------------------------------------------------------------------------------
-// Element build for nx <= 8 in FP64 on the matrix cores, two blocks per wave.  A 16 x 16 product
-// tile of v_mfma_f64_16x16x4f64 takes the two blocks' left factors stacked (rows 8 b + i) and
-// their right factors side by side (columns 8 b + j), so its diagonal 8 x 8 blocks are the two
-// blocks' products (the off-diagonal blocks mix the two and are not used).  In the result layout
-// (lane 16 q + j holds entries (q + 4 r, j)) the lanes of columns 8 b .. 8 b + 7 hold rows q and
-// q + 4 of block b in registers r = 2 b and 2 b + 1, so every state matrix of the RK4 recursion
-// (A - I, J: start, stage, accumulator; C: accumulator) is two registers per lane with nothing
-// wasted; only operands pass through LDS (rows padded).  Entries beyond nx are zero throughout.
-// Same arithmetic as kw_build_mfma16 (K = G J - F, kA = K + A K, kJ = -Q + J K - F^T J,
-// kC = -(A Lc)(A Lc)^T, Theorem 8 with K factored out), two barriers per stage.
-// ------------------------------------------------------------------------------------------
-template <int N>
-__global__ __launch_bounds__(64, 3) void kw_build_mfma8(const KProb kp, double* __restrict__ elts) {
-  static_assert(N <= 8, "two blocks of at most 8 states per 16 x 16 tile");
-  constexpr int XP = 9, YP = 17;  // padded row lengths: stacked (16 x 8), side by side (8 x 16)
-  typedef double R;
-  // left factors stacked [16][XP], right factors side by side [8][YP]
-  __shared__ R xA[16 * XP], xJ[16 * XP], xG[16 * XP], xFT[16 * XP], xAL[16 * XP];
-  __shared__ R yJ[8 * YP], yK[8 * YP], yL[8 * YP], yALT[8 * YP];
-  __shared__ R sF[16 * XP], sQ[16 * XP];  // F and Q of each block's problem (row 8 b + i)
-  __shared__ R se[2][8], sw[2][8], sr[2][3][8], sc[2][3][8];  // samples: 3 per RK4 step
-  const int lane = lane_id(), li = lane & 15, lq = lane >> 4;
-  const int b = li >> 3, lj = li & 7;  // block of this lane's columns, column inside the block
-  const int nu = kp.nu;
-  const long T = kp.T;
-  const int nn = kp.n;
-  // the two blocks of this wave and their problems
-  long kb2[2], s0b[2], tkb[2];
-  int pb[2];
-  bool liveb[2], sepb[2];
-  for (int c = 0; c < 2; ++c) {
-    const long k = 2L * blockIdx.x + c;
-    int p = blockIdx.y;
-    long s0 = (long)p * (2L * nn * T + 1), tk = (long)p * (T + 1) + k;
-    bool live = k < T, sep = false;
-    if (kp.seg && live) {
-      p = seg_find(kp.seg, kp.nseg, k);
-      sep = k == kp.seg[p + 1] - 1 || k == T - 1;
-      s0 = (long)p * (1 - 2L * nn);
-      tk = k;
-    }
-    kb2[c] = k;
-    s0b[c] = s0;
-    tkb[c] = tk;
-    pb[c] = p;
-    liveb[c] = live;
-    sepb[c] = sep;
-  }
-  const bool work0 = liveb[0] && !sepb[0], work1 = liveb[1] && !sepb[1];
-  // per-block constants: G (stacked), F (rows 8 b + i), -F^T (stacked), Q, Lc (side by side)
-  for (int e = lane; e < 2 * 64; e += 64) {
-    const int c = e >> 6, i = (e >> 3) & 7, j = e & 7;
-    const bool wk = c == 0 ? work0 : work1;
-    const bool in = wk && i < N && j < N;
-    const long pc = kp.seg ? pb[c] : 0;
-    const R* cs = (const R*)kp.consts + (long)pb[c] * consts_count(N, nu);
-    xG[(8 * c + i) * XP + j] = in ? cs[consts_off_G(N, nu) + i * N + j] : R(0);
-    sQ[(8 * c + i) * XP + j] = in ? ((const R*)kp.Q)[(long)pb[c] * N * N + i * N + j] : R(0);
-    if (!kp.F_sampled) {
-      const R* Fc = (const R*)kp.F + pc * N * N;
-      sF[(8 * c + i) * XP + j] = in ? Fc[i * N + j] : R(0);
-      xFT[(8 * c + i) * XP + j] = in ? -Fc[j * N + i] : R(0);
-    }
-    yL[i * YP + 8 * c + j] = in && j < nu ? cs[consts_off_Lc(N, nu) + i * nu + j] : R(0);
-  }
-  const R h0 = work0 ? (((const R*)kp.t)[tkb[0] + 1] - ((const R*)kp.t)[tkb[0]]) / R(nn) : R(0);
-  const R h1 = work1 ? (((const R*)kp.t)[tkb[1] + 1] - ((const R*)kp.t)[tkb[1]]) / R(nn) : R(0);
-  const R h = b == 0 ? h0 : h1;  // (selects, not indexing: per-lane indices would go to scratch)
-  // state: entries (lq + 4 s, lj) of block b in slot s
-  R yAs[2], yJs[2], yCs[2], aAs[2], aJs[2], tAs[2], tJs[2];
-#pragma unroll
-  for (int t = 0; t < 2; ++t) yAs[t] = yJs[t] = yCs[t] = R(0);
-  R ye = R(0), yb = R(0), ae = R(0), te = R(0);  // component lj of block b (all four lq alike)
-  // Reference (and drift) samples of an RK4 step: lane L < 48 holds sample 2 n (k + 1) - 2 m - o
-  // (o = (L % 24) / 8) component L % 8 of block L / 24; the next step's are loaded while the
-  // current step runs, so only the first step waits for memory.
-  const int pc_ = lane < 48 ? lane / 24 : 0, po = (lane % 24) / 8, pi = lane & 7;
-  const bool pl = lane < 48 && (pc_ == 0 ? work0 : work1) && pi < N;
-  const long sbase = (pc_ == 0 ? s0b[0] + 2L * nn * kb2[0] : s0b[1] + 2L * nn * kb2[1]) - po;
-  auto sample_at = [&](int m, const void* arr) -> R {
-    if (!pl || !arr) return R(0);
-    return ((const R*)arr)[(sbase + 2L * (nn - m)) * N + pi];
-  };
-  R nr = sample_at(0, kp.r), ncv = sample_at(0, kp.has_c ? kp.c : nullptr);
-  wsync();
-  for (int m = 0; m < nn; ++m) {
-    if (lane < 48) {
-      sr[pc_][po][pi] = nr;
-      sc[pc_][po][pi] = ncv;
-    }
-    if (m + 1 < nn) {
-      nr = sample_at(m + 1, kp.r);
-      ncv = sample_at(m + 1, kp.has_c ? kp.c : nullptr);
-    }
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      tAs[t] = yAs[t];
-      tJs[t] = yJs[t];
-    }
-    te = ye;
-#pragma unroll
-    for (int st = 0; st < 4; ++st) {
-      const int jo = st == 0 ? 0 : (st == 3 ? 2 : 1);  // sample offset below 2 n (k + 1) - 2 m
-      const R wk = (st == 0 || st == 3) ? -h / R(6) : -h / R(3);
-      const R cn = st == 2 ? -h : -h / R(2);
-      if (kp.F_sampled) {
-        for (int e = lane; e < 2 * 64; e += 64) {
-          const int c = e >> 6, i = (e >> 3) & 7, q = e & 7;
-          const bool in = (c == 0 ? work0 : work1) && i < N && q < N;
-          const long j = s0b[c] + 2L * nn * kb2[c] + 2L * (nn - m) - jo;
-          const R* Fj = (const R*)kp.F + j * N * N;
-          sF[(8 * c + i) * XP + q] = in ? Fj[i * N + q] : R(0);
-          xFT[(8 * c + i) * XP + q] = in ? -Fj[q * N + i] : R(0);
-        }
-      }
-      if (kp.L_sampled) {  // Lc = L(t_j) W (side by side), G = Lc Lc^T after the barrier
-        for (int e = lane; e < 2 * 64; e += 64) {
-          const int c = e >> 6, i = (e >> 3) & 7, l = e & 7;
-          const bool in = (c == 0 ? work0 : work1) && i < N && l < nu;
-          const long j = s0b[c] + 2L * nn * kb2[c] + 2L * (nn - m) - jo;
-          const R* Lj = (const R*)kp.L + j * N * nu;
-          const R* Wc = (const R*)kp.consts + (long)pb[c] * consts_count(N, nu) + consts_off_W(N, nu);
-          R a = R(0);
-          if (in)
-            for (int q = 0; q < nu; ++q) a = fma(Lj[i * nu + q], Wc[q * nu + l], a);
-          yL[i * YP + 8 * c + l] = a;
-        }
-      }
-      // publish the stage values: A (left), J (left and right), eta
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const int i = lq + 4 * t;
-        xA[(8 * b + i) * XP + lj] = tAs[t];
-        xJ[(8 * b + i) * XP + lj] = tJs[t];
-        yJ[i * YP + li] = tJs[t];
-      }
-      if (lq == 0) se[b][lj] = te;
-      wsync();
-      if (kp.L_sampled) {
-        for (int e = lane; e < 2 * 64; e += 64) {
-          const int c = e >> 6, i = (e >> 3) & 7, q = e & 7;
-          R a = R(0);
-          for (int l = 0; l < nu; ++l) a = fma(yL[i * YP + 8 * c + l], yL[q * YP + 8 * c + l], a);
-          xG[(8 * c + i) * XP + q] = a;
-        }
-        wsync();
-      }
-      // K = G J - F
-      wd4 K;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) K[r] = (r >> 1) == b ? -sF[(8 * b + lq + 4 * (r & 1)) * XP + lj] : R(0);
-#pragma unroll
-      for (int k0 = 0; k0 < 8; k0 += 4)
-        K = __builtin_amdgcn_mfma_f64_16x16x4f64(xG[li * XP + k0 + lq], yJ[(k0 + lq) * YP + li], K, 0, 0, 0);
-      // A Lc = Lc + (A - I) Lc
-      wd4 ALc;
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        ALc[r] = (r >> 1) == b ? yL[(lq + 4 * (r & 1)) * YP + li] : R(0);
-#pragma unroll
-      for (int k0 = 0; k0 < 8; k0 += 4)
-        ALc = __builtin_amdgcn_mfma_f64_16x16x4f64(xA[li * XP + k0 + lq], yL[(k0 + lq) * YP + li], ALc, 0, 0, 0);
-      // w = G eta + c: lane 16 q + li sums terms 2 q, 2 q + 1 of component lj of block b
-      R w = R(0);
-#pragma unroll
-      for (int t = 0; t < 2; ++t) w = fma(xG[(8 * b + lj) * XP + 2 * lq + t], se[b][2 * lq + t], w);
-      w += __shfl_xor(w, 16);
-      w += __shfl_xor(w, 32);
-      w += sc[b][jo][lj];
-      // publish K (right factor) and A Lc (left factor and its transpose as a right factor)
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const int i = lq + 4 * t;
-        const R kv = K[2 * b + t], av = ALc[2 * b + t];
-        yK[i * YP + li] = kv;
-        xAL[(8 * b + i) * XP + lj] = av;
-        yALT[lj * YP + 8 * b + i] = av;
-      }
-      if (lq == 0) sw[b][lj] = w;
-      wsync();
-      // kA = K + (A - I) K
-      wd4 kA = K;
-#pragma unroll
-      for (int k0 = 0; k0 < 8; k0 += 4)
-        kA = __builtin_amdgcn_mfma_f64_16x16x4f64(xA[li * XP + k0 + lq], yK[(k0 + lq) * YP + li], kA, 0, 0, 0);
-      // kJ = -Q + J K - F^T J
-      wd4 kJ;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) kJ[r] = (r >> 1) == b ? -sQ[(8 * b + lq + 4 * (r & 1)) * XP + lj] : R(0);
-#pragma unroll
-      for (int k0 = 0; k0 < 8; k0 += 4)
-        kJ = __builtin_amdgcn_mfma_f64_16x16x4f64(xJ[li * XP + k0 + lq], yK[(k0 + lq) * YP + li], kJ, 0, 0, 0);
-#pragma unroll
-      for (int k0 = 0; k0 < 8; k0 += 4)
-        kJ = __builtin_amdgcn_mfma_f64_16x16x4f64(xFT[li * XP + k0 + lq], yJ[(k0 + lq) * YP + li], kJ, 0, 0, 0);
-      // kC = -(A Lc)(A Lc)^T (nu <= 4 columns: one k-slice)
-      wd4 kC = {0.0, 0.0, 0.0, 0.0};
-      kC = __builtin_amdgcn_mfma_f64_16x16x4f64(lq < nu ? xAL[li * XP + lq] : R(0),
-                                                lq < nu ? yALT[lq * YP + li] : R(0), kC, 0, 0, 0);
-      if (nu > 4)
-        kC = __builtin_amdgcn_mfma_f64_16x16x4f64(4 + lq < nu ? xAL[li * XP + 4 + lq] : R(0),
-                                                  4 + lq < nu ? yALT[(4 + lq) * YP + li] : R(0), kC, 0, 0, 0);
-      // keta = K^T eta + J c - Q r;  kb = -(w + (A - I) w): component lj of block b, terms 2 q,
-      // 2 q + 1 on lane 16 q + li, then a butterfly over q
-      R ke = R(0), kbv = R(0);
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const int q = 2 * lq + t;
-        ke = fma(yK[q * YP + li], se[b][q], ke);
-        if (kp.has_c) ke = fma(xJ[(8 * b + lj) * XP + q], sc[b][jo][q], ke);
-        ke = fma(-sQ[(8 * b + lj) * XP + q], sr[b][jo][q], ke);
-        kbv = fma(xA[(8 * b + lj) * XP + q], sw[b][q], kbv);
-      }
-      ke += __shfl_xor(ke, 16);
-      ke += __shfl_xor(ke, 32);
-      kbv += __shfl_xor(kbv, 16);
-      kbv += __shfl_xor(kbv, 32);
-      kbv = -(kbv + sw[b][lj]);
-      // RK4 accumulation and the next stage value (this lane's block only)
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const R ka = kA[2 * b + t], kj = kJ[2 * b + t], kc = kC[2 * b + t];
-        aAs[t] = st == 0 ? fma(wk, ka, yAs[t]) : fma(wk, ka, aAs[t]);
-        aJs[t] = st == 0 ? fma(wk, kj, yJs[t]) : fma(wk, kj, aJs[t]);
-        yCs[t] = fma(-wk, kc, yCs[t]);
-        if (st < 3) {
-          tAs[t] = fma(cn, ka, yAs[t]);
-          tJs[t] = fma(cn, kj, yJs[t]);
-        }
-      }
-      ae = st == 0 ? fma(wk, ke, ye) : fma(wk, ke, ae);
-      yb = fma(wk, kbv, yb);
-      if (st < 3) te = fma(cn, ke, ye);
-      wsync();  // the next stage overwrites the operand buffers
-    }
-    // end of step: J and C take their upper entries
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int i = lq + 4 * t;
-      yAs[t] = aAs[t];
-      yJ[i * YP + li] = aJs[t];
-      yK[i * YP + li] = yCs[t];
-    }
-    ye = ae;
-    wsync();
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int i = lq + 4 * t;
-      yJs[t] = i > lj ? yJ[lj * YP + 8 * b + i] : aJs[t];
-      yCs[t] = i > lj ? yK[lj * YP + 8 * b + i] : yCs[t];
-    }
-    wsync();
-  }
-  // outputs of this lane's block (separators write their fixed element)
-  if (!liveb[b]) return;
-  const int pbl = pb[b];
-  const GRef<R> o = elt_ref(elts, kp.seg ? 0 : pbl, kb2[b], T, ne_w(N));
-  constexpr int ns = N * (N + 1) / 2;
-  constexpr int oB = N * N, oC = oB + N, oE = oC + ns, oJ = oE + N;
-  if (sepb[b]) {  // separator after problem p (see KProb): A - I = -I, b = next x0, C = 0, J = Qf
-    const R* Qf = (const R*)kp.Qf + (long)pbl * N * N;
-    const R* rf = (const R*)kp.rf + (long)pbl * N;
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int i = lq + 4 * t;
-      if (i < N && lj < N) {
-        o.g[(i * N + lj) * o.st] = i == lj ? R(-1) : R(0);
-        if (lj >= i) {
-          o.g[(oC + pk(i, lj, N)) * o.st] = R(0);
-          o.g[(oJ + pk(i, lj, N)) * o.st] = Qf[i * N + lj];
-        }
-      }
-    }
-    if (lq == 0 && lj < N) {
-      R e = R(0);
-      for (int q = 0; q < N; ++q) e = fma(Qf[lj * N + q], rf[q], e);
-      o.g[(oB + lj) * o.st] = pbl + 1 >= kp.nseg ? R(0) : ((const R*)kp.x0)[(long)(pbl + 1) * N + lj];
-      o.g[(oE + lj) * o.st] = e;
-    }
-    return;
-  }
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int i = lq + 4 * t;
-    if (i < N && lj < N) {
-      o.g[(i * N + lj) * o.st] = yAs[t];
-      if (lj >= i) {
-        o.g[(oC + pk(i, lj, N)) * o.st] = yCs[t];
-        o.g[(oJ + pk(i, lj, N)) * o.st] = yJs[t];
-      }
-    }
-  }
-  if (lq == 0 && lj < N) {
-    o.g[(oB + lj) * o.st] = yb;
-    o.g[(oE + lj) * o.st] = ye;
-  }
-}
-
-// ------------------------------------------------------------------------------------------
-// Element build at nx = 16 in FP64 on the matrix cores, one wave per block.  Every 16 x 16
-// matrix of the RK4 state (A - I, J: start value, stage value, accumulator; C: accumulator) stays
-// in registers in the result layout of v_mfma_f64_16x16x4f64 (lane 16 q + j holds entries
-// (q + 4 r, j), r = 0..3); only the stage values of A, J and the stage's K go through LDS (rows
-// padded to 17 values) to become matrix-core operands.  Per stage:
-//   publish A, J, eta  | K = G J - F (MFMA from -F),  w = G eta + c,  (A Lc) = Lc + A Lc
-//   publish K, w       | kA = K + A K,  kJ = -Q + J K - F^T J,  kC = -(A Lc)(A Lc)^T (MFMA),
-//                      | keta = K^T eta + J c - Q r,  kb = -(w + A w); RK4 updates in registers.
-// Two barriers per stage.  J and C take their upper entries after every step (as the oracle).
-// ------------------------------------------------------------------------------------------
-template <int DUMMY = 0>
-__global__ __launch_bounds__(64) void kw_build_mfma16(const KProb kp, double* __restrict__ elts) {
-  constexpr int N = 16, P = 17;
-  typedef double R;
-  __shared__ R sA[N * P], sJ[N * P], sK[N * P], sG[N * P], sF[N * P], sQ[N * P], sL[N * P],
-      sAL[N * P];
-  __shared__ R se[N], sw[N], sr[N], sc[N];
-  const int lane = lane_id(), li = lane & 15, lq = lane >> 4;
-  const int nu = kp.nu;
-  const long T = kp.T;
-  const int nn = kp.n;
-  const long k = blockIdx.x;
-  int p = blockIdx.y;
-  long s0 = (long)p * (2L * nn * T + 1), tk = (long)p * (T + 1) + k, pf = 0;
-  bool sep = false;
-  if (kp.seg) {
-    p = seg_find(kp.seg, kp.nseg, k);
-    sep = k == kp.seg[p + 1] - 1 || k == T - 1;
-    s0 = (long)p * (1 - 2L * nn);
-    tk = k;
-    pf = p;
-  }
-  const GRef<R> o = elt_ref(elts, kp.seg ? 0 : p, k, T, ne_w(N));
-  const int ns = N * (N + 1) / 2;
-  const int oB = N * N, oC = oB + N, oE = oC + ns, oJ = oE + N;
-  if (sep) {  // separator after problem p (see KProb): A - I = -I, b = next x0, C = 0, J = Qf
-    const R* Qf = (const R*)kp.Qf + (long)p * N * N;
-    const R* rf = (const R*)kp.rf + (long)p * N;
-    for (int e = lane; e < N * N; e += 64) {
-      const int i = e / N, j = e % N;
-      o.g[e * o.st] = i == j ? R(-1) : R(0);
-      if (j >= i) {
-        o.g[(oC + pk(i, j, N)) * o.st] = R(0);
-        o.g[(oJ + pk(i, j, N)) * o.st] = Qf[i * N + j];
-      }
-    }
-    if (lane < N) {
-      R e = R(0);
-      for (int q = 0; q < N; ++q) e = fma(Qf[lane * N + q], rf[q], e);
-      o.g[(oB + lane) * o.st] = p + 1 >= kp.nseg ? R(0) : ((const R*)kp.x0)[(long)(p + 1) * N + lane];
-      o.g[(oE + lane) * o.st] = e;
-    }
-    return;
-  }
-  const R* cs = (const R*)kp.consts + (long)p * consts_count(N, nu);
-  const R* Qp = (const R*)kp.Q + (long)p * N * N;
-  const R* Fc = (const R*)kp.F + pf * N * N;
-  // per-block constants in LDS: G, Q, F (constant case), Lc
-  for (int e = lane; e < N * N; e += 64) {
-    const int i = e / N, j = e % N;
-    sG[i * P + j] = cs[consts_off_G(N, nu) + e];
-    sQ[i * P + j] = Qp[e];
-    if (!kp.F_sampled) sF[i * P + j] = Fc[e];
-  }
-  for (int e = lane; e < N * nu; e += 64) sL[(e / nu) * P + e % nu] = cs[consts_off_Lc(N, nu) + e];
-  const R* W = cs + consts_off_W(N, nu);
-  const R h = (((const R*)kp.t)[tk + 1] - ((const R*)kp.t)[tk]) / R(nn);
-  // state in the MFMA result layout: entry (lq + 4 r, li)
-  R yA[4], yJ[4], yC[4], aA[4], aJ[4], tA[4], tJ[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) yA[r] = yJ[r] = yC[r] = R(0);
-  R ye = R(0), yb = R(0), ae = R(0), te = R(0);  // lanes < 16: component li
-  wsync();
-  for (int m = 0; m < nn; ++m) {
-    const long j1 = 2L * nn * k + 2L * (nn - m);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      tA[r] = yA[r];
-      tJ[r] = yJ[r];
-    }
-    te = ye;
-    for (int st = 0; st < 4; ++st) {
-      const long j = st == 0 ? j1 : (st == 3 ? j1 - 2 : j1 - 1);
-      const R wk = (st == 0 || st == 3) ? -h / R(6) : -h / R(3);
-      const R cn = st == 2 ? -h : -h / R(2);
-      // samples of this stage; stage values of A, J, eta as operands
-      if (lane < N) {
-        sr[lane] = ((const R*)kp.r)[(s0 + j) * N + lane];
-        sc[lane] = kp.has_c ? ((const R*)kp.c)[(s0 + j) * N + lane] : R(0);
-        se[lane] = te;
-      }
-      if (kp.F_sampled) {
-        const R* Fj = (const R*)kp.F + (s0 + j) * N * N;
-        for (int e = lane; e < N * N; e += 64) sF[(e / N) * P + e % N] = Fj[e];
-      }
-      if (kp.L_sampled) {  // Lc = L(t_j) W, G = Lc Lc^T
-        const R* Lj = (const R*)kp.L + (s0 + j) * N * nu;
-        for (int e = lane; e < N * nu; e += 64) {
-          const int i = e / nu, l = e % nu;
-          R a = R(0);
-          for (int q = 0; q < nu; ++q) a = fma(Lj[i * nu + q], W[q * nu + l], a);
-          sL[i * P + l] = a;
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        sA[(lq + 4 * r) * P + li] = tA[r];
-        sJ[(lq + 4 * r) * P + li] = tJ[r];
-      }
-      wsync();
-      if (kp.L_sampled) {
-        for (int e = lane; e < N * N; e += 64) {
-          const int i = e / N, q = e % N;
-          R a = R(0);
-          for (int l = 0; l < nu; ++l) a = fma(sL[i * P + l], sL[q * P + l], a);
-          sG[i * P + q] = a;
-        }
-        wsync();
-      }
-      // K = G J - F
-      wd4 K;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) K[r] = -sF[(lq + 4 * r) * P + li];
-#pragma unroll
-      for (int k0 = 0; k0 < N; k0 += 4) {
-        const int kk = k0 + lq;
-        K = __builtin_amdgcn_mfma_f64_16x16x4f64(sG[li * P + kk], sJ[kk * P + li], K, 0, 0, 0);
-      }
-      // w = G eta + c: lanes 16 q + i sum terms 4 q .. 4 q + 3 of component i, then a butterfly
-      R w = R(0);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) w = fma(sG[li * P + 4 * lq + t], se[4 * lq + t], w);
-      w += __shfl_xor(w, 16);
-      w += __shfl_xor(w, 32);
-      w += sc[li];
-      // A Lc = Lc + (A - I) Lc on the matrix cores (Lc padded to 16 columns with zeros)
-      wd4 ALc;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) ALc[r] = li < nu ? sL[(lq + 4 * r) * P + li] : R(0);
-#pragma unroll
-      for (int k0 = 0; k0 < N; k0 += 4) {
-        const int kk = k0 + lq;
-        ALc = __builtin_amdgcn_mfma_f64_16x16x4f64(sA[li * P + kk], li < nu ? sL[kk * P + li] : R(0),
-                                                   ALc, 0, 0, 0);
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        sK[(lq + 4 * r) * P + li] = K[r];
-        sAL[(lq + 4 * r) * P + li] = ALc[r];
-      }
-      if (lane < N) sw[lane] = w;
-      wsync();
-      // (A Lc)(li, 4 kb + lq): this lane's operand of both factors of -(A Lc)(A Lc)^T
-      R AL[4];
-#pragma unroll
-      for (int kb = 0; kb < 4; ++kb) AL[kb] = 4 * kb + lq < nu ? sAL[li * P + 4 * kb + lq] : R(0);
-      // kA = K + (A - I) K
-      wd4 kA = K;
-#pragma unroll
-      for (int k0 = 0; k0 < N; k0 += 4) {
-        const int kk = k0 + lq;
-        kA = __builtin_amdgcn_mfma_f64_16x16x4f64(sA[li * P + kk], sK[kk * P + li], kA, 0, 0, 0);
-      }
-      // kJ = -Q + J K - F^T J
-      wd4 kJ;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) kJ[r] = -sQ[(lq + 4 * r) * P + li];
-#pragma unroll
-      for (int k0 = 0; k0 < N; k0 += 4) {
-        const int kk = k0 + lq;
-        kJ = __builtin_amdgcn_mfma_f64_16x16x4f64(sJ[li * P + kk], sK[kk * P + li], kJ, 0, 0, 0);
-      }
-#pragma unroll
-      for (int k0 = 0; k0 < N; k0 += 4) {
-        const int kk = k0 + lq;
-        kJ = __builtin_amdgcn_mfma_f64_16x16x4f64(-sF[kk * P + li], sJ[kk * P + li], kJ, 0, 0, 0);
-      }
-      // kC = -(A Lc)(A Lc)^T: operand (li, 4 kb + lq) of both factors is this lane's AL[kb]
-      wd4 kC = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int kb = 0; kb < 4; ++kb)
-        if (4 * kb < nu) kC = __builtin_amdgcn_mfma_f64_16x16x4f64(AL[kb], AL[kb], kC, 0, 0, 0);
-      // keta = K^T eta + J c - Q r;  kb = -(w + (A - I) w): component li, terms 4 lq .. 4 lq + 3
-      // on lane 16 lq + li, then a butterfly over lq
-      R ke = R(0), kbv = R(0);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int q = 4 * lq + t;
-        ke = fma(sK[q * P + li], se[q], ke);
-        if (kp.has_c) ke = fma(sJ[li * P + q], sc[q], ke);
-        ke = fma(-sQ[li * P + q], sr[q], ke);
-        kbv = fma(sA[li * P + q], sw[q], kbv);
-      }
-      ke += __shfl_xor(ke, 16);
-      ke += __shfl_xor(ke, 32);
-      kbv += __shfl_xor(kbv, 16);
-      kbv += __shfl_xor(kbv, 32);
-      kbv = -(kbv + sw[li]);
-      // RK4 accumulation and the next stage value
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        aA[r] = st == 0 ? fma(wk, kA[r], yA[r]) : fma(wk, kA[r], aA[r]);
-        aJ[r] = st == 0 ? fma(wk, kJ[r], yJ[r]) : fma(wk, kJ[r], aJ[r]);
-        yC[r] = fma(-wk, kC[r], yC[r]);
-        if (st < 3) {
-          tA[r] = fma(cn, kA[r], yA[r]);
-          tJ[r] = fma(cn, kJ[r], yJ[r]);
-        }
-      }
-      ae = st == 0 ? fma(wk, ke, ye) : fma(wk, ke, ae);
-      yb = fma(wk, kbv, yb);
-      if (st < 3) te = fma(cn, ke, ye);
-      wsync();  // the next stage overwrites the operand buffers
-    }
-    // end of step: J and C take their upper entries
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      yA[r] = aA[r];
-      sJ[(lq + 4 * r) * P + li] = aJ[r];
-      sK[(lq + 4 * r) * P + li] = yC[r];
-    }
-    ye = ae;
-    wsync();
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = lq + 4 * r;
-      yJ[r] = i > li ? sJ[li * P + i] : aJ[r];
-      yC[r] = i > li ? sK[li * P + i] : yC[r];
-    }
-    wsync();
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int i = lq + 4 * r;
-    o.g[(i * N + li) * o.st] = yA[r];
-    if (li >= i) {
-      o.g[(oC + pk(i, li, N)) * o.st] = yC[r];
-      o.g[(oJ + pk(i, li, N)) * o.st] = yJ[r];
-    }
-  }
-  if (lane < N) {
-    o.g[(oB + lane) * o.st] = yb;
-    o.g[(oE + lane) * o.st] = ye;
-  }
-}
-
-// ------------------------------------------------------------------------------------------
 // Value tree.  The kernels below are thin launches of device bodies that take their node and
 // problem, LDS and access policy A (coherent.hpp) from the caller: A applies to the tree records,
 // S, v and x0 passed between the bodies (elements, written by an earlier launch, are plain loads),
@@ -1919,160 +1091,55 @@ template <int N>
 struct WSh {  // LDS of the bodies (values of the solve's type)
   static constexpr int kTupW = 3 * N * N + 2 * N, kScr = 4 * N * N + N * (2 * N + 1) + 2 * N;
   static constexpr int vreduce = 2 * kTupW + kScr;
-  static constexpr int vfold = kTupW + kScr + N * N + N;
-  static constexpr int vbottom = vfold + 3 * (N * N + N);
-  static constexpr int treduce = 3 * (N * N + N);
-  static constexpr int tsweep = N * N + 3 * N;
+  static constexpr int treduce = kTupW + kScr + N * N + N + 3 * (N * N + N);
   static constexpr int tbottom = kTupW + kScr + N * N + N + N * N + 4 * N + N * N;
-  static constexpr int max2(int a, int b) { return a > b ? a : b; }
-  static constexpr int all =
-      max2(max2(max2(vreduce, vfold), max2(vbottom, treduce)), max2(tsweep, tbottom));
 };
 
-// Value records (S full symmetric, v): n^2 + n values.
-template <class A = PlainAcc, class R>
-WDEV void val_st(const R* S, const R* v, R* g, int n) {
-  for (int e = lane_id(); e < n * n; e += 64) A::st(g + e, S[e]);
-  for (int i = lane_id(); i < n; i += 64) A::st(g + n * n + i, v[i]);
-  wsync();
-}
-template <class A = PlainAcc, class R>
-WDEV void val_ld(R* S, R* v, const R* g, int n) {
-  for (int e = lane_id(); e < n * n; e += 64) S[e] = A::ld(g + e);
-  for (int i = lane_id(); i < n; i += 64) v[i] = A::ld(g + n * n + i);
-  wsync();
-}
-
 // Map records (P = Psi - I, q = alpha): n^2 + n values.
-template <class A = PlainAcc, class R>
-WDEV void map_ld(R* P, R* q, const R* g, int n) {
-  for (int e = lane_id(); e < n * n; e += 64) P[e] = A::ld(g + e);
-  for (int i = lane_id(); i < n; i += 64) q[i] = A::ld(g + n * n + i);
-  wsync();
-}
-template <class A = PlainAcc, class R>
+template <class R>
 WDEV void map_st(const R* P, const R* q, R* g, int n) {
-  for (int e = lane_id(); e < n * n; e += 64) A::st(g + e, P[e]);
-  for (int i = lane_id(); i < n; i += 64) A::st(g + n * n + i, q[i]);
+  for (int e = lane_id(); e < n * n; e += 64) g[e] = P[e];
+  for (int i = lane_id(); i < n; i += 64) g[n * n + i] = q[i];
   wsync();
 }
 
 // Node i of level l + 1: the product of the wc nodes i wc .. of level l (elements when
 // src_elts), right to left.
-template <int N, class A, class R>
-WDEV void wb_vreduce(R* sh, int* piv, int p, long i, int wc, int src_elts, const R* src,
-                     long n_src, R* dst, long n_dst) {
+template <int N, class R>
+__global__ __launch_bounds__(64) void kw_vreduce(int wc, int src_elts, const R* __restrict__ src,
+                                                 long n_src, R* __restrict__ dst, long n_dst) {
   constexpr int n = N, kTupW = WSh<N>::kTupW;
-  const int NE = ne_w(n);
+  __shared__ R sh[WSh<N>::vreduce];
+  __shared__ int piv;
+  if ((long)blockIdx.x >= n_dst) return;
+  const int p = blockIdx.y, NE = ne_w(n);
+  const long i = blockIdx.x;
   WT<R> acc = wt_at(sh, n), x = wt_at(sh + kTupW, n);
-  WS<R> scr = ws_at(sh + 2 * kTupW, piv, n);
+  WS<R> scr = ws_at(sh + 2 * kTupW, &piv, n);
   const long j0 = i * wc, j1 = min(j0 + wc, n_src);
   auto load = [&](WT<R> t, long j) {
-    if (src_elts)
-      wt_load<PlainAcc>(t, elt_ref(src, p, j, n_src, NE), n);
-    else
-      wt_load<A>(t, rec_ref(src, p, j, n_src, NE), n);
+    wt_load(t, src_elts ? elt_ref(src, p, j, n_src, NE) : rec_ref(src, p, j, n_src, NE), n);
   };
   load(acc, j1 - 1);
   for (long j = j1 - 2; j >= j0; --j) {
     load(x, j);
     w_combine<N>(x, acc, acc, scr, n);
   }
-  wt_store<A>(acc, rec_ref(dst, p, i, n_dst, NE), n);
+  wt_store(acc, rec_ref(dst, p, i, n_dst, NE), n);
 }
 
-template <int N, class R>
-__global__ __launch_bounds__(64) void kw_vreduce(int, int wc, int src_elts,
-                                                 const R* __restrict__ src, long n_src,
-                                                 R* __restrict__ dst, long n_dst) {
-  __shared__ R sh[WSh<N>::vreduce];
-  __shared__ int piv;
-  if ((long)blockIdx.x >= n_dst) return;
-  wb_vreduce<N, PlainAcc>(sh, &piv, blockIdx.y, blockIdx.x, wc, src_elts, src, n_src, dst, n_dst);
-}
-
-// The values at the right ends of the n_top top nodes: the terminal value carried leftwards.
-template <int N, class A, class R>
-WDEV void wb_vtop(R* sh, int* piv, const KProb& kp, int p, const R* tup, long n_top, R* val) {
-  constexpr int n = N, kTupW = WSh<N>::kTupW, kScr = WSh<N>::kScr;
-  const int NE = ne_w(n);
-  WT<R> a = wt_at(sh, n);
-  WS<R> scr = ws_at(sh + kTupW, piv, n);
-  R* S = sh + kTupW + kScr;
-  R* v = S + n * n;
-  const R* Qf = (const R*)kp.Qf + (long)p * n * n;
-  const R* rf = (const R*)kp.rf + (long)p * n;
-  for (int e = lane_id(); e < n * n; e += 64) {
-    const int i = e / n, j = e % n;
-    S[e] = Qf[(i < j ? i : j) * n + (i < j ? j : i)];
-  }
-  for (int i = lane_id(); i < n; i += 64) {
-    R t = R(0);
-    for (int j = 0; j < n; ++j) t = fma(Qf[i * n + j], rf[j], t);
-    v[i] = t;
-  }
-  wsync();
-  const int VR = n * n + n;
-  for (long j = n_top - 1; j >= 0; --j) {
-    val_st<A>(S, v, val + ((long)p * n_top + j) * VR, n);
-    if (j == 0) break;
-    wt_load<A>(a, rec_ref(tup, p, j, n_top, NE), n);
-    w_fold<N>(a, S, v, scr, n, (R*)nullptr, (R*)nullptr);
-  }
-}
-
-template <int N, class R>
-__global__ __launch_bounds__(64) void kw_vtop(const KProb kp, const R* __restrict__ tup, long n_top,
-                                              R* __restrict__ val) {
-  __shared__ R sh[WSh<N>::vfold];
-  __shared__ int piv;
-  wb_vtop<N, PlainAcc>(sh, &piv, kp, blockIdx.y, tup, n_top, val);
-}
-
-// Values at the right ends of the children of node i of level l + 1, from the node's own.
-template <int N, class A, class R>
-WDEV void wb_vdown(R* sh, int* piv, int p, long i, int wc, const R* tup, long n_child,
-                   const R* val_in, long n_par, R* val_out) {
-  constexpr int n = N, kTupW = WSh<N>::kTupW, kScr = WSh<N>::kScr;
-  const int NE = ne_w(n), VR = n * n + n;
-  WT<R> a = wt_at(sh, n);
-  WS<R> scr = ws_at(sh + kTupW, piv, n);
-  R* S = sh + kTupW + kScr;
-  R* v = S + n * n;
-  val_ld<A>(S, v, val_in + ((long)p * n_par + i) * VR, n);
-  const long j0 = i * wc, j1 = min(j0 + wc, n_child);
-  for (long j = j1 - 1; j >= j0; --j) {
-    val_st<A>(S, v, val_out + ((long)p * n_child + j) * VR, n);
-    if (j == j0) break;
-    wt_load<A>(a, rec_ref(tup, p, j, n_child, NE), n);
-    w_fold<N>(a, S, v, scr, n, (R*)nullptr, (R*)nullptr);
-  }
-}
-
-template <int N, class R>
-__global__ __launch_bounds__(64) void kw_vdown(int, int wc, const R* __restrict__ tup, long n_child,
-                                               const R* __restrict__ val_in, long n_par,
-                                               R* __restrict__ val_out) {
-  __shared__ R sh[WSh<N>::vfold];
-  __shared__ int piv;
-  if ((long)blockIdx.x >= n_par) return;
-  wb_vdown<N, PlainAcc>(sh, &piv, blockIdx.y, blockIdx.x, wc, tup, n_child, val_in, n_par,
-                        val_out);
-}
-
-// Two-wave form of a value-tree level above the leaves, for levels of few nodes (each node's
+// Two-wave form of a level of Method 2's tree above the leaves, for levels of few nodes (each node's
 // chain of combinations, not the device's throughput, sets their time).  Node i of level l + 1
 // from its four children t0 .. t3 of level l: wave 0 forms t0 (x) t1 while wave 1 forms
 // t2 (x) t3, then wave 0 combines the two (the Lemma 7 combination is associative), two
-// combinations deep instead of three.  Wave 1 also writes t2 (x) t3 over t2's record, where the
-// down-sweep of the same level (kw_vdown2) reads it: that sweep needs the pair product and not
-// t2.  A node with fewer children (the last of a level) takes the sequential product on both
-// waves and wave 0 stores it.  Where one wave has a step the other lacks, the other repeats a
-// step of the same kind on its own LDS copy or takes the barrier alone, so both pass the same
-// barriers; the wave index is made wave-uniform (readfirstlane), so such branches are scalar.
-// LEFT: keep t0 (x) t1 over t1's record instead, for Method 2's down-sweep (kw_m2_down2), which
-// builds prefixes from the left and needs t0, the left pair and t2.
-template <int N, class R, bool LEFT = false>
+// combinations deep instead of three.  Wave 0 also writes t0 (x) t1 over t1's record, where the
+// down-sweep of the same level (kw_m2_down2) reads it: that sweep builds prefixes from the left
+// and needs t0, the left pair and t2.  A node with fewer children (the last of a level) takes the
+// sequential product on both waves and wave 0 stores it.  Where one wave has a step the other
+// lacks, the other repeats a step of the same kind on its own LDS copy or takes the barrier alone,
+// so both pass the same barriers; the wave index is made wave-uniform (readfirstlane), so such
+// branches are scalar.
+template <int N, class R>
 __global__ __launch_bounds__(128) void kw_vreduce2(int wc, R* __restrict__ src, long n_src,
                                                    R* __restrict__ dst, long n_dst) {
   constexpr int n = N, kTupW = WSh<N>::kTupW;
@@ -2088,11 +1155,11 @@ __global__ __launch_bounds__(128) void kw_vreduce2(int wc, R* __restrict__ src, 
   const long j0 = i * wc, j1 = min(j0 + wc, n_src);
   if (j1 - j0 == 4) {
     const long ja = j0 + 2 * w;
-    wt_load<PlainAcc>(x, rec_ref(in, p, ja, n_src, NE), n);
-    wt_load<PlainAcc>(acc, rec_ref(in, p, ja + 1, n_src, NE), n);
+    wt_load(x, rec_ref(in, p, ja, n_src, NE), n);
+    wt_load(acc, rec_ref(in, p, ja + 1, n_src, NE), n);
     w_combine<N>(x, acc, acc, scr, n);  // wave w: t_2w (x) t_2w+1
-    if (w == (LEFT ? 0 : 1))
-      wt_store<PlainAcc>(acc, rec_ref(src, p, LEFT ? j0 + 1 : j0 + 2, n_src, NE), n);
+    if (w == 0)
+      wt_store(acc, rec_ref(src, p, j0 + 1, n_src, NE), n);
     else
       wsync();
     // wave 0: (t0 t1) (x) (t2 t3) from wave 1's LDS; wave 1: a combination of its own copy of t2
@@ -2100,123 +1167,16 @@ __global__ __launch_bounds__(128) void kw_vreduce2(int wc, R* __restrict__ src, 
     const WT<R> right = wt_at(sh[1], n);
     w_combine<N>(w == 0 ? acc : x, w == 0 ? right : x, w == 0 ? acc : x, scr, n);
   } else {
-    wt_load<PlainAcc>(acc, rec_ref(in, p, j1 - 1, n_src, NE), n);
+    wt_load(acc, rec_ref(in, p, j1 - 1, n_src, NE), n);
     for (long j = j1 - 2; j >= j0; --j) {
-      wt_load<PlainAcc>(x, rec_ref(in, p, j, n_src, NE), n);
+      wt_load(x, rec_ref(in, p, j, n_src, NE), n);
       w_combine<N>(x, acc, acc, scr, n);
     }
   }
   if (w == 0)
-    wt_store<PlainAcc>(acc, rec_ref(dst, p, i, n_dst, NE), n);
+    wt_store(acc, rec_ref(dst, p, i, n_dst, NE), n);
   else
     wsync();
-}
-
-// Down-sweep of a level reduced by kw_vreduce2: the values at the right ends of node i's children
-// from the node's own.  With four children, wave 0 stores the node's value as child 3's and folds
-// t3 into it (child 2) while wave 1 folds the pair product t2 (x) t3 (child 1) and then t1 (child
-// 0): two folds deep instead of three.  Fewer children: the sequential sweep on both waves, wave 0
-// storing.  Barriers as in kw_vreduce2.
-template <int N, class R>
-__global__ __launch_bounds__(128) void kw_vdown2(int wc, const R* __restrict__ tup, long n_child,
-                                                 const R* __restrict__ val_in, long n_par,
-                                                 R* __restrict__ val_out) {
-  constexpr int n = N, kTupW = WSh<N>::kTupW, kScr = WSh<N>::kScr;
-  __shared__ R sh[2][WSh<N>::vfold];
-  __shared__ int piv[2];
-  if ((long)blockIdx.x >= n_par) return;
-  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int p = blockIdx.y, NE = ne_w(n), VR = n * n + n;
-  const long i = blockIdx.x;
-  WT<R> a = wt_at(sh[w], n);
-  WS<R> scr = ws_at(sh[w] + kTupW, &piv[w], n);
-  R* S = sh[w] + kTupW + kScr;
-  R* v = S + n * n;
-  R* out = val_out + (long)p * n_child * VR;
-  val_ld<PlainAcc>(S, v, val_in + ((long)p * n_par + i) * VR, n);
-  const long j0 = i * wc, j1 = min(j0 + wc, n_child);
-  if (j1 - j0 == 4) {
-    if (w == 0)
-      val_st<PlainAcc>(S, v, out + (j0 + 3) * VR, n);
-    else
-      wsync();
-    // wave 0: t3 (child 2); wave 1: the pair product t2 (x) t3 in t2's slot (child 1)
-    wt_load<PlainAcc>(a, rec_ref(tup, p, w == 0 ? j0 + 3 : j0 + 2, n_child, NE), n);
-    w_fold<N>(a, S, v, scr, n, (R*)nullptr, (R*)nullptr);
-    val_st<PlainAcc>(S, v, out + (w == 0 ? j0 + 2 : j0 + 1) * VR, n);
-    // wave 1: t1 (child 0); wave 0 folds the same record into its own copy, discarded
-    wt_load<PlainAcc>(a, rec_ref(tup, p, j0 + 1, n_child, NE), n);
-    w_fold<N>(a, S, v, scr, n, (R*)nullptr, (R*)nullptr);
-    if (w == 1)
-      val_st<PlainAcc>(S, v, out + j0 * VR, n);
-    else
-      wsync();
-  } else {
-    for (long j = j1 - 1; j >= j0; --j) {
-      if (w == 0)
-        val_st<PlainAcc>(S, v, out + j * VR, n);
-      else
-        wsync();
-      if (j == j0) break;
-      wt_load<PlainAcc>(a, rec_ref(tup, p, j, n_child, NE), n);
-      w_fold<N>(a, S, v, scr, n, (R*)nullptr, (R*)nullptr);
-    }
-  }
-}
-
-// Values of every block from the value at the right end of each chunk; level 1 of the
-// trajectory tree (composition of the chunk's block maps) when maps1 != nullptr, and every
-// block's closed-loop map ([batch][T] records P = Psi - I, q = alpha; the fold computes it on the
-// way) when bmaps != nullptr.
-template <int N, class A, class R>
-WDEV void wb_vbottom(R* sh, int* piv, const KProb& kp, int p, long i, int wc, const R* elts,
-                     const R* val1, long n1, R* Sout, R* vout, R* maps1, R* bmaps) {
-  constexpr int n = N, kTupW = WSh<N>::kTupW, kScr = WSh<N>::kScr;
-  const long T = kp.T;
-  const int NE = ne_w(n), VR = n * n + n, MR = n * n + n;
-  WT<R> a = wt_at(sh, n);
-  WS<R> scr = ws_at(sh + kTupW, piv, n);
-  R* S = sh + kTupW + kScr;
-  R* v = S + n * n;
-  R* aP = v + n;
-  R* aq = aP + n * n;
-  R* mP = aq + n;
-  R* mq = mP + n * n;
-  R* tmp = mq + n;
-  val_ld<A>(S, v, val1 + ((long)p * n1 + i) * VR, n);
-  R* Sp = Sout + (long)p * (T + 1) * n * n;
-  R* vp = vout + (long)p * (T + 1) * n;
-  const long j0 = i * wc, j1 = min(j0 + wc, T);
-  if (j1 == T && !kp.seg) {
-    for (int e = lane_id(); e < n * n; e += 64) A::st(Sp + T * n * n + e, S[e]);
-    for (int q = lane_id(); q < n; q += 64) A::st(vp + T * n + q, v[q]);
-  }
-  w_aff_identity(aP, aq, n);
-  for (long k = j1 - 1; k >= j0; --k) {
-    wt_load<PlainAcc>(a, elt_ref(elts, p, k, T, NE), n);
-    w_fold<N>(a, S, v, scr, n, mP, mq);
-    for (int e = lane_id(); e < n * n; e += 64) A::st(Sp + k * n * n + e, S[e]);
-    for (int q = lane_id(); q < n; q += 64) A::st(vp + k * n + q, v[q]);
-    if (bmaps) map_st<A>(mP, mq, bmaps + ((long)p * T + k) * MR, n);
-    if (maps1) w_aff_after(aP, aq, mP, mq, tmp, n);
-  }
-  if (maps1) {
-    R* g = maps1 + ((long)p * n1 + i) * MR;
-    for (int e = lane_id(); e < n * n; e += 64) A::st(g + e, aP[e]);
-    for (int q = lane_id(); q < n; q += 64) A::st(g + n * n + q, aq[q]);
-  }
-}
-
-template <int N, class R>
-__global__ __launch_bounds__(64) void kw_vbottom(const KProb kp, int wc, const R* __restrict__ elts,
-                                                 const R* __restrict__ val1, long n1,
-                                                 R* __restrict__ Sout, R* __restrict__ vout,
-                                                 R* __restrict__ maps1, R* __restrict__ bmaps) {
-  __shared__ R sh[WSh<N>::vbottom];
-  __shared__ int piv;
-  if ((long)blockIdx.x >= n1) return;
-  wb_vbottom<N, PlainAcc>(sh, &piv, kp, blockIdx.y, blockIdx.x, wc, elts, val1, n1, Sout, vout,
-                          maps1, bmaps);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2287,11 +1247,11 @@ WDEV void w_m2_state(const R* Ad, const R* b, const R* C, const R* xk, const R* 
 
 // (S_{k+1}, v_{k+1}) into LDS; zeros for the last block in ragged mode (a separator, whose map
 // does not depend on them; row T does not exist there).
-template <class A = PlainAcc, class R>
+template <class R>
 WDEV void w_right_value(const KProb& kp, const R* Sp, const R* vp, long k, R* S, R* v, int n) {
   const bool none = kp.seg && k + 1 >= kp.T;
-  for (int e = lane_id(); e < n * n; e += 64) S[e] = none ? R(0) : A::ld(Sp + (k + 1) * n * n + e);
-  for (int q = lane_id(); q < n; q += 64) v[q] = none ? R(0) : A::ld(vp + (k + 1) * n + q);
+  for (int e = lane_id(); e < n * n; e += 64) S[e] = none ? R(0) : Sp[(k + 1) * n * n + e];
+  for (int q = lane_id(); q < n; q += 64) v[q] = none ? R(0) : vp[(k + 1) * n + q];
   wsync();
 }
 
@@ -2301,7 +1261,7 @@ __global__ __launch_bounds__(64) void kw_tbottom_reduce(const KProb kp, int wc, 
                                                         const R* __restrict__ vg,
                                                         R* __restrict__ maps1, long n1) {
   constexpr int kTupW = WSh<N>::kTupW, kScr = WSh<N>::kScr;
-  __shared__ R sh[WSh<N>::vbottom];
+  __shared__ R sh[WSh<N>::treduce];
   __shared__ int piv;
   const int p = blockIdx.y;
   const long i = blockIdx.x;
@@ -2331,103 +1291,24 @@ __global__ __launch_bounds__(64) void kw_tbottom_reduce(const KProb kp, int wc, 
   map_st(aP, aq, maps1 + ((long)p * n1 + i) * MR, n);
 }
 
-// Map of node i of level l + 1: the composition of the wc maps i wc .. of level l (time order).
-template <int N, class A, class R>
-WDEV void wb_treduce(R* sh, int p, long i, int wc, const R* src, long n_src, R* dst, long n_dst) {
-  constexpr int n = N;
-  const int MR = n * n + n;
-  R* aP = sh;
-  R* aq = aP + n * n;
-  R* mP = aq + n;
-  R* mq = mP + n * n;
-  R* tmp = mq + n;
-  const long j0 = i * wc, j1 = min(j0 + wc, n_src);
-  map_ld<A>(aP, aq, src + ((long)p * n_src + j0) * MR, n);
-  for (long j = j0 + 1; j < j1; ++j) {
-    map_ld<A>(mP, mq, src + ((long)p * n_src + j) * MR, n);
-    w_aff_then(aP, aq, mP, mq, tmp, n);
-  }
-  map_st<A>(aP, aq, dst + ((long)p * n_dst + i) * MR, n);
-}
-
+// x_k and u_k = -R^{-1} L(t_k)^T (S_k x_k - v_k) of every block of a chunk, the block maps
+// computed from the elements and S, v.
 template <int N, class R>
-__global__ __launch_bounds__(64) void kw_treduce(int, int wc, const R* __restrict__ src, long n_src,
-                                                 R* __restrict__ dst, long n_dst) {
-  __shared__ R sh[WSh<N>::treduce];
-  if ((long)blockIdx.x >= n_dst) return;
-  wb_treduce<N, PlainAcc>(sh, blockIdx.y, blockIdx.x, wc, src, n_src, dst, n_dst);
-}
-
-// x at the left ends of the n_top top nodes: x0 carried rightwards.
-template <int N, class A, class R>
-WDEV void wb_ttop(R* sh, const KProb& kp, int p, const R* maps, long n_top, R* xs) {
-  constexpr int n = N;
-  const int MR = n * n + n;
-  R* mP = sh;
-  R* mq = mP + n * n;
-  R* x = mq + n;
-  R* tmp = x + n;
-  for (int q = lane_id(); q < n; q += 64) x[q] = ((const R*)kp.x0)[(long)p * n + q];
-  wsync();
-  for (long j = 0; j < n_top; ++j) {
-    for (int q = lane_id(); q < n; q += 64) A::st(xs + ((long)p * n_top + j) * n + q, x[q]);
-    if (j == n_top - 1) break;
-    map_ld<A>(mP, mq, maps + ((long)p * n_top + j) * MR, n);
-    w_aff_apply(mP, mq, x, tmp, n);
-  }
-  wsync();
-}
-
-template <int N, class R>
-__global__ __launch_bounds__(64) void kw_ttop(const KProb kp, const R* __restrict__ maps, long n_top,
-                                              R* __restrict__ xs) {
-  __shared__ R sh[WSh<N>::tsweep];
-  wb_ttop<N, PlainAcc>(sh, kp, blockIdx.y, maps, n_top, xs);
-}
-
-// x at the left ends of the children of node i of level l + 1, from the node's own.
-template <int N, class A, class R>
-WDEV void wb_tdown(R* sh, int p, long i, int wc, const R* maps, long n_child, const R* x_in,
-                   long n_par, R* x_out) {
-  constexpr int n = N;
-  const int MR = n * n + n;
-  R* mP = sh;
-  R* mq = mP + n * n;
-  R* x = mq + n;
-  R* tmp = x + n;
-  for (int q = lane_id(); q < n; q += 64) x[q] = A::ld(x_in + ((long)p * n_par + i) * n + q);
-  wsync();
-  const long j0 = i * wc, j1 = min(j0 + wc, n_child);
-  for (long j = j0; j < j1; ++j) {
-    for (int q = lane_id(); q < n; q += 64) A::st(x_out + ((long)p * n_child + j) * n + q, x[q]);
-    if (j == j1 - 1) break;
-    map_ld<A>(mP, mq, maps + ((long)p * n_child + j) * MR, n);
-    w_aff_apply(mP, mq, x, tmp, n);
-  }
-  wsync();
-}
-
-template <int N, class R>
-__global__ __launch_bounds__(64) void kw_tdown(int, int wc, const R* __restrict__ maps, long n_child,
-                                               const R* __restrict__ x_in, long n_par,
-                                               R* __restrict__ x_out) {
-  __shared__ R sh[WSh<N>::tsweep];
-  if ((long)blockIdx.x >= n_par) return;
-  wb_tdown<N, PlainAcc>(sh, blockIdx.y, blockIdx.x, wc, maps, n_child, x_in, n_par, x_out);
-}
-
-// x_k and u_k = -R^{-1} L(t_k)^T (S_k x_k - v_k) of every block of a chunk; the block maps are
-// loaded from bmaps (see wb_vbottom) when given, else computed from the elements and S, v.
-template <int N, class A, class R>
-WDEV void wb_tbottom(R* sh, int* piv, const KProb& kp, int p, long i, int wc, const R* elts,
-                     const R* Sg, const R* vg, const R* x1, long n1, R* xout, R* uout,
-                     const R* bmaps) {
+__global__ __launch_bounds__(64) void kw_tbottom(const KProb kp, int wc, const R* __restrict__ elts,
+                                                 const R* __restrict__ Sg, const R* __restrict__ vg,
+                                                 const R* __restrict__ x1, long n1,
+                                                 R* __restrict__ xout, R* __restrict__ uout) {
   constexpr int n = N, kTupW = WSh<N>::kTupW, kScr = WSh<N>::kScr;
+  __shared__ R sh[WSh<N>::tbottom];
+  __shared__ int piv;
+  if ((long)blockIdx.x >= n1) return;
+  const int p = blockIdx.y;
+  const long i = blockIdx.x;
   const int nu = kp.nu;
   const long T = kp.T;
   const int NE = ne_w(n);
   WT<R> a = wt_at(sh, n);
-  WS<R> scr = ws_at(sh + kTupW, piv, n);
+  WS<R> scr = ws_at(sh + kTupW, &piv, n);
   R* S = sh + kTupW + kScr;
   R* v = S + n * n;
   R* mP = v + n;
@@ -2440,7 +1321,7 @@ WDEV void wb_tbottom(R* sh, int* piv, const KProb& kp, int p, long i, int wc, co
   const R* vp = vg + (long)p * (T + 1) * n;
   R* xp = xout + (long)p * (T + 1) * n;
   R* up = uout ? uout + (long)p * (T + 1) * nu : nullptr;
-  for (int q = lane_id(); q < n; q += 64) x[q] = A::ld(x1 + ((long)p * n1 + i) * n + q);
+  for (int q = lane_id(); q < n; q += 64) x[q] = x1[((long)p * n1 + i) * n + q];
   wsync();
   const long j0 = i * wc, j1 = min(j0 + wc, T);
   auto control = [&](long k) {
@@ -2450,8 +1331,8 @@ WDEV void wb_tbottom(R* sh, int* piv, const KProb& kp, int p, long i, int wc, co
     const long s0 = kp.seg ? (long)pk * (1 - 2L * kp.n) : (long)p * (2L * kp.n * T + 1);
     w_gain(kp, pk, s0 + 2L * kp.n * k, Kc, n, nu);
     for (int r = lane_id(); r < n; r += 64) {
-      R s = -A::ld(vp + k * n + r);
-      for (int j = 0; j < n; ++j) s = fma(A::ld(Sp + k * n * n + r * n + j), x[j], s);
+      R s = -vp[k * n + r];
+      for (int j = 0; j < n; ++j) s = fma(Sp[k * n * n + r * n + j], x[j], s);
       g[r] = s;
     }
     wsync();
@@ -2465,32 +1346,15 @@ WDEV void wb_tbottom(R* sh, int* piv, const KProb& kp, int p, long i, int wc, co
   for (long k = j0; k < j1; ++k) {
     for (int q = lane_id(); q < n; q += 64) xp[k * n + q] = x[q];
     control(k);
-    if (bmaps) {
-      map_ld<A>(mP, mq, bmaps + ((long)p * T + k) * (n * n + n), n);
-    } else {
-      wt_load<PlainAcc>(a, elt_ref(elts, p, k, T, NE), n);
-      w_right_value<A>(kp, Sp, vp, k, S, v, n);
-      w_block_map<N>(a, S, v, scr, n, mP, mq);
-    }
+    wt_load(a, elt_ref(elts, p, k, T, NE), n);
+    w_right_value(kp, Sp, vp, k, S, v, n);
+    w_block_map<N>(a, S, v, scr, n, mP, mq);
     w_aff_apply(mP, mq, x, tmp, n);
   }
   if (j1 == T && !kp.seg) {
     for (int q = lane_id(); q < n; q += 64) xp[T * n + q] = x[q];
     control(T);
   }
-}
-
-template <int N, class R>
-__global__ __launch_bounds__(64) void kw_tbottom(const KProb kp, int wc, const R* __restrict__ elts,
-                                                 const R* __restrict__ Sg, const R* __restrict__ vg,
-                                                 const R* __restrict__ x1, long n1,
-                                                 R* __restrict__ xout, R* __restrict__ uout,
-                                                 const R* __restrict__ bmaps) {
-  __shared__ R sh[WSh<N>::tbottom];
-  __shared__ int piv;
-  if ((long)blockIdx.x >= n1) return;
-  wb_tbottom<N, PlainAcc>(sh, &piv, kp, blockIdx.y, blockIdx.x, wc, elts, Sg, vg, x1, n1, xout,
-                          uout, bmaps);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2519,7 +1383,7 @@ WDEV void wb_m2_sweep(R* sh, int* piv, int p, long j0, long j1, const R* tup, lo
   for (long j = j0; j < j1; ++j) {
     wt_store(run, rec_ref(pre, p, j, n_child, NE), n);
     if (j + 1 == j1) break;
-    wt_load<PlainAcc>(a, rec_ref(tup, p, j, n_child, NE), n);
+    wt_load(a, rec_ref(tup, p, j, n_child, NE), n);
     w_combine<N>(run, a, a, scr, n);
     const WT<R> t = run;
     run = a;
@@ -2546,12 +1410,12 @@ __global__ __launch_bounds__(64) void kw_m2_down(int wc, const R* __restrict__ t
   const long i = blockIdx.x;
   if (i >= n_par) return;
   WT<R> run = wt_at(sh, N);
-  wt_load<PlainAcc>(run, rec_ref(pre_in, blockIdx.y, i, n_par, ne_w(N)), N);
+  wt_load(run, rec_ref(pre_in, blockIdx.y, i, n_par, ne_w(N)), N);
   wb_m2_sweep<N, R>(sh, &piv, blockIdx.y, i * wc, min(i * wc + wc, n_child), tup, n_child,
                     pre_out, run);
 }
 
-// Down-sweep of a level reduced by kw_vreduce2<N, R, true> (left pair products t0 (x) t1 in t1's
+// Down-sweep of a level reduced by kw_vreduce2<N, R> (left pair products t0 (x) t1 in t1's
 // records): with four children, wave 0 stores the node's prefix as child 0's and forms
 // prefix (x) t0 (child 1) while wave 1 forms prefix (x) (t0 t1) (child 2) and then (x) t2
 // (child 3): two combinations deep instead of three.  Fewer children: the sequential sweep on
@@ -2569,32 +1433,32 @@ __global__ __launch_bounds__(128) void kw_m2_down2(int wc, const R* __restrict__
   const long i = blockIdx.x;
   WT<R> run = wt_at(sh[w], n), a = wt_at(sh[w] + kTupW, n);
   WS<R> scr = ws_at(sh[w] + 2 * kTupW, &piv[w], n);
-  wt_load<PlainAcc>(run, rec_ref(pre_in, p, i, n_par, NE), n);
+  wt_load(run, rec_ref(pre_in, p, i, n_par, NE), n);
   const long j0 = i * wc, j1 = min(j0 + wc, n_child);
   if (j1 - j0 == 4) {
     if (w == 0)
-      wt_store<PlainAcc>(run, rec_ref(pre_out, p, j0, n_child, NE), n);
+      wt_store(run, rec_ref(pre_out, p, j0, n_child, NE), n);
     else
       wsync();
     // wave 0: t0 (child 1); wave 1: the left pair product in t1's slot (child 2)
-    wt_load<PlainAcc>(a, rec_ref(tup, p, j0 + w, n_child, NE), n);
+    wt_load(a, rec_ref(tup, p, j0 + w, n_child, NE), n);
     w_combine<N>(run, a, a, scr, n);
-    wt_store<PlainAcc>(a, rec_ref(pre_out, p, j0 + 1 + w, n_child, NE), n);
+    wt_store(a, rec_ref(pre_out, p, j0 + 1 + w, n_child, NE), n);
     // wave 1: (x) t2 (child 3); wave 0 forms the same kind of product on its copy, discarded
-    wt_load<PlainAcc>(run, rec_ref(tup, p, j0 + 2, n_child, NE), n);
+    wt_load(run, rec_ref(tup, p, j0 + 2, n_child, NE), n);
     w_combine<N>(a, run, run, scr, n);
     if (w == 1)
-      wt_store<PlainAcc>(run, rec_ref(pre_out, p, j0 + 3, n_child, NE), n);
+      wt_store(run, rec_ref(pre_out, p, j0 + 3, n_child, NE), n);
     else
       wsync();
   } else {
     for (long j = j0; j < j1; ++j) {
       if (w == 0)
-        wt_store<PlainAcc>(run, rec_ref(pre_out, p, j, n_child, NE), n);
+        wt_store(run, rec_ref(pre_out, p, j, n_child, NE), n);
       else
         wsync();
       if (j + 1 == j1) break;
-      wt_load<PlainAcc>(a, rec_ref(tup, p, j, n_child, NE), n);
+      wt_load(a, rec_ref(tup, p, j, n_child, NE), n);
       w_combine<N>(run, a, a, scr, n);
       const WT<R> t = run;
       run = a;
@@ -2635,7 +1499,7 @@ __global__ __launch_bounds__(64) void kw_m2_bottom(const KProb kp, int wc, const
   R* up = uout ? uout + (long)p * (T + 1) * nu : nullptr;
   const long s0 = (long)p * (2L * kp.n * T + 1);
   for (int q = lane_id(); q < n; q += 64) x0[q] = ((const R*)kp.x0)[(long)p * n + q];
-  wt_load<PlainAcc>(run, rec_ref(pre1, p, i, n1, NE), n);
+  wt_load(run, rec_ref(pre1, p, i, n1, NE), n);
   auto emit = [&](long k) {
     for (int e = lane_id(); e < n * n; e += 64) S[e] = Sp[k * n * n + e];
     for (int q = lane_id(); q < n; q += 64) v[q] = vp[k * n + q];
@@ -2652,7 +1516,7 @@ __global__ __launch_bounds__(64) void kw_m2_bottom(const KProb kp, int wc, const
   for (long k = j0; k < j1; ++k) {
     emit(k);
     if (k + 1 == j1 && j1 < T) break;
-    wt_load<PlainAcc>(a, elt_ref(elts, p, k, T, NE), n);
+    wt_load(a, elt_ref(elts, p, k, T, NE), n);
     w_combine<N>(run, a, a, scr, n);
     const WT<R> t = run;
     run = a;
@@ -2856,116 +1720,6 @@ __global__ __launch_bounds__(64) void kw_dense(const KProb kp, const R* __restri
   wb_fwd_steps<N, R, false>(kp, bk, k, nn - 1, y, ac, st, sh + 3 * kTupW, step);
 }
 
-// ------------------------------------------------------------------------------------------
-// The whole solve after the element build (both trees, every level) in one launch over a work
-// queue.  The items are the nodes of every stage, in the order of the per-level launches above:
-//   value reduce (levels 1 .. L), value top, value down (levels L - 1 .. 1), value bottom,
-//   trajectory reduce (levels 2 .. L), trajectory top, trajectory down (L - 1 .. 1), bottom,
-// problem-minor within a stage.  Every wave takes the next item from a counter, waits until the
-// items it reads from are done (their status words, set after their stores are complete), runs
-// the body and marks its own item done.  An item only reads from items of earlier stages, which
-// were taken from the counter earlier and whose waves are therefore running, so every wait ends;
-// an item reads only what the items it waits for wrote or what those items waited for in turn.
-// ------------------------------------------------------------------------------------------
-enum WqKind : int { kWqVRed = 0, kWqVTop, kWqVDown, kWqVBot, kWqTRed, kWqTTop, kWqTDown, kWqTBot };
-
-template <int N, class R>
-__global__ __launch_bounds__(64) void kw_solve_queue(const KProb kp, const WQueue q,
-                                                     const R* __restrict__ elts, R* __restrict__ S,
-                                                     R* __restrict__ v, R* __restrict__ x,
-                                                     R* __restrict__ u) {
-  __shared__ R sh[WSh<N>::all];
-  __shared__ int piv;
-  const int lane = lane_id();
-  unsigned it0 = 0;
-  if (lane == 0) it0 = atomicAdd(q.done + q.total, 1u);  // the counter follows the status words
-  const long it = (long)__shfl(it0, 0, 64);
-  if (it >= q.total) return;
-  int s = 0;
-  while (s + 1 < q.nst && q.start[s + 1] <= it) ++s;
-  const long B = kp.batch, L = q.levels;
-  auto wcs = [&](long lv) { return (long)q.wcs[lv]; };  // nodes of level lv per node of lv + 1
-  const int p = (int)((it - q.start[s]) % B);
-  const long i = (it - q.start[s]) / B;
-  // stage index of each kind (see the order above)
-  auto st_vred = [&](long l) { return (int)(l - 1); };
-  auto st_vdown = [&](long l) { return (int)(2 * L - l); };  // l = L - 1 .. 1
-  const int st_vtop = (int)L, st_vbot = (int)(2 * L);
-  auto st_tred = [&](long l) { return (int)(2 * L + l - 1); };  // l = 2 .. L
-  auto st_tdown = [&](long l) { return (int)(4 * L - l); };     // l = L - 1 .. 1
-  const int st_ttop = (int)(3 * L);
-  // waits until nodes a .. b - 1 of stage t (problem p) are done
-  auto wait = [&](int t, long a, long b) {
-    const unsigned* f = q.done + q.start[t] + p;
-    for (;;) {
-      const unsigned d = a + lane < b ? lq_flag_load(f + (a + lane) * B) : 1u;
-      if (__ballot(d == 0u) == 0ull) break;
-      __builtin_amdgcn_s_sleep(1);
-    }
-    lq_acquire();
-  };
-  const int kind = q.kind[s];
-  const long l = q.level[s];
-  const R* e = elts;
-  switch (kind) {
-    case kWqVRed: {  // node i of level l from nodes i wcs(l - 1) .. of level l - 1
-      const long b = wcs(l - 1);
-      if (l > 1) wait(st_vred(l - 1), i * b, min(i * b + b, q.n[l - 1]));
-      wb_vreduce<N, DevAcc>(sh, &piv, p, i, (int)b, l == 1, l == 1 ? e : (const R*)q.vtup[l - 1],
-                            q.n[l - 1], (R*)q.vtup[l], q.n[l]);
-      break;
-    }
-    case kWqVTop:
-      wait(st_vred(L), 0, q.n[L]);
-      wb_vtop<N, DevAcc>(sh, &piv, kp, p, (const R*)q.vtup[L], q.n[L], (R*)q.vval[L]);
-      break;
-    case kWqVDown:  // node i of level l + 1 -> its children at level l
-      if (l + 1 == L)
-        wait(st_vtop, 0, 1);
-      else
-        wait(st_vdown(l + 1), i / wcs(l + 1), i / wcs(l + 1) + 1);
-      wb_vdown<N, DevAcc>(sh, &piv, p, i, (int)wcs(l), (const R*)q.vtup[l], q.n[l],
-                          (const R*)q.vval[l + 1], q.n[l + 1], (R*)q.vval[l]);
-      break;
-    case kWqVBot:
-      if (L == 1)
-        wait(st_vtop, 0, 1);
-      else
-        wait(st_vdown(1), i / wcs(1), i / wcs(1) + 1);
-      wb_vbottom<N, DevAcc>(sh, &piv, kp, p, i, (int)wcs(0), e, (const R*)q.vval[1], q.n[1], S, v,
-                            (R*)q.tmap[1], (R*)q.bmap);
-      break;
-    case kWqTRed: {
-      const long b = wcs(l - 1);
-      wait(l == 2 ? st_vbot : st_tred(l - 1), i * b, min(i * b + b, q.n[l - 1]));
-      wb_treduce<N, DevAcc>(sh, p, i, (int)b, (const R*)q.tmap[l - 1], q.n[l - 1], (R*)q.tmap[l],
-                            q.n[l]);
-      break;
-    }
-    case kWqTTop:
-      wait(L == 1 ? st_vbot : st_tred(L), 0, q.n[L]);
-      wb_ttop<N, DevAcc>(sh, kp, p, (const R*)q.tmap[L], q.n[L], (R*)q.tx[L]);
-      break;
-    case kWqTDown:
-      if (l + 1 == L)
-        wait(st_ttop, 0, 1);
-      else
-        wait(st_tdown(l + 1), i / wcs(l + 1), i / wcs(l + 1) + 1);
-      wb_tdown<N, DevAcc>(sh, p, i, (int)wcs(l), (const R*)q.tmap[l], q.n[l],
-                          (const R*)q.tx[l + 1], q.n[l + 1], (R*)q.tx[l]);
-      break;
-    case kWqTBot:
-      if (L == 1)
-        wait(st_ttop, 0, 1);
-      else
-        wait(st_tdown(1), i / wcs(1), i / wcs(1) + 1);
-      wb_tbottom<N, DevAcc>(sh, &piv, kp, p, i, (int)wcs(0), e, S, v, (const R*)q.tx[1], q.n[1], x, u,
-                            (const R*)q.bmap);
-      break;
-  }
-  if (lane == 0) lq_flag_store(q.done + it, 1u);
-}
-
 }  // namespace
 
 // ------------------------------------------------------------------------------------------
@@ -2975,19 +1729,18 @@ __global__ __launch_bounds__(64) void kw_solve_queue(const KProb kp, const WQueu
 namespace {
 
 template <int N, class R>
+using TileB = typename tile::Pick<R, N>::T;
+
+template <int N, class R>
 hipError_t wave_build_t(const KProb& kp, void* elts, hipStream_t s) {
-  if constexpr (N <= 8 && sizeof(R) == 8)
-    hipLaunchKernelGGL((kw_build_mfma8<N>), dim3((unsigned)((kp.T + 1) / 2), kp.batch), dim3(64), 0,
-                       s, kp, (double*)elts);
-  else if constexpr (N <= 8)
-    hipLaunchKernelGGL((kw_build_rows<N, R>), dim3((unsigned)((kp.T + 7) / 8), kp.batch), dim3(64),
-                       0, s, kp, (R*)elts);
-  else if constexpr (kMfma<N, R>)
-    hipLaunchKernelGGL(kw_build_mfma16<0>, dim3((unsigned)kp.T, kp.batch), dim3(64), 0, s, kp,
-                       (double*)elts);
+  using B = TileB<N, R>;
+  // waves 8 g + r take the blocks 8 B::NODES g + 8 s + r
+  const unsigned groups = (unsigned)((kp.T + 8L * B::NODES - 1) / (8L * B::NODES));
+  const dim3 g(8 * groups, kp.batch);
+  if (!kp.F_sampled && !kp.L_sampled && !kp.has_c)
+    hipLaunchKernelGGL((tile::kt_build<B, true>), g, dim3(64), 0, s, kp, (R*)elts);
   else
-    hipLaunchKernelGGL((kw_build<N, R>), dim3((unsigned)kp.T, kp.batch), dim3(64), 0, s, kp,
-                       (R*)elts);
+    hipLaunchKernelGGL((tile::kt_build<B, false>), g, dim3(64), 0, s, kp, (R*)elts);
   return hipGetLastError();
 }
 
@@ -3027,20 +1780,19 @@ constexpr long kTwoWaveNodes = 512;
 template <int N, class R>
 hipError_t wave_method2_t(const KProb& kp, const WTree& t, const Work& w, const void* elts,
                           const void* S, const void* v, void* x, void* u, hipStream_t s) {
-  const int n = N;
   const dim3 b(64);
-  hipLaunchKernelGGL((kw_vreduce<N, R>), dim3((unsigned)t.n[1], kp.batch), b, 0, s, n, t.wc, 1,
+  hipLaunchKernelGGL((kw_vreduce<N, R>), dim3((unsigned)t.n[1], kp.batch), b, 0, s, t.wc, 1,
                      (const R*)elts, t.n[0], (R*)w.vtup[1], t.n[1]);
   // Levels of few nodes on two waves per node, reduce and down-sweep alike (the reduce leaves
   // left pair products in the records the down-sweep reads).
   auto two_wave = [&](int l) { return t.wcs[l] == 4 && t.n[l + 1] * kp.batch <= kTwoWaveNodes; };
   for (int l = 1; l < t.levels; ++l) {
     if (two_wave(l))
-      hipLaunchKernelGGL((kw_vreduce2<N, R, true>), dim3((unsigned)t.n[l + 1], kp.batch),
+      hipLaunchKernelGGL((kw_vreduce2<N, R>), dim3((unsigned)t.n[l + 1], kp.batch),
                          dim3(128), 0, s, t.wcs[l], (R*)w.vtup[l], t.n[l], (R*)w.vtup[l + 1],
                          t.n[l + 1]);
     else
-      hipLaunchKernelGGL((kw_vreduce<N, R>), dim3((unsigned)t.n[l + 1], kp.batch), b, 0, s, n,
+      hipLaunchKernelGGL((kw_vreduce<N, R>), dim3((unsigned)t.n[l + 1], kp.batch), b, 0, s,
                          t.wcs[l], 0, (const R*)w.vtup[l], t.n[l], (R*)w.vtup[l + 1], t.n[l + 1]);
   }
   hipLaunchKernelGGL((kw_m2_top<N, R>), dim3(1, kp.batch), b, 0, s, (const R*)w.vtup[t.levels],
@@ -3069,38 +1821,57 @@ hipError_t wave_dense_t(const KProb& kp, const void* S, const void* v, const voi
   return hipGetLastError();
 }
 
+// Nodes of a level above which its reduce and down-sweep are launches of their own (below, one
+// workgroup per problem takes all remaining levels, kt_vmid / kt_tmid): the parents of the level
+// are then one round of the workgroup's waves.
+template <class B>
+constexpr long kMidParents = (long)tile::kMidWaves * B::NODES;
+
+// The launches of one tree above its level-1 nodes: levels below l0 one at a time, the rest in
+// one workgroup.
+template <class B>
+tile::MidArgs mid_args(const WTree& t, void* const* tup, void* const* val) {
+  tile::MidArgs a;
+  a.L = t.levels;
+  a.l0 = 1;
+  while (a.l0 < a.L && t.n[a.l0 + 1] > kMidParents<B>) ++a.l0;
+  for (int l = 0; l <= a.L; ++l) {
+    a.wcs[l] = t.wcs[l];
+    a.n[l] = t.n[l];
+    a.tup[l] = tup[l];
+    a.val[l] = val[l];
+  }
+  a.n[a.L + 1] = 1;
+  return a;
+}
+
+template <class B>
+dim3 node_waves(long n, int batch) {
+  return dim3((unsigned)((n + B::NODES - 1) / B::NODES), (unsigned)batch, 1);
+}
+template <class B>
+dim3 bottom_waves(long n, int batch, int run) {
+  return dim3(tile::spread_grid((n + B::NODES - 1) / B::NODES, run), (unsigned)batch, 1);
+}
 template <int N, class R>
 hipError_t wave_value_t(const KProb& kp, const WTree& t, const Work& w, const void* elts, void* S,
                         void* v, void* maps1, hipStream_t s) {
-  const int n = N, wc = t.wc;
+  using B = TileB<N, R>;
+  if (t.levels > kTreeMaxLevels) return hipErrorInvalidValue;
+  const int nb = kp.batch, run = tile::bottom_run<B>(t.wc);
   const dim3 b(64);
-  hipLaunchKernelGGL((kw_vreduce<N, R>), dim3((unsigned)t.n[1], kp.batch), b, 0, s, n, wc, 1,
+  hipLaunchKernelGGL((tile::kt_vreduce<B>), bottom_waves<B>(t.n[1], nb, run), b, 0, s, t.wc, 1, run,
                      (const R*)elts, t.n[0], (R*)w.vtup[1], t.n[1]);
-  // Levels of few nodes run on two waves per node (kw_vreduce2 / kw_vdown2); a level's
-  // reduce and down-sweep take the same form (the two-wave reduce leaves pair products in the
-  // records its down-sweep reads).
-  auto two_wave = [&](int l) { return t.wcs[l] == 4 && t.n[l + 1] * kp.batch <= kTwoWaveNodes; };
-  for (int l = 1; l < t.levels; ++l) {
-    if (two_wave(l))
-      hipLaunchKernelGGL((kw_vreduce2<N, R>), dim3((unsigned)t.n[l + 1], kp.batch), dim3(128), 0,
-                         s, t.wcs[l], (R*)w.vtup[l], t.n[l], (R*)w.vtup[l + 1], t.n[l + 1]);
-    else
-      hipLaunchKernelGGL((kw_vreduce<N, R>), dim3((unsigned)t.n[l + 1], kp.batch), b, 0, s, n,
-                         t.wcs[l], 0, (const R*)w.vtup[l], t.n[l], (R*)w.vtup[l + 1], t.n[l + 1]);
-  }
-  hipLaunchKernelGGL((kw_vtop<N, R>), dim3(1, kp.batch), b, 0, s, kp, (const R*)w.vtup[t.levels],
-                     t.n[t.levels], (R*)w.vval[t.levels]);
-  for (int l = t.levels - 1; l >= 1; --l) {
-    if (two_wave(l))
-      hipLaunchKernelGGL((kw_vdown2<N, R>), dim3((unsigned)t.n[l + 1], kp.batch), dim3(128), 0,
-                         s, t.wcs[l], (const R*)w.vtup[l], t.n[l], (const R*)w.vval[l + 1],
-                         t.n[l + 1], (R*)w.vval[l]);
-    else
-      hipLaunchKernelGGL((kw_vdown<N, R>), dim3((unsigned)t.n[l + 1], kp.batch), b, 0, s, n,
-                         t.wcs[l], (const R*)w.vtup[l], t.n[l], (const R*)w.vval[l + 1],
-                         t.n[l + 1], (R*)w.vval[l]);
-  }
-  hipLaunchKernelGGL((kw_vbottom<N, R>), dim3((unsigned)t.n[1], kp.batch), b, 0, s, kp, wc,
+  const tile::MidArgs m = mid_args<B>(t, w.vtup, w.vval);
+  for (int l = 1; l < m.l0; ++l)
+    hipLaunchKernelGGL((tile::kt_vreduce<B>), node_waves<B>(t.n[l + 1], nb), b, 0, s, t.wcs[l], 0, 1,
+                       (const R*)w.vtup[l], t.n[l], (R*)w.vtup[l + 1], t.n[l + 1]);
+  hipLaunchKernelGGL((tile::kt_vmid<B>), dim3(1, nb), dim3(64 * tile::kMidWaves), 0, s, kp, m);
+  for (int l = m.l0 - 1; l >= 1; --l)
+    hipLaunchKernelGGL((tile::kt_vdown<B>), node_waves<B>(t.n[l + 1], nb), b, 0, s, kp, t.wcs[l],
+                       (const R*)w.vtup[l], t.n[l], (const R*)w.vval[l + 1], t.n[l + 1],
+                       (R*)w.vval[l]);
+  hipLaunchKernelGGL((tile::kt_vbottom<B>), bottom_waves<B>(t.n[1], nb, run), b, 0, s, kp, t.wc, run,
                      (const R*)elts, (const R*)w.vval[1], t.n[1], (R*)S, (R*)v, (R*)maps1,
                      (R*)(maps1 ? w.bmap : nullptr));
   return hipGetLastError();
@@ -3110,31 +1881,32 @@ template <int N, class R>
 hipError_t wave_traj_t(const KProb& kp, const WTree& t, const Work& w, const void* elts,
                        const void* S, const void* v, void* x, void* u, bool maps_ready,
                        hipStream_t s) {
-  const int n = N, wc = t.wc;
+  using B = TileB<N, R>;
+  if (t.levels > kTreeMaxLevels) return hipErrorInvalidValue;
   const dim3 b(64);
   if (!maps_ready)
     hipLaunchKernelGGL((kw_tbottom_reduce<N, R>), dim3((unsigned)t.n[1], kp.batch), b, 0, s, kp,
-                       wc, (const R*)elts, (const R*)S, (const R*)v, (R*)w.tmap[1], t.n[1]);
-  for (int l = 1; l < t.levels; ++l)
-    hipLaunchKernelGGL((kw_treduce<N, R>), dim3((unsigned)t.n[l + 1], kp.batch), b, 0, s, n,
+                       t.wc, (const R*)elts, (const R*)S, (const R*)v, (R*)w.tmap[1], t.n[1]);
+  const tile::MidArgs m = mid_args<B>(t, w.tmap, w.tx);
+  for (int l = 1; l < m.l0; ++l)
+    hipLaunchKernelGGL((tile::kt_treduce<B>), node_waves<B>(t.n[l + 1], kp.batch), b, 0, s,
                        t.wcs[l], (const R*)w.tmap[l], t.n[l], (R*)w.tmap[l + 1], t.n[l + 1]);
-  hipLaunchKernelGGL((kw_ttop<N, R>), dim3(1, kp.batch), b, 0, s, kp, (const R*)w.tmap[t.levels],
-                     t.n[t.levels], (R*)w.tx[t.levels]);
-  for (int l = t.levels - 1; l >= 1; --l)
-    hipLaunchKernelGGL((kw_tdown<N, R>), dim3((unsigned)t.n[l + 1], kp.batch), b, 0, s, n,
+  hipLaunchKernelGGL((tile::kt_tmid<B>), dim3(1, kp.batch), dim3(64 * tile::kMidWaves), 0, s, kp, m);
+  for (int l = m.l0 - 1; l >= 1; --l)
+    hipLaunchKernelGGL((tile::kt_tdown<B>), node_waves<B>(t.n[l + 1], kp.batch), b, 0, s,
                        t.wcs[l], (const R*)w.tmap[l], t.n[l], (const R*)w.tx[l + 1], t.n[l + 1],
                        (R*)w.tx[l]);
-  hipLaunchKernelGGL((kw_tbottom<N, R>), dim3((unsigned)t.n[1], kp.batch), b, 0, s, kp, wc,
-                     (const R*)elts, (const R*)S, (const R*)v, (const R*)w.tx[1], t.n[1], (R*)x,
-                     (R*)u, (const R*)(maps_ready ? w.bmap : nullptr));
-  return hipGetLastError();
-}
-
-template <int N, class R>
-hipError_t wave_solve_queue_t(const KProb& kp, const WQueue& q, const void* elts, void* S, void* v,
-                              void* x, void* u, hipStream_t s) {
-  hipLaunchKernelGGL((kw_solve_queue<N, R>), dim3((unsigned)q.total), dim3(64), 0, s, kp, q,
-                     (const R*)elts, (R*)S, (R*)v, (R*)x, (R*)u);
+  // The block maps kept by the value sweep, when the workspace has room for them; otherwise they
+  // are formed again from the elements and S, v.
+  if (maps_ready && w.bmap) {
+    hipLaunchKernelGGL((tile::kt_tbottom<B>), node_waves<B>(t.n[1], kp.batch), b, 0, s, kp, t.wc,
+                       (const R*)S, (const R*)v, (const R*)w.tx[1], t.n[1], (R*)x, (R*)u,
+                       (const R*)w.bmap);
+  } else {
+    hipLaunchKernelGGL((kw_tbottom<N, R>), dim3((unsigned)t.n[1], kp.batch), b, 0, s, kp, t.wc,
+                       (const R*)elts, (const R*)S, (const R*)v, (const R*)w.tx[1], t.n[1], (R*)x,
+                       (R*)u);
+  }
   return hipGetLastError();
 }
 
@@ -3148,7 +1920,7 @@ struct Fns {
   static const WaveFns* get() {
     if constexpr (wave_shard(N, sizeof(R) == 4) == LQT_SHARD) {
       static const WaveFns f = {wave_build_t<N, R>,       wave_value_t<N, R>,
-                                wave_traj_t<N, R>,        wave_solve_queue_t<N, R>,
+                                wave_traj_t<N, R>,
                                 wave_build_fwd_t<N, R>,   wave_build_split_t<N, R>,
                                 wave_method2_t<N, R>,     wave_dense_t<N, R>,
                                 wave_lti_prep_t<N, R>,    wave_lti_build_t<N, R>};
