@@ -20,8 +20,8 @@ INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "liblqt.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
-SOURCES = ["lqt_api.hip", "lqt_prep.hip", "lqt_lane.hip", "lqt_adjoint.hip", "lqt_wave.hip",
-           "lqt_batched.hip"]
+SOURCES = ["lqt_api.hip", "lqt_prep.hip", "lqt_lane.hip", "lqt_tile.hip", "lqt_adjoint.hip",
+           "lqt_wave.hip", "lqt_batched.hip"]
 # Sources compiled once per build shard (-DLQT_SHARD=i): each object holds a share of the
 # template instantiations, so the shards compile in parallel.  Must match kLaneShards and
 # kWaveShards in csrc/lqt_internal.hpp (a mismatch fails at link time).

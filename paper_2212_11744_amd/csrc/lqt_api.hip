@@ -89,7 +89,7 @@ Tree plan_tree(long T) {
   return t;
 }
 
-// Wave-path trees: n[0] = T, n[l + 1] = ceil(n[l] / wcs[l]) while n[l] > wcs[l], with
+// Wave-path trees of Method 2: n[0] = T, n[l + 1] = ceil(n[l] / wcs[l]) while n[l] > wcs[l], with
 // wcs[0] = wc and kWaveUpperChunk above.
 WTree wave_tree(long T, int wc) {
   WTree t;
@@ -102,6 +102,50 @@ WTree wave_tree(long T, int wc) {
     const int b = t.wcs[t.levels];
     t.n[t.levels + 1] = (t.n[t.levels] + b - 1) / b;
     ++t.levels;
+  }
+  return t;
+}
+
+namespace {
+// Slots of a group (kGroup in tile_kernels.hpp).
+int group_slots(int nx) { return nx <= 4 ? 32 : nx <= 8 ? 16 : 4; }
+void upper_stages(GTree& t) {
+  long n = t.m;
+  for (t.up = 0; n > 1 && t.up < kMaxStages; ++t.up) {
+    // the last stage takes up to 8 (4 where a step takes longer than a launch) nodes per slot
+    const bool root = n <= t.G * (t.G > 8 ? 8L : 4L);
+    const int j = t.up, c = root ? (int)((n + t.G - 1) / t.G) : 4;
+    t.c[j] = c;
+    t.src[j] = n;
+    t.slot[j] = (n + c - 1) / c;
+    t.grp[j] = n = root ? 1 : (t.slot[j] + t.G - 1) / t.G;
+  }
+}
+}  // namespace
+
+GTree group_tree(int nx, long T, int wc) {
+  GTree t;
+  t.G = group_slots(nx);
+  // a horizon of one group: as few blocks in a row as that allows
+  while (wc > 1 && T <= wc / 2 * t.G) wc /= 2;
+  t.wc = wc;
+  t.T = T;
+  t.n1 = (T + wc - 1) / wc;
+  t.m = (t.n1 + t.G - 1) / t.G;
+  upper_stages(t);
+  return t;
+}
+GTree node_tree(int nx, long T, int wc) {
+  GTree t;
+  t.G = group_slots(nx);
+  t.wc = wc;
+  t.T = T;
+  t.n1 = t.m = (T + wc - 1) / wc;
+  upper_stages(t);
+  if (t.up == 0) {  // one node: a stage that starts it at x0
+    t.up = 1;
+    t.c[0] = 1;
+    t.src[0] = t.slot[0] = t.grp[0] = 1;
   }
   return t;
 }
@@ -165,17 +209,22 @@ hipError_t wave_dense(const KProb& kp, int dtype, const void* S, const void* v, 
   return f ? f->dense(kp, S, v, x, Sd, vd, xd, ud, s) : hipErrorInvalidValue;
 }
 
-hipError_t wave_value(const KProb& kp, int dtype, const WTree& t, const Work& w, const void* elts,
-                      void* S, void* v, void* maps1, hipStream_t s) {
+hipError_t wave_value(const KProb& kp, int dtype, const GTree& t, const Work& w, const void* elts,
+                      void* S, void* v, hipStream_t s) {
   const WaveFns* f = wave_fns(kp.nx, dtype);
-  return f ? f->value(kp, t, w, elts, S, v, maps1, s) : hipErrorInvalidValue;
+  return f ? f->value(kp, t, w, elts, S, v, s) : hipErrorInvalidValue;
 }
 
-hipError_t wave_traj(const KProb& kp, int dtype, const WTree& t, const Work& w, const void* elts,
-                     const void* S, const void* v, void* x, void* u, bool maps_ready,
-                     hipStream_t s) {
+hipError_t wave_traj(const KProb& kp, int dtype, const GTree& t, const Work& w, const void* elts,
+                     const void* S, const void* v, void* x, void* u, hipStream_t s) {
   const WaveFns* f = wave_fns(kp.nx, dtype);
-  return f ? f->traj(kp, t, w, elts, S, v, x, u, maps_ready, s) : hipErrorInvalidValue;
+  return f ? f->traj(kp, t, w, elts, S, v, x, u, s) : hipErrorInvalidValue;
+}
+
+hipError_t wave_scans(const KProb& kp, int dtype, const GTree& t, const Work& w, const void* elts,
+                      void* S, void* v, void* x, void* u, hipStream_t s) {
+  const WaveFns* f = wave_fns(kp.nx, dtype);
+  return f ? f->scans(kp, t, w, elts, S, v, x, u, s) : hipErrorInvalidValue;
 }
 
 namespace {
@@ -195,6 +244,30 @@ bool use_wave(const lqt_dims* d) { return lane_ops(d->nx, d->nu, d->dtype) == nu
 constexpr int kWaveChunk = 4;
 
 WTree wtree_for(const lqt_dims* d) { return wave_tree(d->T, kWaveChunk); }
+
+// Where the small sizes take the kernels of lqt_tile.hip: four lanes times four to a block or node
+// instead of one lane, a quarter of the latency of a step and about half of the throughput.
+// Element build, measured against the per-lane one (us, n = 4): nx = 4 FP64 4.9 vs 17 at T = 64, 20 vs
+// 21 at 32000, 37 vs 23 at 2^16 (n = 10: 6.5 vs 38 at 64, 22 vs 41 at 16000); nx = 4 FP32 7.0 vs
+// 14.6 at 8000, 20 vs 16 at 32000; nx = 3 8.6 vs 12.4 at 8000, 14 vs 13 at 16000; nx = 2 4.7 vs 4.3
+// at 64 and slower beyond.
+bool use_tile_build(const lqt_dims* d) {
+  if (use_wave(d) || d->nx < 3) return false;
+  const long blocks = (long)d->T * d->batch;
+  return blocks <= (d->nx == 4 && d->dtype == LQT_F64 ? 1L << 15 : 1L << 13);
+}
+// Scans, nx = 4 FP64, as long as every group has a CU of its own.  Against the single-pass scans of
+// the per-lane path, in a solve (us): 27 vs 76 at T = 64 and n = 10, 98 vs 131 at T = 2^16, the most
+// that 256 groups take.  FP32 (whose per-lane arithmetic is four times as fast) and nx <= 3
+// (smaller systems, the same number of steps) are at best even: 23 vs 27 in FP32 at T = 64, 23 vs
+// 23 at nx = 3, 73 vs 50 at nx = 3 and T = 16000.
+constexpr long kTileGroups = 256;
+constexpr int kTileChunk = 8;  // blocks per slot
+GTree tile_tree(const lqt_dims* d) { return group_tree(d->nx, d->T, kTileChunk); }
+bool use_tile_scans(const lqt_dims* d) {
+  return !use_wave(d) && d->nx == 4 && d->dtype == LQT_F64 &&
+         tile_tree(d).m * d->batch <= kTileGroups;
+}
 
 }  // namespace
 
@@ -237,31 +310,52 @@ size_t layout(const lqt_dims* d, lqt_call call, char* base, Work* w, int wc, lon
   const bool want_v = call == LQT_CALL_SCAN_VALUE || call == LQT_CALL_SOLVE ||
                       call == LQT_CALL_TRAJ_METHOD2;
   const bool want_t = call == LQT_CALL_FORWARD_TRAJ || call == LQT_CALL_SOLVE;
-  if (use_wave(d)) {
+  const bool tile = use_tile_scans(d) && (call == LQT_CALL_SCAN_VALUE ||
+                                          (call == LQT_CALL_SOLVE && keep_maps));
+  if (use_wave(d) && call == LQT_CALL_TRAJ_METHOD2) {
     const WTree t = wave_tree(d->T, wc);
     for (int l = 1; l <= t.levels; ++l) {
-      if (want_v) {
-        void* a = take(es * B * ne_of(d->nx) * t.n[l]);
-        void* b = take(es * B * nm_of(d->nx) * t.n[l]);
-        if (w) {
-          w->vtup[l] = a;
-          w->vval[l] = b;
-        }
-      }
-      if (want_t) {
-        void* a = take(es * B * nm_of(d->nx) * t.n[l]);
-        void* b = take(es * B * d->nx * t.n[l]);
-        if (w) {
-          w->tmap[l] = a;
-          w->tx[l] = b;
-        }
-      }
-      if (call == LQT_CALL_TRAJ_METHOD2) {  // prefix records of the nodes
-        void* a = take(es * B * ne_of(d->nx) * t.n[l]);
-        if (w) w->vpart[l] = a;
+      void* a = take(es * B * ne_of(d->nx) * t.n[l]);
+      void* b = take(es * B * nm_of(d->nx) * t.n[l]);
+      void* c = take(es * B * ne_of(d->nx) * t.n[l]);  // prefix records of the nodes
+      if (w) {
+        w->vtup[l] = a;
+        w->vval[l] = b;
+        w->vpart[l] = c;
       }
     }
-    if (call == LQT_CALL_SOLVE && ws_elts) {
+    return off;
+  }
+  if (use_wave(d) || tile) {
+    // array 1: the bottom stage's slots, then the nodes the upper stages start from and the
+    // slots and groups of each (launch_value in tile_host.hpp)
+    const GTree t = !use_wave(d)                       ? tile_tree(d)
+                    : call == LQT_CALL_FORWARD_TRAJ ? node_tree(d->nx, d->T, wc)
+                                                    : group_tree(d->nx, d->T, wc);
+    auto slots = [&](int l, long n) {
+      void* a = want_v ? take(es * B * ne_of(d->nx) * n) : nullptr;
+      void* b = want_t ? take(es * B * nm_of(d->nx) * n) : nullptr;
+      if (w) w->vtup[l] = a, w->tmap[l] = b;
+    };
+    auto nodes = [&](int l, long n) {
+      slots(l, n);
+      void* a = want_v ? take(es * B * nm_of(d->nx) * n) : nullptr;
+      void* b = want_t ? take(es * B * d->nx * n) : nullptr;
+      if (w) w->vval[l] = a, w->tx[l] = b;
+    };
+    if (want_v) slots(1, t.n1);
+    if (call == LQT_CALL_SOLVE && !keep_maps) {
+      void* a = take(es * B * d->nx * t.n1);
+      if (w) w->tx[1] = a;
+    }
+    nodes(2, t.m);
+    for (int j = 0; j < t.up; ++j) {
+      // the last stage of a tree from fewer nodes may have more slots, up to a group
+      const bool root = j + 1 == t.up;
+      slots(3 + 2 * j, root ? std::min((long)t.G, t.src[j]) : t.slot[j]);
+      if (!root) nodes(4 + 2 * j, t.grp[j]);
+    }
+    if (call == LQT_CALL_SOLVE && ws_elts && use_wave(d)) {
       void* e = take(es * B * ne_of(d->nx) * (size_t)padt(d->T));
       if (w) w->elts = e;
     }
@@ -272,7 +366,7 @@ size_t layout(const lqt_dims* d, lqt_call call, char* base, Work* w, int wc, lon
         if (w) w->bmap = bm;
       }
     }
-    return off;
+    if (use_wave(d)) return off;
   }
   const Tree t = tree_for(d);
   // Single-pass scans: the counter and status words of a scan first (one clear), then payloads.
@@ -670,6 +764,8 @@ lqt_status lqt_build_elements(const lqt_dims* dims, const lqt_problem* prob, voi
     const Ops* o = lane_ops(dims->nx, dims->nu, dims->dtype);
     LQT_HIP(o->lti_prep(kp, w.lti, stream));
     LQT_HIP(o->lti_build(kp, w.lti, elts, stream));
+  } else if (use_tile_build(dims)) {
+    LQT_HIP(tile_build(kp, dims->dtype, elts, stream));
   } else {
     LQT_HIP(lane_ops(dims->nx, dims->nu, dims->dtype)->build(kp, elts, stream));
   }
@@ -795,10 +891,14 @@ lqt_status lqt_scan_value(const lqt_dims* dims, const void* elts, const void* Qf
   p.rf = rf;
   KProb kp = make_kprob(dims, &p, w.consts);
   if (use_wave(dims)) {
-    LQT_HIP(wave_value(kp, dims->dtype, wtree_for(dims), w, elts, S, v, nullptr, stream));
+    LQT_HIP(wave_value(kp, dims->dtype, group_tree(dims->nx, dims->T, kWaveChunk), w, elts, S, v,
+                       stream));
   } else {
     const Ops* o = lane_ops(dims->nx, dims->nu, dims->dtype);
-    LQT_TRY(run_value(o, kp, w, elts, S, v, stream));
+    if (use_tile_scans(dims))
+      LQT_HIP(tile_value(kp, tile_tree(dims), w, elts, S, v, stream));
+    else
+      LQT_TRY(run_value(o, kp, w, elts, S, v, stream));
   }
   const long nb = dims->batch, T1 = (long)dims->T + 1, nx = dims->nx;
   LQT_TRY(finite_check(dims, w, stream, {{S, nb * T1 * nx * nx, false}, {v, nb * T1 * nx, false}}));
@@ -824,7 +924,8 @@ lqt_status lqt_forward_traj(const lqt_dims* dims, const lqt_problem* prob, const
   KProb kp = make_kprob(dims, prob, w.consts);
   LQT_HIP(prep(dims, kp, w.consts, stream));
   if (use_wave(dims)) {
-    LQT_HIP(wave_traj(kp, dims->dtype, wtree_for(dims), w, elts, S, v, x, u, false, stream));
+    LQT_HIP(wave_traj(kp, dims->dtype, node_tree(dims->nx, dims->T, kWaveChunk), w, elts, S, v, x, u,
+                      stream));
   } else {
     const Ops* o = lane_ops(dims->nx, dims->nu, dims->dtype);
     LQT_TRY(run_traj(o, kp, w, elts, S, v, x, u, stream));
@@ -846,13 +947,12 @@ lqt_status run_solve(const lqt_dims* dims, const KProb& kp, const Work& w, void*
   if (kp.seg) kprep.batch = kp.nseg;
   if (use_wave(dims)) {
     LQT_HIP(prep(dims, kprep, w.consts, stream));
-    const WTree wt = wave_tree(dims->T, o.wave_chunk);
     if (kp.lti && !kp.seg && w.lti)
       LQT_HIP(wave_lti(kp, dims->dtype, w.lti, e, stream));
     else
       LQT_HIP(wave_build(kp, dims->dtype, e, stream));
-    LQT_HIP(wave_value(kp, dims->dtype, wt, w, e, S, v, w.tmap[1], stream));
-    LQT_HIP(wave_traj(kp, dims->dtype, wt, w, e, S, v, x, u, true, stream));
+    LQT_HIP(wave_scans(kp, dims->dtype, group_tree(dims->nx, dims->T, o.wave_chunk), w, e, S, v, x, u,
+                       stream));
     return LQT_OK;
   }
   const Ops* op = lane_ops(dims->nx, dims->nu, dims->dtype);
@@ -862,8 +962,15 @@ lqt_status run_solve(const lqt_dims* dims, const KProb& kp, const Work& w, void*
   if (lti) {
     LQT_HIP(op->lti_prep(kp, w.lti, stream));
     LQT_HIP(op->lti_build(kp, w.lti, e, stream));
+  } else if (use_tile_build(dims)) {
+    LQT_HIP(tile_build(kp, dims->dtype, e, stream));
   } else {
     LQT_HIP(op->build(kp, e, stream));
+  }
+  if (use_tile_scans(dims) && w.bmap && !kp.seg) {
+    LQT_HIP(tile_scans(kp, tile_tree(dims), w, e, S, v, x, u, stream));
+    LQT_HIP(hipPeekAtLastError());  // of the sequence as a whole
+    return LQT_OK;
   }
   if (o.queue_chunk) {
     const int cv = o.queue_chunk;

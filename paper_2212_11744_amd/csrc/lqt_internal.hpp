@@ -254,10 +254,10 @@ const Ops* lane_ops_shard(int nx, int nu, int dtype);
 const Ops* lane_ops(int nx, int nu, int dtype);
 
 // Wavefront-per-tuple path (lqt_wave.hip) for any nx <= 16: one wavefront per block or tree
-// node, matrices in LDS.  Its trees reduce wcs[l] nodes per wave at level l: n[0] = T,
-// n[l + 1] = ceil(n[l] / wcs[l]) while n[l] > wcs[l] (wcs[0] = wc, above kWaveUpperChunk).  Tree nodes are records ([batch][n[l]][record]):
-// tuples (NE values, element order), values (S full, v: nx^2 + nx), maps (P = Psi - I, q:
-// nx^2 + nx), states (nx).
+// node, matrices in LDS.  Its trees (Method 2) reduce wcs[l] nodes per wave at level l: n[0] = T,
+// n[l + 1] = ceil(n[l] / wcs[l]) while n[l] > wcs[l] (wcs[0] = wc, above kWaveUpperChunk).  Tree
+// nodes are records ([batch][n[l]][record]): tuples (NE values, element order), values (S full, v:
+// nx^2 + nx), maps (P = Psi - I, q: nx^2 + nx), states (nx).
 struct WTree {
   int levels = 0;
   int wc = 8;                     // blocks per wave at the bottom (= wcs[0])
@@ -268,15 +268,32 @@ struct WTree {
 // so the serial chain of a wave (wcs[l] combinations or folds) is what they cost.
 constexpr int kWaveUpperChunk = 4;
 WTree wave_tree(long T, int wc);
-// Levels the wave path's launches have room for (T up to 2^31 with 4 nodes per node).
-constexpr int kTreeMaxLevels = 16;
+// Tree of the solve, the value scan and the Method 1 trajectory on the kernels of
+// tile_kernels.hpp, in stages of slots (c consecutive nodes each) and groups of G slots: the bottom
+// stage takes the T blocks, upper stage j the groups of the stage below; the last has one group.
+constexpr int kMaxStages = 12;
+struct GTree {
+  int G = 0;           // slots per group
+  int wc = 0;          // blocks per slot of the bottom stage
+  long T = 0, n1 = 0;  // blocks, slots of the bottom stage
+  long m = 0;          // nodes the upper stages start from
+  int up = 0;          // upper stages
+  int c[kMaxStages] = {};
+  long src[kMaxStages] = {}, slot[kMaxStages] = {}, grp[kMaxStages] = {};
+};
+GTree group_tree(int nx, long T, int wc);   // from the blocks
+GTree node_tree(int nx, long T, int wc);    // from nodes of wc blocks, which no stage here forms
 // Launchers of one wave-path instantiation (state size, dtype).
 struct WaveFns {
   hipError_t (*build)(const KProb&, void* elts, hipStream_t);
-  hipError_t (*value)(const KProb&, const WTree&, const Work&, const void* elts, void* S, void* v,
-                      void* maps1, hipStream_t);
-  hipError_t (*traj)(const KProb&, const WTree&, const Work&, const void* elts, const void* S,
-                     const void* v, void* x, void* u, bool maps_ready, hipStream_t);
+  hipError_t (*value)(const KProb&, const GTree&, const Work&, const void* elts, void* S, void* v,
+                      hipStream_t);
+  // trajectory from the nodes of node_tree
+  hipError_t (*traj)(const KProb&, const GTree&, const Work&, const void* elts, const void* S,
+                     const void* v, void* x, void* u, hipStream_t);
+  // both scans of a solve (block maps in w.bmap if there is room, formed twice if not)
+  hipError_t (*scans)(const KProb&, const GTree&, const Work&, const void* elts, void* S, void* v,
+                      void* x, void* u, hipStream_t);
   hipError_t (*build_fwd)(const KProb&, void* elts, hipStream_t);    // Theorem 9
   hipError_t (*build_split)(const KProb&, void* elts, hipStream_t);  // split blocks
   // Method 2 trajectory (node products in w.vtup, prefix records in w.vpart)
@@ -299,11 +316,20 @@ hipError_t wave_method2(const KProb& kp, int dtype, const WTree& t, const Work& 
 hipError_t wave_lti(const KProb& kp, int dtype, void* tab, void* elts, hipStream_t s);
 hipError_t wave_dense(const KProb& kp, int dtype, const void* S, const void* v, const void* x,
                       void* Sd, void* vd, void* xd, void* ud, hipStream_t s);
-hipError_t wave_value(const KProb& kp, int dtype, const WTree& t, const Work& w, const void* elts,
-                      void* S, void* v, void* maps1, hipStream_t s);
-hipError_t wave_traj(const KProb& kp, int dtype, const WTree& t, const Work& w, const void* elts,
-                     const void* S, const void* v, void* x, void* u, bool maps_ready,
-                     hipStream_t s);
+hipError_t wave_value(const KProb& kp, int dtype, const GTree& t, const Work& w, const void* elts,
+                      void* S, void* v, hipStream_t s);
+hipError_t wave_traj(const KProb& kp, int dtype, const GTree& t, const Work& w, const void* elts,
+                     const void* S, const void* v, void* x, void* u, hipStream_t s);
+hipError_t wave_scans(const KProb& kp, int dtype, const GTree& t, const Work& w, const void* elts,
+                      void* S, void* v, void* x, void* u, hipStream_t s);
+
+// Short horizons of the small sizes on the kernels of tile_kernels.hpp (lqt_tile.hip): the element
+// build at nx = 3, 4, and in FP64 at nx = 4 the value scan alone and both scans (block maps in w.bmap).
+hipError_t tile_build(const KProb& kp, int dtype, void* elts, hipStream_t s);
+hipError_t tile_value(const KProb& kp, const GTree& t, const Work& w, const void* elts, void* S,
+                      void* v, hipStream_t s);
+hipError_t tile_scans(const KProb& kp, const GTree& t, const Work& w, const void* elts, void* S,
+                      void* v, void* x, void* u, hipStream_t s);
 
 // Options of a full solve: the number of nodes per wave of the wave path's trees.
 struct SolveOpts {

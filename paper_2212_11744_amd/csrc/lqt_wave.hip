@@ -6,15 +6,16 @@
 //
 // Elements use the tiled layout of the C ABI; tree nodes are records ([batch][n][NQ]) with the
 // element's value order: A - I (nx*nx, row-major), b, C (upper triangle, row by row), eta, J.
-// Scans: every wave reduces wcs[l] consecutive nodes of level l serially (the bottom chunk chosen at
-// run time, upper levels kWaveUpperChunk); level l + 1 has ceil(n_l / wcs[l]) nodes while
-// n_l > wcs[l]; the top (<= wcs[L] nodes) is swept by one wave.
+// The element build, the value scan and the Method 1 trajectory are those of tile_kernels.hpp, with
+// the matrices in registers; here are the trajectory's block maps where none were kept, and Method 2:
+// every wave reduces wcs[l] consecutive nodes of level l serially (the bottom chunk chosen at run
+// time, upper levels kWaveUpperChunk); level l + 1 has ceil(n_l / wcs[l]) nodes while n_l > wcs[l];
+// the top (<= wcs[L] nodes) is swept by one wave.
 #include <cstring>
 
 #include "../../include/lqt.h"
-#include "coherent.hpp"
 #include "lqt_internal.hpp"
-#include "tile_kernels.hpp"
+#include "tile_host.hpp"
 
 namespace lqt {
 namespace {
@@ -25,7 +26,7 @@ constexpr int kTile = kEltTile;  // element tile (blocks per tile of the element
 
 WDEV int lane_id() { return threadIdx.x & 63; }
 // A workgroup barrier.  Most kernels run one wavefront per workgroup; the two-wave tree kernels
-// (kw_vreduce2, kw_vdown2) have both of their waves pass the same number of these.
+// (kw_vreduce2, kw_m2_down2) have both of their waves pass the same number of these.
 WDEV void wsync() { __syncthreads(); }
 
 WDEV int pk(int i, int j, int n) {  // packed upper index
@@ -136,12 +137,6 @@ WDEV void w_gemm(R* C, const R* A, const R* B, int m, int kk, int p, bool tA, bo
 template <class R>
 WDEV void w_copy(R* dst, const R* src, int n) {
   for (int e = lane_id(); e < n; e += 64) dst[e] = src[e];
-  wsync();
-}
-
-template <class R>
-WDEV void w_fill(R* dst, R v, int n) {
-  for (int e = lane_id(); e < n; e += 64) dst[e] = v;
   wsync();
 }
 
@@ -288,7 +283,6 @@ WDEV WT<R> wt_at(R* base, int n) {  // 3 n^2 + 2 n values
   t.J = t.e + n;
   return t;
 }
-__host__ __device__ inline int wt_size(int n) { return 3 * n * n + 2 * n; }
 __host__ __device__ inline int ne_w(int n) { return 2 * n * n + 3 * n; }
 
 // A tuple in global memory: value q at g[q * st] (st = 1 for tree nodes, kTile for elements).
@@ -493,81 +487,6 @@ WDEV void w_combine(WT<R> x1, WT<R> x2, WT<R> o, WS<R> s, int n) {
   wsync();
 }
 
-// Fold with a terminal-form right operand: (S, v) <- a (x) (S, v); also the block map
-// (P = Psi - I, q = alpha) into P, q (nullable).  S full symmetric.
-template <int N, class R>
-WDEV void w_fold(WT<R> a, R* S, R* v, WS<R> s, int n, R* P, R* q) {
-  const int nb = n + 1;
-  // C and S are symmetric: the left factors and the vector products read them by columns
-  w_gemm<kMfma<N, R>>(s.X, a.C, S, n, n, n, kMfma<N, R>, false, R(1), R(0));  // C S
-  for (int e = lane_id(); e < n * n; e += 64) {
-    const int i = e / n, j = e % n;
-    s.M[e] = (i == j ? R(1) : R(0)) + s.X[e];
-    s.B[i * nb + j] = a.A[e] - s.X[e];
-  }
-  for (int i = lane_id(); i < n; i += 64) {
-    R g = a.b[i];
-    for (int k = 0; k < n; ++k) g = fma(a.C[k * n + i], v[k], g);
-    s.B[i * nb + n] = g;
-  }
-  wsync();
-  w_solve<N, N + 1>(s.M, s.B);
-  if (P) {
-    for (int e = lane_id(); e < n * n; e += 64) P[e] = s.B[(e / n) * nb + e % n];
-    for (int i = lane_id(); i < n; i += 64) q[i] = s.B[i * nb + n];
-  }
-  // w = v - S b -> f;  X = S (I + Ad) -> X
-  for (int i = lane_id(); i < n; i += 64) {
-    R t = v[i];
-    for (int k = 0; k < n; ++k) t = fma(-S[k * n + i], a.b[k], t);
-    s.f[i] = t;
-  }
-  if constexpr (kMfma<N, R>) {
-    w_mm16(s.X, 16, S, 16, true, a.A, 16, false, 16, 1.0, S, 16, 1.0);      // S (I + Ad)
-    w_mm16(s.M, 16, s.B, nb, true, s.X, 16, false, 16, 1.0, s.X, 16, 1.0);  // (I + Yd)^T X
-    w_symadd16(s.M, a.J);
-    const int i = lane_id();
-    R vn = R(0);
-    if (i < n) {
-      R t = R(0);
-      for (int k = 0; k < n; ++k) t = fma(s.B[k * nb + i], s.f[k], t);
-      vn = a.e[i] + (s.f[i] + t);
-    }
-    wsync();
-    for (int e = i; e < n * n; e += 64) S[e] = s.M[e];
-    if (i < n) v[i] = vn;
-    wsync();
-    return;
-  }
-  for (int e = lane_id(); e < n * n; e += 64) {
-    const int i = e / n, j = e % n;
-    R t = S[e];
-    for (int k = 0; k < n; ++k) t = fma(S[i * n + k], a.A[k * n + j], t);
-    s.X[e] = t;
-  }
-  wsync();
-  R sn[4], vn = R(0);
-  int cnt = 0;
-  for (int e = lane_id(); e < n * n; e += 64, ++cnt) {
-    const int r = e / n, j = e % n;
-    const int aa = r < j ? r : j, bb = r < j ? j : r;
-    R t = R(0);
-    for (int k = 0; k < n; ++k) t = fma(s.B[k * nb + aa], s.X[k * n + bb], t);
-    sn[cnt] = a.J[aa * n + bb] + (s.X[aa * n + bb] + t);
-  }
-  const int i = lane_id();
-  if (i < n) {
-    R t = R(0);
-    for (int k = 0; k < n; ++k) t = fma(s.B[k * nb + i], s.f[k], t);
-    vn = a.e[i] + (s.f[i] + t);
-  }
-  wsync();
-  cnt = 0;
-  for (int e = lane_id(); e < n * n; e += 64, ++cnt) S[e] = sn[cnt];
-  if (i < n) v[i] = vn;
-  wsync();
-}
-
 // Block map only: (P, q) from (Ad, b, C) of a block and (S, v) at its right end.
 template <int N, class R>
 WDEV void w_block_map(WT<R> a, const R* S, const R* v, WS<R> s, int n, R* P, R* q) {
@@ -603,26 +522,6 @@ WDEV void w_aff_then(R* aP, R* aq, const R* lP, const R* lq, R* tmp, int n) {
     R t = R(0);
     for (int k = 0; k < n; ++k) t = fma(lP[i * n + k], aq[k], t);
     tmp[n * n + i] = lq[i] + aq[i] + t;
-  }
-  wsync();
-  for (int e = lane_id(); e < n * n; e += 64) aP[e] = tmp[e];
-  for (int i = lane_id(); i < n; i += 64) aq[i] = tmp[n * n + i];
-  wsync();
-}
-
-// acc <- acc o earlier
-template <class R>
-WDEV void w_aff_after(R* aP, R* aq, const R* eP, const R* eq, R* tmp, int n) {
-  for (int e = lane_id(); e < n * n; e += 64) {
-    const int i = e / n, j = e % n;
-    R t = R(0);
-    for (int k = 0; k < n; ++k) t = fma(aP[i * n + k], eP[k * n + j], t);
-    tmp[e] = eP[e] + aP[e] + t;
-  }
-  for (int i = lane_id(); i < n; i += 64) {
-    R t = R(0);
-    for (int k = 0; k < n; ++k) t = fma(aP[i * n + k], eq[k], t);
-    tmp[n * n + i] = aq[i] + eq[i] + t;
   }
   wsync();
   for (int e = lane_id(); e < n * n; e += 64) aP[e] = tmp[e];
@@ -1081,11 +980,7 @@ __global__ __launch_bounds__(64) void kw_build_split(const KProb kp, R* __restri
 }
 
 // ------------------------------------------------------------------------------------------
-// Value tree.  The kernels below are thin launches of device bodies that take their node and
-// problem, LDS and access policy A (coherent.hpp) from the caller: A applies to the tree records,
-// S, v and x0 passed between the bodies (elements, written by an earlier launch, are plain loads),
-// so the same bodies run as one launch per tree level (A = PlainAcc) and as the items of the
-// single-launch solve below (A = DevAcc).
+// Value tree of Method 2.
 // ------------------------------------------------------------------------------------------
 template <int N>
 struct WSh {  // LDS of the bodies (values of the solve's type)
@@ -1733,15 +1628,7 @@ using TileB = typename tile::Pick<R, N>::T;
 
 template <int N, class R>
 hipError_t wave_build_t(const KProb& kp, void* elts, hipStream_t s) {
-  using B = TileB<N, R>;
-  // waves 8 g + r take the blocks 8 B::NODES g + 8 s + r
-  const unsigned groups = (unsigned)((kp.T + 8L * B::NODES - 1) / (8L * B::NODES));
-  const dim3 g(8 * groups, kp.batch);
-  if (!kp.F_sampled && !kp.L_sampled && !kp.has_c)
-    hipLaunchKernelGGL((tile::kt_build<B, true>), g, dim3(64), 0, s, kp, (R*)elts);
-  else
-    hipLaunchKernelGGL((tile::kt_build<B, false>), g, dim3(64), 0, s, kp, (R*)elts);
-  return hipGetLastError();
+  return tile::launch_build<TileB<N, R>>(kp, elts, s);
 }
 
 template <int N, class R>
@@ -1821,93 +1708,38 @@ hipError_t wave_dense_t(const KProb& kp, const void* S, const void* v, const voi
   return hipGetLastError();
 }
 
-// Nodes of a level above which its reduce and down-sweep are launches of their own (below, one
-// workgroup per problem takes all remaining levels, kt_vmid / kt_tmid): the parents of the level
-// are then one round of the workgroup's waves.
-template <class B>
-constexpr long kMidParents = (long)tile::kMidWaves * B::NODES;
-
-// The launches of one tree above its level-1 nodes: levels below l0 one at a time, the rest in
-// one workgroup.
-template <class B>
-tile::MidArgs mid_args(const WTree& t, void* const* tup, void* const* val) {
-  tile::MidArgs a;
-  a.L = t.levels;
-  a.l0 = 1;
-  while (a.l0 < a.L && t.n[a.l0 + 1] > kMidParents<B>) ++a.l0;
-  for (int l = 0; l <= a.L; ++l) {
-    a.wcs[l] = t.wcs[l];
-    a.n[l] = t.n[l];
-    a.tup[l] = tup[l];
-    a.val[l] = val[l];
-  }
-  a.n[a.L + 1] = 1;
-  return a;
-}
-
-template <class B>
-dim3 node_waves(long n, int batch) {
-  return dim3((unsigned)((n + B::NODES - 1) / B::NODES), (unsigned)batch, 1);
-}
-template <class B>
-dim3 bottom_waves(long n, int batch, int run) {
-  return dim3(tile::spread_grid((n + B::NODES - 1) / B::NODES, run), (unsigned)batch, 1);
-}
 template <int N, class R>
-hipError_t wave_value_t(const KProb& kp, const WTree& t, const Work& w, const void* elts, void* S,
-                        void* v, void* maps1, hipStream_t s) {
-  using B = TileB<N, R>;
-  if (t.levels > kTreeMaxLevels) return hipErrorInvalidValue;
-  const int nb = kp.batch, run = tile::bottom_run<B>(t.wc);
-  const dim3 b(64);
-  hipLaunchKernelGGL((tile::kt_vreduce<B>), bottom_waves<B>(t.n[1], nb, run), b, 0, s, t.wc, 1, run,
-                     (const R*)elts, t.n[0], (R*)w.vtup[1], t.n[1]);
-  const tile::MidArgs m = mid_args<B>(t, w.vtup, w.vval);
-  for (int l = 1; l < m.l0; ++l)
-    hipLaunchKernelGGL((tile::kt_vreduce<B>), node_waves<B>(t.n[l + 1], nb), b, 0, s, t.wcs[l], 0, 1,
-                       (const R*)w.vtup[l], t.n[l], (R*)w.vtup[l + 1], t.n[l + 1]);
-  hipLaunchKernelGGL((tile::kt_vmid<B>), dim3(1, nb), dim3(64 * tile::kMidWaves), 0, s, kp, m);
-  for (int l = m.l0 - 1; l >= 1; --l)
-    hipLaunchKernelGGL((tile::kt_vdown<B>), node_waves<B>(t.n[l + 1], nb), b, 0, s, kp, t.wcs[l],
-                       (const R*)w.vtup[l], t.n[l], (const R*)w.vval[l + 1], t.n[l + 1],
-                       (R*)w.vval[l]);
-  hipLaunchKernelGGL((tile::kt_vbottom<B>), bottom_waves<B>(t.n[1], nb, run), b, 0, s, kp, t.wc, run,
-                     (const R*)elts, (const R*)w.vval[1], t.n[1], (R*)S, (R*)v, (R*)maps1,
-                     (R*)(maps1 ? w.bmap : nullptr));
+hipError_t wave_value_t(const KProb& kp, const GTree& t, const Work& w, const void* elts, void* S,
+                        void* v, hipStream_t s) {
+  return tile::launch_value<TileB<N, R>>(kp, t, w, elts, S, v, false, s);
+}
+// x, u of every block from the states of its node (x1), the block maps formed from the elements
+// and S, v.
+template <int N, class R>
+hipError_t wave_tbottom_t(const KProb& kp, const GTree& t, const void* elts, const void* S,
+                          const void* v, const void* x1, void* x, void* u, hipStream_t s) {
+  hipLaunchKernelGGL((kw_tbottom<N, R>), dim3((unsigned)t.n1, kp.batch), dim3(64), 0, s, kp, t.wc,
+                     (const R*)elts, (const R*)S, (const R*)v, (const R*)x1, t.n1, (R*)x, (R*)u);
   return hipGetLastError();
 }
-
 template <int N, class R>
-hipError_t wave_traj_t(const KProb& kp, const WTree& t, const Work& w, const void* elts,
-                       const void* S, const void* v, void* x, void* u, bool maps_ready,
-                       hipStream_t s) {
+hipError_t wave_traj_t(const KProb& kp, const GTree& t, const Work& w, const void* elts,
+                       const void* S, const void* v, void* x, void* u, hipStream_t s) {
+  hipLaunchKernelGGL((kw_tbottom_reduce<N, R>), dim3((unsigned)t.n1, kp.batch), dim3(64), 0, s, kp,
+                     t.wc, (const R*)elts, (const R*)S, (const R*)v, (R*)w.tmap[2], t.n1);
+  const hipError_t e = tile::launch_traj_tree<TileB<N, R>>(kp, t, w, s);
+  if (e != hipSuccess) return e;
+  return wave_tbottom_t<N, R>(kp, t, elts, S, v, w.tx[2], x, u, s);
+}
+template <int N, class R>
+hipError_t wave_scans_t(const KProb& kp, const GTree& t, const Work& w, const void* elts, void* S,
+                        void* v, void* x, void* u, hipStream_t s) {
   using B = TileB<N, R>;
-  if (t.levels > kTreeMaxLevels) return hipErrorInvalidValue;
-  const dim3 b(64);
-  if (!maps_ready)
-    hipLaunchKernelGGL((kw_tbottom_reduce<N, R>), dim3((unsigned)t.n[1], kp.batch), b, 0, s, kp,
-                       t.wc, (const R*)elts, (const R*)S, (const R*)v, (R*)w.tmap[1], t.n[1]);
-  const tile::MidArgs m = mid_args<B>(t, w.tmap, w.tx);
-  for (int l = 1; l < m.l0; ++l)
-    hipLaunchKernelGGL((tile::kt_treduce<B>), node_waves<B>(t.n[l + 1], kp.batch), b, 0, s,
-                       t.wcs[l], (const R*)w.tmap[l], t.n[l], (R*)w.tmap[l + 1], t.n[l + 1]);
-  hipLaunchKernelGGL((tile::kt_tmid<B>), dim3(1, kp.batch), dim3(64 * tile::kMidWaves), 0, s, kp, m);
-  for (int l = m.l0 - 1; l >= 1; --l)
-    hipLaunchKernelGGL((tile::kt_tdown<B>), node_waves<B>(t.n[l + 1], kp.batch), b, 0, s,
-                       t.wcs[l], (const R*)w.tmap[l], t.n[l], (const R*)w.tx[l + 1], t.n[l + 1],
-                       (R*)w.tx[l]);
-  // The block maps kept by the value sweep, when the workspace has room for them; otherwise they
-  // are formed again from the elements and S, v.
-  if (maps_ready && w.bmap) {
-    hipLaunchKernelGGL((tile::kt_tbottom<B>), node_waves<B>(t.n[1], kp.batch), b, 0, s, kp, t.wc,
-                       (const R*)S, (const R*)v, (const R*)w.tx[1], t.n[1], (R*)x, (R*)u,
-                       (const R*)w.bmap);
-  } else {
-    hipLaunchKernelGGL((kw_tbottom<N, R>), dim3((unsigned)t.n[1], kp.batch), b, 0, s, kp, t.wc,
-                       (const R*)elts, (const R*)S, (const R*)v, (const R*)w.tx[1], t.n[1], (R*)x,
-                       (R*)u);
-  }
-  return hipGetLastError();
+  if (w.bmap) return tile::launch_scans<B>(kp, t, w, elts, S, v, x, u, s);
+  hipError_t e = tile::launch_value<B>(kp, t, w, elts, S, v, true, s);
+  if (e == hipSuccess) e = tile::launch_traj_tree<B>(kp, t, w, s);
+  if (e == hipSuccess) e = tile::launch_slot_states<B>(kp, t, w, s);
+  return e != hipSuccess ? e : wave_tbottom_t<N, R>(kp, t, elts, S, v, w.tx[1], x, u, s);
 }
 
 #ifndef LQT_SHARD
@@ -1920,7 +1752,7 @@ struct Fns {
   static const WaveFns* get() {
     if constexpr (wave_shard(N, sizeof(R) == 4) == LQT_SHARD) {
       static const WaveFns f = {wave_build_t<N, R>,       wave_value_t<N, R>,
-                                wave_traj_t<N, R>,
+                                wave_traj_t<N, R>,        wave_scans_t<N, R>,
                                 wave_build_fwd_t<N, R>,   wave_build_split_t<N, R>,
                                 wave_method2_t<N, R>,     wave_dense_t<N, R>,
                                 wave_lti_prep_t<N, R>,    wave_lti_build_t<N, R>};

@@ -113,6 +113,10 @@ struct Q64 {
   static TDEV int col(int r) { return 4 * (r % NT) + (lane_id() & 3); }
   static TDEV int vrow(int v) { return 4 * v + (lane_id() >> 4); }
   static TDEV bool rep() { return (lane_id() & 3) == 0; }
+  // where in a dump of the registers ([r][sub]) register r's transposed entry lies
+  static TDEV int tpos(int r) {
+    return ((r % NT) * NT + r / NT) * LANES + ((lane_id() & 3) << 2) + (lane_id() >> 4);
+  }
   // acc += X^T Y.  UP: the tiles on and above the diagonal only.  it: tile rows of the result (the
   // others are not touched), kt: tiles of inner dimension (the rest of X and Y is zero).
   template <bool UP = false>
@@ -195,6 +199,10 @@ struct W64 {
   static TDEV int col(int) { return lane_id() & 15; }
   static TDEV int vrow(int) { return (lane_id() & 12) + (lane_id() >> 4); }
   static TDEV bool rep() { return (lane_id() & 3) == 0; }
+  static TDEV int tpos(int r) {
+    const int l = lane_id();
+    return ((l & 15) >> 2) * LANES + ((l & 3) << 4) + (l >> 4) + 4 * r;
+  }
   template <bool UP = false>
   static TDEV void mm(R (&acc)[MR], const R (&X)[MR], const R (&Y)[MR], int = NT, int kt = NT) {
     d4 a = {0, 0, 0, 0};
@@ -260,6 +268,10 @@ struct W32 {
   static TDEV int col(int) { return lane_id() & 15; }
   static TDEV int vrow(int v) { return 4 * (lane_id() >> 4) + v; }
   static TDEV bool rep() { return (lane_id() & 15) == 0; }
+  static TDEV int tpos(int r) {
+    const int l = lane_id();
+    return (l & 3) * LANES + ((l & 15) >> 2) * 16 + 4 * (l >> 4) + r;
+  }
   static TDEV f4 pack(const R (&x)[MR]) { return f4{x[0], x[1], x[2], x[3]}; }
   static TDEV void mirror(R (&)[MR]) {}
   template <bool UP = false>
@@ -435,57 +447,57 @@ TDEV Mat<B> sym32(const Mat<B>& M) {
 
 // Loads and stores.  at(i, j): the offset of entry (i, j); entries beyond N and nodes that are not
 // live read as zero (a tuple of zeros is the identity in the A - I form) and are not written.
-template <class B, class F>
-TDEV Mat<B> mload(bool live, const typename B::Mem* g, const F& at) {
+template <class B, class P, class F>
+TDEV Mat<B> mload(bool live, const P* g, const F& at) {
   // lanes beyond N read entry N - 1 and drop it: the loads of a matrix are then one straight run
   Mat<B> m = mzero<B>();
   if (live) {
 #pragma unroll
     for (int r = 0; r < B::MR; ++r) {
       const int i = B::row(r), j = B::col(r);
-      const typename B::Mem v = g[at(min(i, B::N - 1), min(j, B::N - 1))];
+      const P v = g[at(min(i, B::N - 1), min(j, B::N - 1))];
       m.x[r] = i < B::N && j < B::N ? (typename B::R)v : 0;
     }
   }
   return m;
 }
-template <class B, class F>
-TDEV Vec<B> vload(bool live, const typename B::Mem* g, const F& at) {
+template <class B, class P, class F>
+TDEV Vec<B> vload(bool live, const P* g, const F& at) {
   Vec<B> v = vzero<B>();
   if (live) {
 #pragma unroll
     for (int r = 0; r < B::VR; ++r) {
       const int i = B::vrow(r);
-      const typename B::Mem x = g[at(min(i, B::N - 1))];
+      const P x = g[at(min(i, B::N - 1))];
       v.x[r] = i < B::N ? (typename B::R)x : 0;
     }
   }
   return v;
 }
-template <class B, class F>
-TDEV void mstore(bool live, const Mat<B>& m, typename B::Mem* g, const F& at) {
+template <class B, class P, class F>
+TDEV void mstore(bool live, const Mat<B>& m, P* g, const F& at) {
 #pragma unroll
   for (int r = 0; r < B::MR; ++r) {
     const int i = B::row(r), j = B::col(r);
-    if (live && i < B::N && j < B::N) g[at(i, j)] = (typename B::Mem)m.x[r];
+    if (live && i < B::N && j < B::N) g[at(i, j)] = (P)m.x[r];
   }
 }
 // Upper triangle only.
-template <class B, class F>
-TDEV void ustore(bool live, const Mat<B>& m, typename B::Mem* g, const F& at) {
+template <class B, class P, class F>
+TDEV void ustore(bool live, const Mat<B>& m, P* g, const F& at) {
 #pragma unroll
   for (int r = 0; r < B::MR; ++r) {
     const int i = B::row(r), j = B::col(r);
-    if (live && i <= j && j < B::N) g[at(i, j)] = (typename B::Mem)m.x[r];
+    if (live && i <= j && j < B::N) g[at(i, j)] = (P)m.x[r];
   }
 }
-template <class B, class F>
-TDEV void vstore(bool live, const Vec<B>& v, typename B::Mem* g, const F& at) {
+template <class B, class P, class F>
+TDEV void vstore(bool live, const Vec<B>& v, P* g, const F& at) {
   if (!B::rep()) return;
 #pragma unroll
   for (int r = 0; r < B::VR; ++r) {
     const int i = B::vrow(r);
-    if (live && i < B::N) g[at(i)] = (typename B::Mem)v.x[r];
+    if (live && i < B::N) g[at(i)] = (P)v.x[r];
   }
 }
 
@@ -608,8 +620,8 @@ struct Ref {
   long st;
 };
 
-template <class B, bool TRANS>
-TDEV Tup<B> tload(bool live, Ref<const typename B::Mem> f) {
+template <class B, bool TRANS, class P>
+TDEV Tup<B> tload(bool live, Ref<P> f) {
   constexpr int N = B::N, NS = N * (N + 1) / 2, oB = N * N, oC = oB + N, oE = oC + NS, oJ = oE + N;
   const long st = f.st;
   Tup<B> t;
@@ -622,8 +634,8 @@ TDEV Tup<B> tload(bool live, Ref<const typename B::Mem> f) {
 }
 
 // Stores a tuple whose A is held transposed.
-template <class B>
-TDEV void tstore_t(bool live, const Tup<B>& t, Ref<typename B::Mem> f) {
+template <class B, class P>
+TDEV void tstore_t(bool live, const Tup<B>& t, Ref<P> f) {
   constexpr int N = B::N, NS = N * (N + 1) / 2, oB = N * N, oC = oB + N, oE = oC + NS, oJ = oE + N;
   const long st = f.st;
   mstore<B>(live, t.A, f.g, [=](int i, int j) { return (j * N + i) * st; });

@@ -3,10 +3,14 @@
 // side by side and exchanges nothing with other waves; LDS holds only the scratch of the rare
 // pivoted inverse.
 //
-// Trees: node i of level l + 1 is the product of the wcs[l] nodes i wcs[l] .. of level l, combined
-// right to left by one slot of a wave; nodes beyond the end of a level read as the identity.  Tree
-// nodes are records ([batch][n][record]): tuples (NE values, element order), values (S full, v:
-// nx^2 + nx), maps (P = Psi - I, q: nx^2 + nx), states (nx).
+// Trees: a slot of a wave takes c consecutive nodes of a level one after the other, and the slots of
+// a workgroup (a group) are combined pairwise in LDS, so that a stage of the tree reduces c G
+// nodes to one in one launch and 2 c + 2 log2 G steps up and down: a launch costs more than two
+// or three steps, a step more than its arithmetic (chains of dependent matrix products), and the
+// stages of a tree (T = 2^14 blocks at nx = 16: 3; nx <= 8: 2 up to 2^15) are what a short or
+// middle horizon waits for.  What a sweep down needs of a stage are the left-to-right sibling
+// products of its slots, one record per slot.  Records ([batch][n][record]): tuples (NE values,
+// element order), values (S full, v: nx^2 + nx), maps (P = Psi - I, q: nx^2 + nx), states (nx).
 #pragma once
 
 #include "tile.hpp"
@@ -28,9 +32,9 @@ TDEV Ref<R> elt_ref(R* elts, int p, long k, long T) {
   return {elts + ((p * nt + k / kEltT) * kNE<N>)*kEltT + ((k & 7) << 6) + ((k & 511) >> 3), kEltT};
 }
 
-// Waves of one launch are dealt to the eight XCDs in turn (workgroup w to XCD w % 8), each with its
-// own L2.  Wave w takes group of slots `spread(w, run)`: runs of `run` consecutive groups, whose
-// element columns share 128-byte lines, go to one XCD.  The grid is a multiple of 8 run waves.
+// Workgroups of one launch are dealt to the eight XCDs in turn (workgroup w to XCD w % 8), each with
+// its own L2.  Workgroup w takes group `spread(w, run)`: runs of `run` consecutive groups, whose
+// element columns share 128-byte lines, go to one XCD.  The grid is a multiple of 8 run.
 TDEV long spread(long w, int run) {
   const long blk = 8L * run;
   return (w / blk) * blk + (w % 8) * run + (w % blk) / 8;
@@ -38,13 +42,18 @@ TDEV long spread(long w, int run) {
 inline unsigned spread_grid(long groups, int run) {
   return (unsigned)((groups + 8L * run - 1) / (8L * run) * (8L * run));
 }
-// Run length for the bottom level: 16 (FP64) or 32 (FP32) element columns to a line, a column per
-// 8 blocks, B::NODES nodes of wc blocks per wave.
+// Waves and slots of a group, and the run length of the bottom stage: 16 (FP64) or 32 (FP32)
+// element columns to a line, a column per 8 blocks, wc blocks per slot.
+// One wave a SIMD (the steps of a group are serial, and two waves of matrix instructions on a SIMD
+// wait for each other); two for nx <= 4, whose steps are short.
+template <class B>
+constexpr int kGroupWaves = B::N <= 4 ? 8 : 4;
+template <class B>
+constexpr int kGroup = kGroupWaves<B> * B::NODES;
 template <class B>
 constexpr int bottom_run(int wc) {
-  return (int)(128 / sizeof(typename B::Mem)) * 8 / wc / B::NODES > 0
-             ? (int)(128 / sizeof(typename B::Mem)) * 8 / wc / B::NODES
-             : 1;
+  const int run = (int)(128 / sizeof(typename B::Mem)) * 8 / (wc * kGroup<B>);
+  return run > 0 ? run : 1;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -214,66 +223,208 @@ __global__ __launch_bounds__(64, 2) void kt_build(const KProb kp, typename B::Me
 // ------------------------------------------------------------------------------------------
 // Value scan (Theorem 6).
 // ------------------------------------------------------------------------------------------
-template <class B>
-TDEV Ref<typename B::Mem> rec(typename B::Mem* r, int p, long i, long n) {
-  return {r + ((long)p * n + i) * kNE<B::N>, 1};
+template <class P>
+TDEV Ref<P> rec(P* r, int size, long i) {
+  return {r + i * size, 1};
 }
-template <class B>
-TDEV void vrec_store(bool live, const Mat<B>& S, const Vec<B>& v, typename B::Mem* g) {
+template <class B, class P>
+TDEV void vrec_store(bool live, const Mat<B>& S, const Vec<B>& v, P* g) {
   constexpr int N = B::N;
   // symmetric: the upper entries, mirrored
   ustore<B>(live, S, g, [](int i, int j) { return i * N + j; });
   ustore<B>(live, S, g, [](int i, int j) { return j * N + i; });
   vstore<B>(live, v, g + N * N, [](int i) { return i; });
 }
-template <class B>
-TDEV void vrec_load(bool live, Mat<B>& S, Vec<B>& v, const typename B::Mem* g) {
+template <class B, class P>
+TDEV void vrec_load(bool live, Mat<B>& S, Vec<B>& v, const P* g) {
   constexpr int N = B::N;
   S = mload<B>(live, g, [](int i, int j) { return i * N + j; });
   v = vload<B>(live, g + N * N, [](int i) { return i; });
 }
 
-// Node i of level l + 1: the product of its wc children (elements when src_elts).
+// One stage of a tree: slot i takes the nodes i c .. of n_src, group g the slots g G ...
+struct Stage {
+  int c = 1;
+  long n_src = 0, n_slot = 0, n_grp = 0;
+};
+// The slots of group g, and this wave's slot of them.
 template <class B>
-TDEV void t_vreduce(typename B::R* scr, int p, long i, int wc, bool src_elts,
-                    const typename B::Mem* src, long n_src, typename B::Mem* dst, long n_dst) {
-  using R = typename B::R;
-  using Mem = typename B::Mem;
-  auto ref = [&](long j) -> Ref<const Mem> {
-    if (src_elts) {
-      const Ref<const Mem> f = elt_ref<const Mem, B::N>(src, p, j, n_src);
-      return f;
-    }
-    return {src + ((long)p * n_src + j) * kNE<B::N>, 1};
-  };
-  const bool live = i < n_dst;
-  const long j0 = i * wc;
-  auto ok = [&](long j) { return live && j < n_src; };
-  Tup<B> acc = tload<B, true>(ok(j0 + wc - 1), ref(j0 + wc - 1));
-  Tup<B> nxt = tload<B, false>(ok(j0 + wc - 2), ref(j0 + wc - 2));
-#pragma unroll 1
-  for (int c = wc - 2; c >= 0; --c) {
-    const Tup<B> x = nxt;
-    if (c > 0) nxt = tload<B, false>(ok(j0 + c - 1), ref(j0 + c - 1));
-    acc = combine<B>(x, acc, scr);
+struct Here {
+  int w, p;    // wave, problem
+  long g, i;   // group, slot
+  int cnt;     // slots of the group
+  int loc;     // i within the group
+  bool live;
+  TDEV Here(const Stage& st, long g_, int p_) : p(p_), g(g_) {
+    w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    cnt = (int)min((long)kGroup<B>, st.n_slot - g * kGroup<B>);
+    loc = w * B::NODES + B::node();
+    i = g * kGroup<B> + loc;
+    live = loc < cnt;
   }
-  tstore_t<B>(live, acc, rec<B>(dst, p, i, n_dst));
+};
+
+// Barrier of the workgroup for what is exchanged in LDS: loads from and stores to memory stay in
+// flight (__syncthreads would wait for them: 7 instead of 3 us a round at nx = 16).
+TDEV void lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// What the waves of a group exchange in LDS: dumps of a node's registers, so that neither side has
+// entries to mask or offsets to compute.
 template <class B>
-__global__ __launch_bounds__(64) void kt_vreduce(int wc, int src_elts, int run,
-                                                 const typename B::Mem* __restrict__ src, long n_src,
-                                                 typename B::Mem* __restrict__ dst, long n_dst) {
-  __shared__ typename B::R scr[kInvScr<B>];
-  const long g = run > 1 ? spread(blockIdx.x, run) : (long)blockIdx.x;
-  if (g * B::NODES >= n_dst) return;
-  t_vreduce<B>(scr, blockIdx.y, g * B::NODES + B::node(), wc, src_elts, src, n_src, dst, n_dst);
+constexpr int kDumpT = (3 * B::MR + 2 * B::VR) * B::LANES;
+template <class B>
+constexpr int kDumpV = (B::MR + B::VR) * B::LANES;  // values and maps
+template <class B>
+constexpr int kDumpX = B::VR * B::LANES;
+template <class B, int CNT>
+TDEV void put(const typename B::R (&x)[CNT], typename B::R* g) {
+#pragma unroll
+  for (int r = 0; r < CNT; ++r) g[r * B::LANES] = x[r];
+}
+template <class B, int CNT>
+TDEV void get(typename B::R (&x)[CNT], const typename B::R* g) {
+#pragma unroll
+  for (int r = 0; r < CNT; ++r) x[r] = g[r * B::LANES];
+}
+template <class B>
+TDEV void get_t(Mat<B>& m, const typename B::R* node) {  // transposed
+#pragma unroll
+  for (int r = 0; r < B::MR; ++r) m.x[r] = node[B::tpos(r)];
+}
+template <class B>
+TDEV void dump(const Tup<B>& t, typename B::R* node) {
+  typename B::R* g = node + B::sub();
+  constexpr int M = B::MR * B::LANES;
+  put<B>(t.A.x, g);
+  put<B>(t.C.x, g + M);
+  put<B>(t.J.x, g + 2 * M);
+  put<B>(t.b.x, g + 3 * M);
+  put<B>(t.e.x, g + 3 * M + kDumpX<B>);
+}
+template <class B, bool TRANS>  // TRANS: A transposed against what was dumped
+TDEV Tup<B> undump(const typename B::R* node) {
+  const typename B::R* g = node + B::sub();
+  constexpr int M = B::MR * B::LANES;
+  Tup<B> t;
+  if (TRANS)
+    get_t<B>(t.A, node);
+  else
+    get<B>(t.A.x, g);
+  get<B>(t.C.x, g + M);
+  get<B>(t.J.x, g + 2 * M);
+  get<B>(t.b.x, g + 3 * M);
+  get<B>(t.e.x, g + 3 * M + kDumpX<B>);
+  return t;
+}
+template <class B>
+TDEV void vdump(const Mat<B>& S, const Vec<B>& v, typename B::R* node) {
+  put<B>(S.x, node + B::sub());
+  put<B>(v.x, node + B::MR * B::LANES + B::sub());
+}
+template <class B, bool TRANS = false>
+TDEV void vundump(Mat<B>& S, Vec<B>& v, const typename B::R* node) {
+  if (TRANS)
+    get_t<B>(S, node);
+  else
+    get<B>(S.x, node + B::sub());
+  get<B>(v.x, node + B::MR * B::LANES + B::sub());
+}
+
+// Product of the c nodes of slot i, the right one first; transposed (see Tup).
+template <class B>
+TDEV Tup<B> t_serial(const Here<B>& h, const Stage& st, bool src_elts, const typename B::Mem* src,
+                     typename B::R* scr) {
+  using Mem = typename B::Mem;
+  auto ref = [&](long j) -> Ref<const Mem> {
+    if (src_elts) return elt_ref<const Mem, B::N>(src, h.p, j, st.n_src);
+    return rec(src, kNE<B::N>, (long)h.p * st.n_src + j);
+  };
+  const int c = st.c;
+  const long j0 = h.i * c;
+  auto ok = [&](long j) { return h.live && j < st.n_src; };
+  Tup<B> acc = tload<B, true>(ok(j0 + c - 1), ref(j0 + c - 1));
+  if (c == 1) return acc;
+  Tup<B> nxt = tload<B, false>(ok(j0 + c - 2), ref(j0 + c - 2));
+#pragma unroll 1
+  for (int q = c - 2; q >= 0; --q) {
+    const Tup<B> x = nxt;
+    if (q > 0) nxt = tload<B, false>(ok(j0 + q - 1), ref(j0 + q - 1));
+    acc = combine<B>(x, acc, scr);
+  }
+  return acc;
+}
+
+// Pair q of a round of distance s: places 2 s q and 2 s q + s of a group of cnt slots.  A node
+// without a pair takes the first one's operands and stores nothing.
+template <class B>
+struct Pair {
+  int r;
+  bool any, on;  // a pair in the wave, in the node
+  TDEV Pair(const Here<B>& h, int s) {
+    r = 2 * s * (h.w * B::NODES + B::node());
+    any = 2 * s * h.w * B::NODES + s < h.cnt;
+    on = r + s < h.cnt;
+    if (!on) r = 0;
+  }
+};
+
+// Group product of the slots' products.  Slot loc sits at place cnt - 1 - loc of ex (the last slot
+// at place 0): a round of distance s combines places 2 s q (right) and 2 s q + s (left) into the
+// former, whose product until then, the right sibling of place 2 s q + s, is kept in
+// sib[2 s q + s] for the sweep down.  The root has no use for the product of all of its slots.
+template <class B>
+TDEV void t_vup(const Here<B>& h, typename B::R (*ex)[kDumpT<B>], typename B::Mem* sib, bool root,
+                typename B::R* scr) {
+#pragma unroll 1
+  for (int s = 1; s < h.cnt; s *= 2) {
+    lds_sync();
+    const Pair<B> q(h, s);
+    if (!q.any) continue;
+    Tup<B> acc = undump<B, false>(ex[q.r]);
+    tstore_t<B>(q.on, acc, rec(sib, kNE<B::N>, q.r + s));
+    if (root && 2 * s >= h.cnt) continue;
+    acc = combine<B>(undump<B, true>(ex[q.r + s]), acc, scr);
+    if (q.on) dump<B>(acc, ex[q.r]);
+  }
+  __syncthreads();
+}
+
+// The value at the right end of every slot (val, by place) from that at place 0: the reverse rounds.
+template <class B>
+TDEV void t_vdown(const Here<B>& h, typename B::R (*val)[kDumpV<B>], const typename B::Mem* sib,
+                  typename B::R* scr) {
+  int s = 1;
+  while (2 * s < h.cnt) s *= 2;
+  auto load = [&](int s_) {
+    const Pair<B> q(h, s_);
+    return tload<B, false>(q.on, rec(sib, kNE<B::N>, q.r + s_));
+  };
+  if (h.cnt > 1) {
+    Tup<B> nxt = load(s);
+#pragma unroll 1
+    for (; s >= 1; s /= 2) {
+      const Tup<B> a = nxt;
+      if (s > 1) nxt = load(s / 2);
+      lds_sync();
+      const Pair<B> q(h, s);
+      if (!q.any) continue;
+      Mat<B> S;
+      Vec<B> v;
+      vundump<B>(S, v, val[q.r]);
+      fold<B>(a, S, v, scr);
+      if (q.on) vdump<B>(S, v, val[q.r + s]);
+    }
+  }
+  lds_sync();
 }
 
 // The terminal value (Sec. IV-D) of problem p: the value at the right end of the tree's root.
 template <class B>
 TDEV void t_terminal(const KProb& kp, int p, bool live, Mat<B>& S, Vec<B>& v) {
-  using R = typename B::R;
   using Mem = typename B::Mem;
   constexpr int N = B::N;
   const Mem* Qf = (const Mem*)kp.Qf + (long)p * N * N;
@@ -282,116 +433,153 @@ TDEV void t_terminal(const KProb& kp, int p, bool live, Mat<B>& S, Vec<B>& v) {
   v = mv0<B>(QT, vload<B>(live, (const Mem*)kp.rf + (long)p * N, [](int i) { return i; }));
 }
 
-// Values at the right ends of the children of node i of level l + 1, from the node's own (root:
-// from the terminal value).
+// Place 0 of a group's values: the terminal value (root) or val_in, the group's own.
 template <class B>
-TDEV void t_vdown(const KProb& kp, typename B::R* scr, int p, long i, int wc, bool root,
-                  const typename B::Mem* tup, long n_child, const typename B::Mem* val_in, long n_par,
-                  typename B::Mem* val_out) {
-  using R = typename B::R;
-  using Mem = typename B::Mem;
-  const bool live = i < n_par;
-  const long j0 = i * wc;
-  auto ok = [&](long j) { return live && j < n_child; };
-  auto ref = [&](long j) -> Ref<const Mem> {
-    return {tup + ((long)p * n_child + j) * kNE<B::N>, 1};
-  };
+TDEV void t_vtop(const KProb& kp, const Here<B>& h, bool root, const typename B::Mem* val_in,
+                 typename B::R (*val)[kDumpV<B>]) {
+  if (h.w) return;
+  const bool on = B::node() == 0;
   Mat<B> S;
   Vec<B> v;
   if (root)
-    t_terminal<B>(kp, p, live, S, v);
+    t_terminal<B>(kp, h.p, on, S, v);
   else
-    vrec_load<B>(live, S, v, val_in + ((long)p * n_par + i) * kVR<B::N>);
-  Tup<B> nxt = tload<B, false>(ok(j0 + wc - 1), ref(j0 + wc - 1));
+    vrec_load<B>(on, S, v, val_in);
+  if (on) vdump<B>(S, v, val[0]);
+}
+
+// Values at the right ends of the c nodes of a slot from the slot's.
+template <class B>
+TDEV void t_vspread(const Here<B>& h, const Stage& st, const typename B::Mem* src,
+                    const typename B::R (*val)[kDumpV<B>], typename B::Mem* val_out,
+                    typename B::R* scr) {
+  using Mem = typename B::Mem;
+  if (h.w * B::NODES >= h.cnt) return;
+  const int c = st.c;
+  const long j0 = h.i * c;
+  auto ok = [&](long j) { return h.live && j < st.n_src; };
+  auto ref = [&](long j) -> Ref<const Mem> {
+    return rec(src, kNE<B::N>, (long)h.p * st.n_src + j);
+  };
+  Tup<B> nxt = tload<B, false>(c > 1 && ok(j0 + c - 1), ref(j0 + c - 1));
+  Mat<B> S;
+  Vec<B> v;
+  vundump<B>(S, v, val[h.live ? h.cnt - 1 - h.loc : 0]);
 #pragma unroll 1
-  for (int c = wc - 1; c >= 0; --c) {
-    const long j = j0 + c;
-    vrec_store<B>(ok(j), S, v, val_out + ((long)p * n_child + j) * kVR<B::N>);
-    if (c == 0) break;
+  for (int q = c - 1; q >= 0; --q) {
+    const long j = j0 + q;
+    vrec_store<B>(ok(j), S, v, val_out + ((long)h.p * st.n_src + j) * kVR<B::N>);
+    if (q == 0) break;
     const Tup<B> a = nxt;
-    if (c > 1) nxt = tload<B, false>(ok(j - 1), ref(j - 1));
+    if (q > 1) nxt = tload<B, false>(ok(j - 1), ref(j - 1));
     fold<B>(a, S, v, scr);
   }
 }
 
+// Reduction of a stage: the groups' products and their slots' sibling records.
 template <class B>
-__global__ __launch_bounds__(64) void kt_vdown(const KProb kp, int wc,
-                                               const typename B::Mem* __restrict__ tup, long n_child,
-                                               const typename B::Mem* __restrict__ val_in, long n_par,
-                                               typename B::Mem* __restrict__ val_out) {
-  __shared__ typename B::R scr[kInvScr<B>];
-  t_vdown<B>(kp, scr, blockIdx.y, (long)blockIdx.x * B::NODES + B::node(), wc, false, tup, n_child,
-             val_in, n_par, val_out);
+__global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_vup(const Stage st, int src_elts, int run,
+                                                           const typename B::Mem* __restrict__ src,
+                                                           typename B::Mem* __restrict__ sib,
+                                                           typename B::Mem* __restrict__ grp) {
+  constexpr int NE = kNE<B::N>;
+  __shared__ typename B::R ex[kGroup<B>][kDumpT<B>], scr_all[kGroupWaves<B>][kInvScr<B>];
+  const long g = run > 1 ? spread(blockIdx.x, run) : (long)blockIdx.x;
+  if (g >= st.n_grp) return;
+  const Here<B> h(st, g, blockIdx.y);
+  typename B::R* scr = scr_all[h.w];
+  if (h.w * B::NODES < h.cnt) {
+    const Tup<B> acc = t_serial<B>(h, st, src_elts, src, scr);
+    if (h.live) dump<B>(acc, ex[h.cnt - 1 - h.loc]);
+  }
+  t_vup<B>(h, ex, sib + ((long)h.p * st.n_slot + g * kGroup<B>)*NE, false, scr);
+  if (h.w == 0)
+    tstore_t<B>(B::node() == 0, undump<B, false>(ex[0]), rec(grp, NE, (long)h.p * st.n_grp + g));
 }
 
-// The upper levels of a value tree in one workgroup per problem: levels l0 .. L reduced (the root,
-// above level L, needs no product of its own), then the terminal value carried back down to the
-// values at level l0.
-constexpr int kMidWaves = 8;
-struct MidArgs {
-  int l0 = 0, L = 0;
-  int wcs[kTreeMaxLevels + 2] = {};
-  long n[kTreeMaxLevels + 2] = {};
-  void* tup[kTreeMaxLevels + 2] = {};  // tuples (value) or maps (trajectory) of level l
-  void* val[kTreeMaxLevels + 2] = {};  // values or states of level l
-};
-
+// The root stage: up, and down to the values of its nodes.
 template <class B>
-__global__ __launch_bounds__(64 * kMidWaves) void kt_vmid(const KProb kp, const MidArgs a) {
-  using R = typename B::R;
-  using Mem = typename B::Mem;
-  __shared__ R scr_all[kMidWaves][kInvScr<B>];
-  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), p = blockIdx.y;
-  R* scr = scr_all[w];
-  for (int l = a.l0; l < a.L; ++l) {
-    for (long g = w; g * B::NODES < a.n[l + 1]; g += kMidWaves)
-      t_vreduce<B>(scr, p, g * B::NODES + B::node(), a.wcs[l], false, (const Mem*)a.tup[l], a.n[l],
-                   (Mem*)a.tup[l + 1], a.n[l + 1]);
-    __syncthreads();
+__global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_vroot(const KProb kp, const Stage st,
+                                                             const typename B::Mem* src,
+                                                             typename B::Mem* sib,
+                                                             typename B::Mem* __restrict__ val_out) {
+  constexpr int NE = kNE<B::N>;
+  __shared__ typename B::R ex[kGroup<B>][kDumpT<B>], scr_all[kGroupWaves<B>][kInvScr<B>];
+  const Here<B> h(st, 0, blockIdx.y);
+  typename B::R* scr = scr_all[h.w];
+  if (h.w * B::NODES < h.cnt) {
+    const Tup<B> acc = t_serial<B>(h, st, false, src, scr);
+    if (h.live) dump<B>(acc, ex[h.cnt - 1 - h.loc]);
   }
-  for (int l = a.L; l >= a.l0; --l) {
-    for (long g = w; g * B::NODES < a.n[l + 1]; g += kMidWaves)
-      t_vdown<B>(kp, scr, p, g * B::NODES + B::node(), a.wcs[l], l == a.L, (const Mem*)a.tup[l],
-                 a.n[l], (const Mem*)a.val[l + 1], a.n[l + 1], (Mem*)a.val[l]);
-    __syncthreads();
-  }
+  typename B::Mem* sb = sib + (long)h.p * st.n_slot * NE;
+  t_vup<B>(h, ex, sb, true, scr);
+  auto val = (typename B::R(*)[kDumpV<B>])ex[0];
+  t_vtop<B>(kp, h, true, sb, val);
+  t_vdown<B>(h, val, sb, scr);
+  t_vspread<B>(h, st, src, val, val_out, scr);
 }
 
-// Values of every block from the value at the right end of each level-1 node; the composed
-// closed-loop map of the node's blocks (maps1) and every block's own map (bmaps) when given.
+// Values of a stage's nodes from those of its groups.
 template <class B>
-__global__ __launch_bounds__(64) void kt_vbottom(const KProb kp, int wc, int run,
-                                                 const typename B::Mem* __restrict__ elts,
-                                                 const typename B::Mem* __restrict__ val1, long n1,
-                                                 typename B::Mem* __restrict__ Sout,
-                                                 typename B::Mem* __restrict__ vout,
-                                                 typename B::Mem* __restrict__ maps1,
-                                                 typename B::Mem* __restrict__ bmaps) {
-  using R = typename B::R;
+__global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_vdown(
+    const KProb kp, const Stage st, const typename B::Mem* __restrict__ src,
+    const typename B::Mem* __restrict__ sib, const typename B::Mem* __restrict__ val_in,
+    typename B::Mem* __restrict__ val_out) {
+  __shared__ typename B::R val[kGroup<B>][kDumpV<B>], scr_all[kGroupWaves<B>][kInvScr<B>];
+  const Here<B> h(st, blockIdx.x, blockIdx.y);
+  typename B::R* scr = scr_all[h.w];
+  t_vtop<B>(kp, h, st.n_grp == 1, val_in + ((long)h.p * st.n_grp + h.g) * kVR<B::N>, val);
+  t_vdown<B>(h, val, sib + ((long)h.p * st.n_slot + h.g * kGroup<B>)*kNE<B::N>, scr);
+  t_vspread<B>(h, st, src, val, val_out, scr);
+}
+
+// ------------------------------------------------------------------------------------------
+// Trajectory (Method 1, Sec. IV-E): maps composed up a tree, states carried down.  Here the places
+// of a group are its slots in time order.
+// ------------------------------------------------------------------------------------------
+template <class B, bool TRANS, class P>
+TDEV Map<B> map_load(bool live, const P* g) {
+  constexpr int N = B::N;
+  return {mload<B>(live, g, [](int i, int j) { return TRANS ? j * N + i : i * N + j; }),
+          vload<B>(live, g + N * N, [](int i) { return i; })};
+}
+template <class B, class P>  // m.P transposed
+TDEV void map_store_t(bool live, const Map<B>& m, P* g) {
+  constexpr int N = B::N;
+  mstore<B>(live, m.P, g, [](int i, int j) { return j * N + i; });
+  vstore<B>(live, m.q, g + N * N, [](int i) { return i; });
+}
+
+// Values of every block of a slot from the one at its right end, and the composed closed-loop map
+// of the blocks (transposed) when asked for; every block's own map in bmaps when given.
+template <class B>
+TDEV Map<B> t_vbottom(const KProb& kp, const Here<B>& h, int wc, const typename B::Mem* elts,
+                      const typename B::R (*val)[kDumpV<B>], typename B::Mem* Sout,
+                      typename B::Mem* vout, typename B::Mem* bmaps, bool compose,
+                      typename B::R* scr) {
   using Mem = typename B::Mem;
   constexpr int N = B::N;
-  __shared__ R scr[kInvScr<B>];
-  const long g = run > 1 ? spread(blockIdx.x, run) : (long)blockIdx.x;
-  if (g * B::NODES >= n1) return;
-  const int p = blockIdx.y;
-  const long T = kp.T, i = g * B::NODES + B::node();
-  const bool live = i < n1;
-  const long j0 = i * wc;
+  const long T = kp.T;
+  const int p = h.p;
+  const bool live = h.live;
+  const long j0 = h.i * wc;
   auto ok = [&](long k) { return live && k < T; };
   auto ref = [&](long k) -> Ref<const Mem> { return elt_ref<const Mem, N>(elts, p, k, T); };
   Mem* Sp = Sout + (long)p * (T + 1) * N * N;
   Mem* vp = vout + (long)p * (T + 1) * N;
   auto put = [&](bool on, long k, const Mat<B>& S, const Vec<B>& v) {
+    vstore<B>(on, v, vp + k * N, [](int a) { return a; });
     ustore<B>(on, S, Sp + k * N * N, [](int a, int b) { return a * N + b; });
     ustore<B>(on, S, Sp + k * N * N, [](int a, int b) { return b * N + a; });
-    vstore<B>(on, v, vp + k * N, [](int a) { return a; });
   };
   Mat<B> S;
   Vec<B> v;
-  vrec_load<B>(live, S, v, val1 + ((long)p * n1 + i) * kVR<N>);
-  if (!kp.seg) put(live && j0 + wc >= T, T, S, v);
+  vundump<B>(S, v, val[live ? h.cnt - 1 - h.loc : 0]);
+  if (compose) lds_sync();  // the maps take the place of the values
   Map<B> acc{mzero<B>(), vzero<B>()};  // P transposed
+  if (h.w * B::NODES >= h.cnt) return acc;
   Tup<B> nxt = tload<B, false>(ok(j0 + wc - 1), ref(j0 + wc - 1));
+  if (!kp.seg) put(live && j0 + wc >= T, T, S, v);
 #pragma unroll 1
   for (int c = wc - 1; c >= 0; --c) {
     const long k = j0 + c;
@@ -404,113 +592,191 @@ __global__ __launch_bounds__(64) void kt_vbottom(const KProb kp, int wc, int run
       mstore<B>(ok(k), m.P, b, [](int x, int y) { return x * N + y; });
       vstore<B>(ok(k), m.q, b + N * N, [](int x) { return x; });
     }
-    if (maps1) map_after<B>(acc, m);
+    if (compose) map_after<B>(acc, m);
   }
-  if (maps1) {
-    Mem* b = maps1 + ((long)p * n1 + i) * kVR<N>;
-    mstore<B>(live, acc.P, b, [](int x, int y) { return y * N + x; });
-    vstore<B>(live, acc.q, b + N * N, [](int x) { return x; });
-  }
+  return acc;
 }
 
-// ------------------------------------------------------------------------------------------
-// Trajectory (Method 1, Sec. IV-E): maps composed up a tree, states carried down.
-// ------------------------------------------------------------------------------------------
-template <class B, bool TRANS>
-TDEV Map<B> map_load(bool live, const typename B::Mem* g) {
-  constexpr int N = B::N;
-  return {mload<B>(live, g, [](int i, int j) { return TRANS ? j * N + i : i * N + j; }),
-          vload<B>(live, g + N * N, [](int i) { return i; })};
-}
-
+// Group map: a round of distance s composes places 2 s q (earlier) and 2 s q + s into the former,
+// whose map until then, the left sibling of place 2 s q + s, is kept in sib[2 s q + s].  The dumps
+// hold P transposed.
 template <class B>
-TDEV void t_treduce(int p, long i, int wc, const typename B::Mem* src, long n_src,
-                    typename B::Mem* dst, long n_dst) {
-  constexpr int N = B::N;
-  const bool live = i < n_dst;
-  const long j0 = i * wc;
-  auto at = [&](long j) { return src + ((long)p * n_src + j) * kVR<N>; };
-  auto ok = [&](long j) { return live && j < n_src; };
-  Map<B> acc = map_load<B, true>(ok(j0 + wc - 1), at(j0 + wc - 1));
+TDEV void t_tup(const Here<B>& h, typename B::R (*ex)[kDumpV<B>], typename B::Mem* sib, bool root) {
+  constexpr int VR = kVR<B::N>, N = B::N;
 #pragma unroll 1
-  for (int c = wc - 2; c >= 0; --c) map_after<B>(acc, map_load<B, false>(ok(j0 + c), at(j0 + c)));
-  typename B::Mem* b = dst + ((long)p * n_dst + i) * kVR<N>;
-  mstore<B>(live, acc.P, b, [](int x, int y) { return y * N + x; });
-  vstore<B>(live, acc.q, b + N * N, [](int x) { return x; });
+  for (int s = 1; s < h.cnt; s *= 2) {
+    lds_sync();
+    const Pair<B> q(h, s);
+    if (!q.any) continue;
+    Map<B> m, acc;
+    vundump<B, true>(m.P, m.q, ex[q.r]);
+    typename B::Mem* g = sib + (long)(q.r + s) * VR;
+    mstore<B>(q.on, m.P, g, [](int i, int j) { return i * N + j; });
+    vstore<B>(q.on, m.q, g + N * N, [](int i) { return i; });
+    if (root && 2 * s >= h.cnt) continue;
+    vundump<B>(acc.P, acc.q, ex[q.r + s]);
+    map_after<B>(acc, m);
+    if (q.on) vdump<B>(acc.P, acc.q, ex[q.r]);
+  }
+  __syncthreads();
+}
+template <class B>
+TDEV void t_tgroup(const typename B::R (*ex)[kDumpV<B>], typename B::Mem* grp) {
+  Map<B> m;
+  vundump<B>(m.P, m.q, ex[0]);
+  map_store_t<B>(B::node() == 0, m, grp);
 }
 
+// The state at the left end of every slot from that at place 0.
 template <class B>
-__global__ __launch_bounds__(64) void kt_treduce(int wc, const typename B::Mem* __restrict__ src,
-                                                 long n_src, typename B::Mem* __restrict__ dst,
-                                                 long n_dst) {
-  t_treduce<B>(blockIdx.y, (long)blockIdx.x * B::NODES + B::node(), wc, src, n_src, dst, n_dst);
-}
-
-template <class B>
-TDEV void t_tdown(int p, long i, int wc, const typename B::Mem* maps, long n_child,
-                  const typename B::Mem* x_in, long n_par, typename B::Mem* x_out) {
-  constexpr int N = B::N;
-  const bool live = i < n_par;
-  const long j0 = i * wc;
-  auto ok = [&](long j) { return live && j < n_child; };
-  Vec<B> x = vload<B>(live, x_in + ((long)p * n_par + i) * N, [](int q) { return q; });
+TDEV void t_tdown(const Here<B>& h, typename B::R (*xs)[kDumpX<B>], const typename B::Mem* sib) {
+  int s = 1;
+  while (2 * s < h.cnt) s *= 2;
+  auto load = [&](int s_) {
+    const Pair<B> q(h, s_);
+    return map_load<B, true>(q.on, sib + (long)(q.r + s_) * kVR<B::N>);
+  };
+  if (h.cnt > 1) {
+    Map<B> nxt = load(s);
 #pragma unroll 1
-  for (int c = 0; c < wc; ++c) {
-    const long j = j0 + c;
-    vstore<B>(ok(j), x, x_out + ((long)p * n_child + j) * N, [](int q) { return q; });
-    if (c + 1 < wc)
-      x = map_apply<B>(map_load<B, true>(ok(j), maps + ((long)p * n_child + j) * kVR<N>), x);
+    for (; s >= 1; s /= 2) {
+      const Map<B> m = nxt;
+      if (s > 1) nxt = load(s / 2);
+      lds_sync();
+      const Pair<B> q(h, s);
+      if (!q.any) continue;
+      Vec<B> x;
+      get<B>(x.x, xs[q.r] + B::sub());
+      x = map_apply<B>(m, x);
+      if (q.on) put<B>(x.x, xs[q.r + s] + B::sub());
+    }
+  }
+  lds_sync();
+}
+
+// Place 0 of a group's states: x0 (root) or x_in, the group's own.
+template <class B>
+TDEV void t_ttop(const KProb& kp, const Here<B>& h, bool root, const typename B::Mem* x_in,
+                 typename B::R (*xs)[kDumpX<B>]) {
+  if (h.w) return;
+  const bool on = B::node() == 0;
+  const typename B::Mem* g = root ? (const typename B::Mem*)kp.x0 + (long)h.p * B::N : x_in;
+  const Vec<B> x = vload<B>(on, g, [](int i) { return i; });
+  if (on) put<B>(x.x, xs[0] + B::sub());
+}
+
+// Composed map of a slot's c nodes into its place.
+template <class B>
+TDEV void t_tserial(const Here<B>& h, const Stage& st, const typename B::Mem* src,
+                    typename B::R (*ex)[kDumpV<B>]) {
+  const int c = st.c;
+  const long j0 = h.i * c;
+  auto at = [&](long j) { return src + ((long)h.p * st.n_src + j) * kVR<B::N>; };
+  auto ok = [&](long j) { return h.live && j < st.n_src; };
+  Map<B> acc = map_load<B, true>(ok(j0 + c - 1), at(j0 + c - 1));
+#pragma unroll 1
+  for (int q = c - 2; q >= 0; --q) map_after<B>(acc, map_load<B, false>(ok(j0 + q), at(j0 + q)));
+  if (h.live) vdump<B>(acc.P, acc.q, ex[h.loc]);
+}
+
+// States at the left ends of the c nodes of a slot from the slot's.
+template <class B>
+TDEV void t_tspread(const Here<B>& h, const Stage& st, const typename B::Mem* src,
+                    const typename B::R (*xs)[kDumpX<B>], typename B::Mem* x_out) {
+  constexpr int N = B::N;
+  const int c = st.c;
+  const long j0 = h.i * c;
+  auto ok = [&](long j) { return h.live && j < st.n_src; };
+  auto vec = [](int i) { return i; };
+  Vec<B> x;
+  get<B>(x.x, xs[h.live ? h.loc : 0] + B::sub());
+#pragma unroll 1
+  for (int q = 0; q < c; ++q) {
+    const long j = (long)h.p * st.n_src + j0 + q;
+    vstore<B>(ok(j0 + q), x, x_out + j * N, vec);
+    if (q + 1 < c) x = map_apply<B>(map_load<B, true>(ok(j0 + q), src + j * kVR<N>), x);
   }
 }
 
 template <class B>
-__global__ __launch_bounds__(64) void kt_tdown(int wc, const typename B::Mem* __restrict__ maps,
-                                               long n_child,
-                                               const typename B::Mem* __restrict__ x_in, long n_par,
-                                               typename B::Mem* __restrict__ x_out) {
-  t_tdown<B>(blockIdx.y, (long)blockIdx.x * B::NODES + B::node(), wc, maps, n_child, x_in, n_par,
-             x_out);
+__global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_tup(const Stage st,
+                                                           const typename B::Mem* __restrict__ src,
+                                                           typename B::Mem* __restrict__ sib,
+                                                           typename B::Mem* __restrict__ grp) {
+  constexpr int VR = kVR<B::N>;
+  __shared__ typename B::R ex[kGroup<B>][kDumpV<B>];
+  const Here<B> h(st, blockIdx.x, blockIdx.y);
+  t_tserial<B>(h, st, src, ex);
+  t_tup<B>(h, ex, sib + ((long)h.p * st.n_slot + h.g * kGroup<B>)*VR, false);
+  if (h.w == 0) t_tgroup<B>(ex, grp + ((long)h.p * st.n_grp + h.g) * VR);
 }
 
-// The upper levels of the trajectory tree in one workgroup per problem (see kt_vmid).
 template <class B>
-__global__ __launch_bounds__(64 * kMidWaves) void kt_tmid(const KProb kp, const MidArgs a) {
+__global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_troot(const KProb kp, const Stage st,
+                                                             const typename B::Mem* src,
+                                                             typename B::Mem* sib,
+                                                             typename B::Mem* __restrict__ x_out) {
+  constexpr int VR = kVR<B::N>;
+  __shared__ typename B::R ex[kGroup<B>][kDumpV<B>], xs[kGroup<B>][kDumpX<B>];
+  const Here<B> h(st, 0, blockIdx.y);
+  typename B::Mem* sb = sib + (long)h.p * st.n_slot * VR;
+  t_tserial<B>(h, st, src, ex);
+  t_tup<B>(h, ex, sb, true);
+  t_ttop<B>(kp, h, true, sb, xs);
+  t_tdown<B>(h, xs, sb);
+  t_tspread<B>(h, st, src, xs, x_out);
+}
+
+template <class B>
+__global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_tdown(
+    const KProb kp, const Stage st, const typename B::Mem* __restrict__ src,
+    const typename B::Mem* __restrict__ sib, const typename B::Mem* __restrict__ x_in,
+    typename B::Mem* __restrict__ x_out) {
+  __shared__ typename B::R xs[kGroup<B>][kDumpX<B>];
+  const Here<B> h(st, blockIdx.x, blockIdx.y);
+  t_ttop<B>(kp, h, st.n_grp == 1, x_in + ((long)h.p * st.n_grp + h.g) * B::N, xs);
+  t_tdown<B>(h, xs, sib + ((long)h.p * st.n_slot + h.g * kGroup<B>)*kVR<B::N>);
+  t_tspread<B>(h, st, src, xs, x_out);
+}
+
+// The bottom stage down: values of every block, and with grp the group's map (msib: its slots'
+// sibling maps).
+template <class B>
+__global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_vbottom(
+    const KProb kp, const Stage st, int run, const typename B::Mem* __restrict__ elts,
+    const typename B::Mem* __restrict__ sib, const typename B::Mem* __restrict__ val_in,
+    typename B::Mem* __restrict__ Sout, typename B::Mem* __restrict__ vout,
+    typename B::Mem* __restrict__ msib, typename B::Mem* __restrict__ grp,
+    typename B::Mem* __restrict__ bmaps) {
+  constexpr int VR = kVR<B::N>;
+  __shared__ typename B::R val[kGroup<B>][kDumpV<B>], scr_all[kGroupWaves<B>][kInvScr<B>];
+  const long g = run > 1 ? spread(blockIdx.x, run) : (long)blockIdx.x;
+  if (g >= st.n_grp) return;
+  const Here<B> h(st, g, blockIdx.y);
+  typename B::R* scr = scr_all[h.w];
+  t_vtop<B>(kp, h, st.n_grp == 1, val_in + ((long)h.p * st.n_grp + h.g) * kVR<B::N>, val);
+  t_vdown<B>(h, val, sib + ((long)h.p * st.n_slot + g * kGroup<B>)*kNE<B::N>, scr);
+  const Map<B> acc = t_vbottom<B>(kp, h, st.c, elts, val, Sout, vout, bmaps, grp != nullptr, scr);
+  if (!grp) return;
+  if (h.live) vdump<B>(acc.P, acc.q, val[h.loc]);
+  t_tup<B>(h, val, msib + ((long)h.p * st.n_slot + g * kGroup<B>)*VR, st.n_grp == 1);
+  if (h.w == 0) t_tgroup<B>(val, grp + ((long)h.p * st.n_grp + g) * VR);
+}
+
+// x_k and u_k = -R^{-1} L(t_k)^T (S_k x_k - v_k) of every block of a slot, from the block maps the
+// value sweep kept.
+template <class B>
+TDEV void t_tbottom(const KProb& kp, const Here<B>& h, int wc, const typename B::Mem* Sg,
+                    const typename B::Mem* vg, const typename B::R (*xs)[kDumpX<B>],
+                    typename B::Mem* xout, typename B::Mem* uout, const typename B::Mem* bmaps) {
   using R = typename B::R;
   using Mem = typename B::Mem;
-  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), p = blockIdx.y;
-  for (int l = a.l0; l < a.L; ++l) {
-    for (long g = w; g * B::NODES < a.n[l + 1]; g += kMidWaves)
-      t_treduce<B>(p, g * B::NODES + B::node(), a.wcs[l], (const Mem*)a.tup[l], a.n[l],
-                   (Mem*)a.tup[l + 1], a.n[l + 1]);
-    __syncthreads();
-  }
-  for (int l = a.L; l >= a.l0; --l) {
-    // the one node above the top level starts at x0
-    const Mem* xin = l == a.L ? (const Mem*)kp.x0 : (const Mem*)a.val[l + 1];
-    for (long g = w; g * B::NODES < a.n[l + 1]; g += kMidWaves)
-      t_tdown<B>(p, g * B::NODES + B::node(), a.wcs[l], (const Mem*)a.tup[l], a.n[l], xin,
-                 a.n[l + 1], (Mem*)a.val[l]);
-    __syncthreads();
-  }
-}
-
-// x_k and u_k = -R^{-1} L(t_k)^T (S_k x_k - v_k) of every block of a level-1 node, from the block
-// maps the value sweep kept.
-template <class B>
-__global__ __launch_bounds__(64) void kt_tbottom(const KProb kp, int wc,
-                                                 const typename B::Mem* __restrict__ Sg,
-                                                 const typename B::Mem* __restrict__ vg,
-                                                 const typename B::Mem* __restrict__ x1, long n1,
-                                                 typename B::Mem* __restrict__ xout,
-                                                 typename B::Mem* __restrict__ uout,
-                                                 const typename B::Mem* __restrict__ bmaps) {
-  using R = typename B::R;
-  using Mem = typename B::Mem;
   constexpr int N = B::N;
-  const int p = blockIdx.y, nu = kp.nu;
-  const long T = kp.T, i = (long)blockIdx.x * B::NODES + B::node();
-  const bool live = i < n1;
-  const long j0 = i * wc;
+  const int nu = kp.nu;
+  const long T = kp.T;
+  const int p = h.p;
+  const bool live = h.live;
+  const long j0 = h.i * wc;
   auto ok = [&](long k) { return live && k < T; };
   const Mem* Sp = Sg + (long)p * (T + 1) * N * N;
   const Mem* vp = vg + (long)p * (T + 1) * N;
@@ -554,7 +820,8 @@ __global__ __launch_bounds__(64) void kt_tbottom(const KProb kp, int wc,
         if (on && B::vrow(r) < nu) up[k * nu + B::vrow(r)] = (Mem)u.x[r];
     }
   };
-  Vec<B> x = vload<B>(live, x1 + ((long)p * n1 + i) * N, vec);
+  Vec<B> x;
+  get<B>(x.x, xs[live ? h.loc : 0] + B::sub());
 #pragma unroll 1
   for (int c = 0; c < wc; ++c) {
     const long k = j0 + c;
@@ -568,6 +835,49 @@ __global__ __launch_bounds__(64) void kt_tbottom(const KProb kp, int wc,
     vstore<B>(end, x, xp + T * N, vec);
     control(end, T, x);
   }
+}
+
+template <class B>
+__global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_tbottom(
+    const KProb kp, const Stage st, const typename B::Mem* __restrict__ Sg,
+    const typename B::Mem* __restrict__ vg, const typename B::Mem* __restrict__ msib,
+    const typename B::Mem* __restrict__ x_in, typename B::Mem* __restrict__ xout,
+    typename B::Mem* __restrict__ uout, const typename B::Mem* __restrict__ bmaps) {
+  __shared__ typename B::R xs[kGroup<B>][kDumpX<B>];
+  const Here<B> h(st, blockIdx.x, blockIdx.y);
+  t_ttop<B>(kp, h, st.n_grp == 1, x_in + ((long)h.p * st.n_grp + h.g) * B::N, xs);
+  t_tdown<B>(h, xs, msib + ((long)h.p * st.n_slot + h.g * kGroup<B>)*kVR<B::N>);
+  if (h.w * B::NODES < h.cnt) t_tbottom<B>(kp, h, st.c, Sg, vg, xs, xout, uout, bmaps);
+}
+
+// Both scans of a horizon of one group in one launch.
+template <class B>
+__global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_small(
+    const KProb kp, const Stage st, const typename B::Mem* __restrict__ elts, typename B::Mem* sib,
+    typename B::Mem* msib, typename B::Mem* Sout, typename B::Mem* vout,
+    typename B::Mem* __restrict__ xout, typename B::Mem* __restrict__ uout, typename B::Mem* bmaps) {
+  constexpr int NE = kNE<B::N>, VR = kVR<B::N>;
+  __shared__ typename B::R ex[kGroup<B>][kDumpT<B>], scr_all[kGroupWaves<B>][kInvScr<B>];
+  const Here<B> h(st, 0, blockIdx.y);
+  typename B::R* scr = scr_all[h.w];
+  typename B::Mem* sb = sib + (long)h.p * st.n_slot * NE;
+  typename B::Mem* mb = msib + (long)h.p * st.n_slot * VR;
+  const bool any = h.w * B::NODES < h.cnt;
+  if (any) {
+    const Tup<B> acc = t_serial<B>(h, st, true, elts, scr);
+    if (h.live) dump<B>(acc, ex[h.cnt - 1 - h.loc]);
+  }
+  t_vup<B>(h, ex, sb, true, scr);
+  auto val = (typename B::R(*)[kDumpV<B>])ex[0];
+  t_vtop<B>(kp, h, true, sb, val);
+  t_vdown<B>(h, val, sb, scr);
+  const Map<B> acc = t_vbottom<B>(kp, h, st.c, elts, val, Sout, vout, bmaps, true, scr);
+  if (h.live) vdump<B>(acc.P, acc.q, val[h.loc]);
+  t_tup<B>(h, val, mb, true);
+  auto xs = (typename B::R(*)[kDumpX<B>])ex[0];
+  t_ttop<B>(kp, h, true, mb, xs);
+  t_tdown<B>(h, xs, mb);
+  if (any) t_tbottom<B>(kp, h, st.c, Sout, vout, xs, xout, uout, bmaps);
 }
 
 }  // namespace tile
