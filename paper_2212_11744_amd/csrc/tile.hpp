@@ -106,6 +106,7 @@ struct Q64 {
   using R = double;
   using Mem = Mem_;
   static constexpr int N = N_, NT = (N + 3) / 4, MR = NT * NT, VR = NT, NODES = 4, LANES = 16;
+  static constexpr bool kFull = N % 4 == 0;  // no register holds an entry beyond N
   static_assert(N <= 8, "two tiles of 4 a side at most");
   static TDEV int node() { return (lane_id() >> 2) & 3; }
   static TDEV int sub() { return ((lane_id() >> 4) << 2) | (lane_id() & 3); }
@@ -193,6 +194,7 @@ struct W64 {
   using Mem = double;
   static constexpr int N = N_, NT = (N + 3) / 4, MR = NT, VR = 1, NODES = 1, LANES = 64;
   static_assert(N <= 16, "one 16 x 16 tile");
+  static constexpr bool kFull = N == 16;
   static TDEV int node() { return 0; }
   static TDEV int sub() { return lane_id(); }
   static TDEV int row(int r) { return 4 * r + (lane_id() >> 4); }
@@ -262,6 +264,7 @@ struct W32 {
   using Mem = float;
   static constexpr int N = N_, NT = 4, MR = 4, VR = 4, NODES = 1, LANES = 64;
   static_assert(N <= 16, "one 16 x 16 tile");
+  static constexpr bool kFull = N == 16;
   static TDEV int node() { return 0; }
   static TDEV int sub() { return lane_id(); }
   static TDEV int row(int r) { return 4 * (lane_id() >> 4) + r; }
@@ -501,6 +504,37 @@ TDEV void vstore(bool live, const Vec<B>& v, P* g, const F& at) {
   }
 }
 
+// The same in two halves, so that a load can stay in flight until its values are used: a mask or a
+// conversion right after a load waits for it.  fetch reads every entry (lanes beyond N entry
+// N - 1), so its address has to be valid for nodes that are not live, too.
+template <class B, class P, int CNT, class F>
+TDEV void fetch(P (&x)[CNT], const P* g, const F& at) {
+#pragma unroll
+  for (int r = 0; r < CNT; ++r) x[r] = g[at(min(B::row(r), B::N - 1), min(B::col(r), B::N - 1))];
+}
+template <class B, class P, int CNT, class F>
+TDEV void vfetch(P (&x)[CNT], const P* g, const F& at) {
+#pragma unroll
+  for (int r = 0; r < CNT; ++r) x[r] = g[at(min(B::vrow(r), B::N - 1))];
+}
+template <class B, class P>
+TDEV Mat<B> settle(const P (&x)[B::MR], bool on) {
+  Mat<B> m;
+#pragma unroll
+  for (int r = 0; r < B::MR; ++r)
+    m.x[r] = on && (B::kFull || (B::row(r) < B::N && B::col(r) < B::N)) ? (typename B::R)x[r]
+                                                                             : 0;
+  return m;
+}
+template <class B, class P>
+TDEV Vec<B> vsettle(const P (&x)[B::VR], bool on) {
+  Vec<B> v;
+#pragma unroll
+  for (int r = 0; r < B::VR; ++r)
+    v.x[r] = on && (B::kFull || B::vrow(r) < B::N) ? (typename B::R)x[r] : 0;
+  return v;
+}
+
 template <int N>
 TDEV int pk(int i, int j) {  // packed upper index
   const int a = i < j ? i : j, b = i < j ? j : i;
@@ -620,20 +654,28 @@ struct Ref {
   long st;
 };
 
-template <class B, bool TRANS, class P>
-TDEV Tup<B> tload(bool live, Ref<P> f) {
+template <class B>
+struct RawTup {
+  typename B::Mem A[B::MR], C[B::MR], J[B::MR], b[B::VR], e[B::VR];
+};
+template <class B, bool TRANS>
+TDEV RawTup<B> tfetch(Ref<const typename B::Mem> f) {
   constexpr int N = B::N, NS = N * (N + 1) / 2, oB = N * N, oC = oB + N, oE = oC + NS, oJ = oE + N;
   const long st = f.st;
-  Tup<B> t;
-  t.A = mload<B>(live, f.g, [=](int i, int j) { return (TRANS ? j * N + i : i * N + j) * st; });
-  t.C = mload<B>(live, f.g, [=](int i, int j) { return (oC + pk<N>(i, j)) * st; });
-  t.J = mload<B>(live, f.g, [=](int i, int j) { return (oJ + pk<N>(i, j)) * st; });
-  t.b = vload<B>(live, f.g, [=](int i) { return (oB + i) * st; });
-  t.e = vload<B>(live, f.g, [=](int i) { return (oE + i) * st; });
+  RawTup<B> t;
+  fetch<B>(t.A, f.g, [=](int i, int j) { return (TRANS ? j * N + i : i * N + j) * st; });
+  fetch<B>(t.C, f.g, [=](int i, int j) { return (oC + pk<N>(i, j)) * st; });
+  fetch<B>(t.J, f.g, [=](int i, int j) { return (oJ + pk<N>(i, j)) * st; });
+  vfetch<B>(t.b, f.g, [=](int i) { return (oB + i) * st; });
+  vfetch<B>(t.e, f.g, [=](int i) { return (oE + i) * st; });
   return t;
 }
+template <class B>
+TDEV Tup<B> tsettle(const RawTup<B>& t, bool on) {
+  return {settle<B>(t.A, on), settle<B>(t.C, on), settle<B>(t.J, on), vsettle<B>(t.b, on),
+          vsettle<B>(t.e, on)};
+}
 
-// Stores a tuple whose A is held transposed.
 template <class B, class P>
 TDEV void tstore_t(bool live, const Tup<B>& t, Ref<P> f) {
   constexpr int N = B::N, NS = N * (N + 1) / 2, oB = N * N, oC = oB + N, oE = oC + NS, oJ = oE + N;

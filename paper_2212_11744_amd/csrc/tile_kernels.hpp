@@ -339,20 +339,22 @@ template <class B>
 TDEV Tup<B> t_serial(const Here<B>& h, const Stage& st, bool src_elts, const typename B::Mem* src,
                      typename B::R* scr) {
   using Mem = typename B::Mem;
-  auto ref = [&](long j) -> Ref<const Mem> {
+  const int c = st.c;
+  const long j0 = h.i * c;
+  auto ok = [&](int q) { return h.live && j0 + q < st.n_src; };
+  auto ref = [&](int q) -> Ref<const Mem> {
+    const long j = min(j0 + q, st.n_src - 1);
     if (src_elts) return elt_ref<const Mem, B::N>(src, h.p, j, st.n_src);
     return rec(src, kNE<B::N>, (long)h.p * st.n_src + j);
   };
-  const int c = st.c;
-  const long j0 = h.i * c;
-  auto ok = [&](long j) { return h.live && j < st.n_src; };
-  Tup<B> acc = tload<B, true>(ok(j0 + c - 1), ref(j0 + c - 1));
-  if (c == 1) return acc;
-  Tup<B> nxt = tload<B, false>(ok(j0 + c - 2), ref(j0 + c - 2));
+  const RawTup<B> last = tfetch<B, true>(ref(c - 1));
+  RawTup<B> nxt;
+  if (c > 1) nxt = tfetch<B, false>(ref(c - 2));
+  Tup<B> acc = tsettle<B>(last, ok(c - 1));
 #pragma unroll 1
   for (int q = c - 2; q >= 0; --q) {
-    const Tup<B> x = nxt;
-    if (q > 0) nxt = tload<B, false>(ok(j0 + q - 1), ref(j0 + q - 1));
+    const Tup<B> x = tsettle<B>(nxt, ok(q));
+    if (q > 0) nxt = tfetch<B, false>(ref(q - 1));
     acc = combine<B>(x, acc, scr);
   }
   return acc;
@@ -401,13 +403,13 @@ TDEV void t_vdown(const Here<B>& h, typename B::R (*val)[kDumpV<B>], const typen
   while (2 * s < h.cnt) s *= 2;
   auto load = [&](int s_) {
     const Pair<B> q(h, s_);
-    return tload<B, false>(q.on, rec(sib, kNE<B::N>, q.r + s_));
+    return tfetch<B, false>(rec(sib, kNE<B::N>, q.r + s_));
   };
   if (h.cnt > 1) {
-    Tup<B> nxt = load(s);
+    RawTup<B> nxt = load(s);
 #pragma unroll 1
     for (; s >= 1; s /= 2) {
-      const Tup<B> a = nxt;
+      const Tup<B> a = tsettle<B>(nxt, true);
       if (s > 1) nxt = load(s / 2);
       lds_sync();
       const Pair<B> q(h, s);
@@ -459,9 +461,10 @@ TDEV void t_vspread(const Here<B>& h, const Stage& st, const typename B::Mem* sr
   const long j0 = h.i * c;
   auto ok = [&](long j) { return h.live && j < st.n_src; };
   auto ref = [&](long j) -> Ref<const Mem> {
-    return rec(src, kNE<B::N>, (long)h.p * st.n_src + j);
+    return rec(src, kNE<B::N>, (long)h.p * st.n_src + min(j, st.n_src - 1));
   };
-  Tup<B> nxt = tload<B, false>(c > 1 && ok(j0 + c - 1), ref(j0 + c - 1));
+  RawTup<B> nxt;
+  if (c > 1) nxt = tfetch<B, false>(ref(j0 + c - 1));
   Mat<B> S;
   Vec<B> v;
   vundump<B>(S, v, val[h.live ? h.cnt - 1 - h.loc : 0]);
@@ -470,8 +473,8 @@ TDEV void t_vspread(const Here<B>& h, const Stage& st, const typename B::Mem* sr
     const long j = j0 + q;
     vrec_store<B>(ok(j), S, v, val_out + ((long)h.p * st.n_src + j) * kVR<B::N>);
     if (q == 0) break;
-    const Tup<B> a = nxt;
-    if (q > 1) nxt = tload<B, false>(ok(j - 1), ref(j - 1));
+    const Tup<B> a = tsettle<B>(nxt, ok(j));
+    if (q > 1) nxt = tfetch<B, false>(ref(j - 1));
     fold<B>(a, S, v, scr);
   }
 }
@@ -537,11 +540,21 @@ __global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_vdown(
 // Trajectory (Method 1, Sec. IV-E): maps composed up a tree, states carried down.  Here the places
 // of a group are its slots in time order.
 // ------------------------------------------------------------------------------------------
-template <class B, bool TRANS, class P>
-TDEV Map<B> map_load(bool live, const P* g) {
+template <class B>
+struct RawMap {
+  typename B::Mem P[B::MR], q[B::VR];
+};
+template <class B, bool TRANS>
+TDEV RawMap<B> map_fetch(const typename B::Mem* g) {
   constexpr int N = B::N;
-  return {mload<B>(live, g, [](int i, int j) { return TRANS ? j * N + i : i * N + j; }),
-          vload<B>(live, g + N * N, [](int i) { return i; })};
+  RawMap<B> m;
+  fetch<B>(m.P, g, [](int i, int j) { return TRANS ? j * N + i : i * N + j; });
+  vfetch<B>(m.q, g + N * N, [](int i) { return i; });
+  return m;
+}
+template <class B>
+TDEV Map<B> map_settle(const RawMap<B>& m, bool on) {
+  return {settle<B>(m.P, on), vsettle<B>(m.q, on)};
 }
 template <class B, class P>  // m.P transposed
 TDEV void map_store_t(bool live, const Map<B>& m, P* g) {
@@ -564,7 +577,7 @@ TDEV Map<B> t_vbottom(const KProb& kp, const Here<B>& h, int wc, const typename 
   const bool live = h.live;
   const long j0 = h.i * wc;
   auto ok = [&](long k) { return live && k < T; };
-  auto ref = [&](long k) -> Ref<const Mem> { return elt_ref<const Mem, N>(elts, p, k, T); };
+  auto ref = [&](long k) -> Ref<const Mem> { return elt_ref<const Mem, N>(elts, p, min(k, T - 1), T); };
   Mem* Sp = Sout + (long)p * (T + 1) * N * N;
   Mem* vp = vout + (long)p * (T + 1) * N;
   auto put = [&](bool on, long k, const Mat<B>& S, const Vec<B>& v) {
@@ -578,13 +591,13 @@ TDEV Map<B> t_vbottom(const KProb& kp, const Here<B>& h, int wc, const typename 
   if (compose) lds_sync();  // the maps take the place of the values
   Map<B> acc{mzero<B>(), vzero<B>()};  // P transposed
   if (h.w * B::NODES >= h.cnt) return acc;
-  Tup<B> nxt = tload<B, false>(ok(j0 + wc - 1), ref(j0 + wc - 1));
+  RawTup<B> nxt = tfetch<B, false>(ref(j0 + wc - 1));
   if (!kp.seg) put(live && j0 + wc >= T, T, S, v);
 #pragma unroll 1
   for (int c = wc - 1; c >= 0; --c) {
     const long k = j0 + c;
-    const Tup<B> a = nxt;
-    if (c > 0) nxt = tload<B, false>(ok(k - 1), ref(k - 1));
+    const Tup<B> a = tsettle<B>(nxt, ok(k));
+    if (c > 0) nxt = tfetch<B, false>(ref(k - 1));
     const Map<B> m = fold<B>(a, S, v, scr);
     put(ok(k), k, S, v);
     if (bmaps) {
@@ -634,13 +647,13 @@ TDEV void t_tdown(const Here<B>& h, typename B::R (*xs)[kDumpX<B>], const typena
   while (2 * s < h.cnt) s *= 2;
   auto load = [&](int s_) {
     const Pair<B> q(h, s_);
-    return map_load<B, true>(q.on, sib + (long)(q.r + s_) * kVR<B::N>);
+    return map_fetch<B, true>(sib + (long)(q.r + s_) * kVR<B::N>);
   };
   if (h.cnt > 1) {
-    Map<B> nxt = load(s);
+    RawMap<B> nxt = load(s);
 #pragma unroll 1
     for (; s >= 1; s /= 2) {
-      const Map<B> m = nxt;
+      const Map<B> m = map_settle<B>(nxt, true);
       if (s > 1) nxt = load(s / 2);
       lds_sync();
       const Pair<B> q(h, s);
@@ -671,11 +684,20 @@ TDEV void t_tserial(const Here<B>& h, const Stage& st, const typename B::Mem* sr
                     typename B::R (*ex)[kDumpV<B>]) {
   const int c = st.c;
   const long j0 = h.i * c;
-  auto at = [&](long j) { return src + ((long)h.p * st.n_src + j) * kVR<B::N>; };
-  auto ok = [&](long j) { return h.live && j < st.n_src; };
-  Map<B> acc = map_load<B, true>(ok(j0 + c - 1), at(j0 + c - 1));
+  auto at = [&](int q) {
+    return src + ((long)h.p * st.n_src + min(j0 + q, st.n_src - 1)) * kVR<B::N>;
+  };
+  auto ok = [&](int q) { return h.live && j0 + q < st.n_src; };
+  const RawMap<B> last = map_fetch<B, true>(at(c - 1));
+  RawMap<B> nxt;
+  if (c > 1) nxt = map_fetch<B, false>(at(c - 2));
+  Map<B> acc = map_settle<B>(last, ok(c - 1));
 #pragma unroll 1
-  for (int q = c - 2; q >= 0; --q) map_after<B>(acc, map_load<B, false>(ok(j0 + q), at(j0 + q)));
+  for (int q = c - 2; q >= 0; --q) {
+    const Map<B> m = map_settle<B>(nxt, ok(q));
+    if (q > 0) nxt = map_fetch<B, false>(at(q - 1));
+    map_after<B>(acc, m);
+  }
   if (h.live) vdump<B>(acc.P, acc.q, ex[h.loc]);
 }
 
@@ -686,15 +708,21 @@ TDEV void t_tspread(const Here<B>& h, const Stage& st, const typename B::Mem* sr
   constexpr int N = B::N;
   const int c = st.c;
   const long j0 = h.i * c;
-  auto ok = [&](long j) { return h.live && j < st.n_src; };
-  auto vec = [](int i) { return i; };
+  auto at = [&](int q) {
+    return src + ((long)h.p * st.n_src + min(j0 + q, st.n_src - 1)) * kVR<N>;
+  };
   Vec<B> x;
   get<B>(x.x, xs[h.live ? h.loc : 0] + B::sub());
+  RawMap<B> nxt;
+  if (c > 1) nxt = map_fetch<B, true>(at(0));
 #pragma unroll 1
   for (int q = 0; q < c; ++q) {
-    const long j = (long)h.p * st.n_src + j0 + q;
-    vstore<B>(ok(j0 + q), x, x_out + j * N, vec);
-    if (q + 1 < c) x = map_apply<B>(map_load<B, true>(ok(j0 + q), src + j * kVR<N>), x);
+    const bool on = h.live && j0 + q < st.n_src;
+    vstore<B>(on, x, x_out + ((long)h.p * st.n_src + j0 + q) * N, [](int i) { return i; });
+    if (q + 1 == c) break;
+    const Map<B> m = map_settle<B>(nxt, on);
+    if (q + 2 < c) nxt = map_fetch<B, true>(at(q + 1));
+    x = map_apply<B>(m, x);
   }
 }
 
@@ -808,11 +836,24 @@ TDEV void t_tbottom(const KProb& kp, const Here<B>& h, int wc, const typename B:
   const bool per_k = kp.L_sampled || kp.seg;
   Mat<B> Kc = mzero<B>();
   if (up && !per_k) Kc = gain(live, 0);
-  auto control = [&](bool on, long k, const Vec<B>& x) {
-    if (!up) return;
+  // S, v and the map of a block, loaded a block ahead
+  struct Raw {
+    typename B::Mem S[B::MR], v[B::VR];
+    RawMap<B> m;
+  };
+  auto load = [&](long k_) {
+    const long k = min(k_, T - 1);
+    Raw w;
+    if (up) {
+      fetch<B>(w.S, Sp + k * N * N, full);
+      vfetch<B>(w.v, vp + k * N, vec);
+    }
+    w.m = map_fetch<B, true>(bmaps + ((long)p * T + k) * kVR<N>);
+    return w;
+  };
+  auto control = [&](bool on, long k, const Mat<B>& S, const Vec<B>& v, const Vec<B>& x) {
     if (per_k) Kc = gain(on, k);
-    const Mat<B> S = mload<B>(on, Sp + k * N * N, full);
-    const Vec<B> gv = mv<B>(neg<B>(vload<B>(on, vp + k * N, vec)), S, x);
+    const Vec<B> gv = mv<B>(neg<B>(v), S, x);
     const Vec<B> u = neg<B>(mv0<B>(Kc, gv));
     if (B::rep()) {
 #pragma unroll
@@ -822,18 +863,21 @@ TDEV void t_tbottom(const KProb& kp, const Here<B>& h, int wc, const typename B:
   };
   Vec<B> x;
   get<B>(x.x, xs[live ? h.loc : 0] + B::sub());
+  Raw nxt = load(j0);
 #pragma unroll 1
   for (int c = 0; c < wc; ++c) {
     const long k = j0 + c;
-    const Map<B> m = map_load<B, true>(ok(k), bmaps + ((long)p * T + k) * kVR<N>);
+    const Raw w = nxt;
+    if (c + 1 < wc) nxt = load(k + 1);
     vstore<B>(ok(k), x, xp + k * N, vec);
-    control(ok(k), k, x);
-    x = map_apply<B>(m, x);
+    if (up) control(ok(k), k, settle<B>(w.S, ok(k)), vsettle<B>(w.v, ok(k)), x);
+    x = map_apply<B>(map_settle<B>(w.m, ok(k)), x);
   }
   if (!kp.seg) {
     const bool end = live && j0 + wc >= T;
     vstore<B>(end, x, xp + T * N, vec);
-    control(end, T, x);
+    if (up)
+      control(end, T, mload<B>(end, Sp + T * N * N, full), vload<B>(end, vp + T * N, vec), x);
   }
 }
 
