@@ -1,5 +1,6 @@
 // Host side of the C ABI declared in include/lqt.h: argument validation, workspace planning,
 // dispatch to the kernel instantiation of (nx, nu, dtype) and the launch sequence of every stage.
+#include <algorithm>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -269,6 +270,23 @@ bool use_tile_scans(const lqt_dims* d) {
          tile_tree(d).m * d->batch <= kTileGroups;
 }
 
+// The value scan of the per-lane path in three launches (k_vred, the tree over its tiles, k_vswp)
+// instead of a single pass.  Measured in a solve or alone (us): nx = 4 FP64
+// scan 84 vs 101 at T = 150000, 189 vs 233 at 600000; nx = 4 FP32 solve 62 vs 62 at 600, 58 vs 71 at
+// 4000, 282 vs 344 at 600000; nx = 3 solve 45.8 vs 49.2 at 2000, 67 vs 71 at 20000, 79.3 vs 79.3 at
+// 40000 and slower beyond; nx = 1, 2, whose combinations are short: 46 vs 42 at nx = 2 and T = 17000.
+// Blocks per lane: the single pass's, of all problems, but at least 2 (a wave's scan over its lanes is
+// six combinations, so fewer blocks a lane only add waves of them: T = 100000 29 + 17 us with 4, 32 +
+// 22 with 2).
+int split_chunk(long T, long batch) {
+  return std::max(2, scan_chunk(T * batch, kScanMaxVChunk));
+}
+GTree split_tree(int nx, long T, long batch) { return node_tree(nx, T, 64 * split_chunk(T, batch)); }
+bool use_split_scan(const lqt_dims* d) {
+  if (use_wave(d) || d->nx < 3) return false;
+  return d->nx == 4 ? d->T > 512 : d->T > 512 && d->T <= 1L << 15;
+}
+
 }  // namespace
 
 // Byte layout of the workspace of one call.  Returns the total; fills w when base != nullptr.
@@ -310,6 +328,28 @@ size_t layout(const lqt_dims* d, lqt_call call, char* base, Work* w, int wc, lon
   const bool want_v = call == LQT_CALL_SCAN_VALUE || call == LQT_CALL_SOLVE ||
                       call == LQT_CALL_TRAJ_METHOD2;
   const bool want_t = call == LQT_CALL_FORWARD_TRAJ || call == LQT_CALL_SOLVE;
+  // arrays of a tree in stages (launch_value in tile_host.hpp): 1 the bottom stage's slots, 2 the
+  // nodes the upper stages start from, then the slots and groups of each
+  auto slots = [&](int l, long n, bool val, bool traj) {
+    void* a = val ? take(es * B * ne_of(d->nx) * n) : nullptr;
+    void* b = traj ? take(es * B * nm_of(d->nx) * n) : nullptr;
+    if (w) w->vtup[l] = a, w->tmap[l] = b;
+  };
+  auto nodes = [&](int l, long n, bool val, bool traj) {
+    slots(l, n, val, traj);
+    void* a = val ? take(es * B * nm_of(d->nx) * n) : nullptr;
+    void* b = traj ? take(es * B * d->nx * n) : nullptr;
+    if (w) w->vval[l] = a, w->tx[l] = b;
+  };
+  auto upper_stages = [&](const GTree& t, bool val, bool traj) {
+    nodes(2, t.m, val, traj);
+    for (int j = 0; j < t.up; ++j) {
+      // the last stage of a tree from fewer nodes may have more slots, up to a group
+      const bool root = j + 1 == t.up;
+      slots(3 + 2 * j, root ? std::min((long)t.G, t.src[j]) : t.slot[j], val, traj);
+      if (!root) nodes(4 + 2 * j, t.grp[j], val, traj);
+    }
+  };
   const bool tile = use_tile_scans(d) && (call == LQT_CALL_SCAN_VALUE ||
                                           (call == LQT_CALL_SOLVE && keep_maps));
   if (use_wave(d) && call == LQT_CALL_TRAJ_METHOD2) {
@@ -327,34 +367,15 @@ size_t layout(const lqt_dims* d, lqt_call call, char* base, Work* w, int wc, lon
     return off;
   }
   if (use_wave(d) || tile) {
-    // array 1: the bottom stage's slots, then the nodes the upper stages start from and the
-    // slots and groups of each (launch_value in tile_host.hpp)
     const GTree t = !use_wave(d)                       ? tile_tree(d)
                     : call == LQT_CALL_FORWARD_TRAJ ? node_tree(d->nx, d->T, wc)
                                                     : group_tree(d->nx, d->T, wc);
-    auto slots = [&](int l, long n) {
-      void* a = want_v ? take(es * B * ne_of(d->nx) * n) : nullptr;
-      void* b = want_t ? take(es * B * nm_of(d->nx) * n) : nullptr;
-      if (w) w->vtup[l] = a, w->tmap[l] = b;
-    };
-    auto nodes = [&](int l, long n) {
-      slots(l, n);
-      void* a = want_v ? take(es * B * nm_of(d->nx) * n) : nullptr;
-      void* b = want_t ? take(es * B * d->nx * n) : nullptr;
-      if (w) w->vval[l] = a, w->tx[l] = b;
-    };
-    if (want_v) slots(1, t.n1);
+    if (want_v) slots(1, t.n1, want_v, want_t);
     if (call == LQT_CALL_SOLVE && !keep_maps) {
       void* a = take(es * B * d->nx * t.n1);
       if (w) w->tx[1] = a;
     }
-    nodes(2, t.m);
-    for (int j = 0; j < t.up; ++j) {
-      // the last stage of a tree from fewer nodes may have more slots, up to a group
-      const bool root = j + 1 == t.up;
-      slots(3 + 2 * j, root ? std::min((long)t.G, t.src[j]) : t.slot[j]);
-      if (!root) nodes(4 + 2 * j, t.grp[j]);
-    }
+    upper_stages(t, want_v, want_t);
     if (call == LQT_CALL_SOLVE && ws_elts && use_wave(d)) {
       void* e = take(es * B * ne_of(d->nx) * (size_t)padt(d->T));
       if (w) w->elts = e;
@@ -395,6 +416,13 @@ size_t layout(const lqt_dims* d, lqt_call call, char* base, Work* w, int wc, lon
   if (call == LQT_CALL_SCAN_VALUE || call == LQT_CALL_SOLVE)
     take_lb(w ? &w->lbv : nullptr, 64, ne_of(d->nx), nv_of(d->nx));
   if (want_t) take_lb(w ? &w->lbt : nullptr, 64, nm_of(d->nx), d->nx);
+  if (!tile && use_split_scan(d) &&
+      (call == LQT_CALL_SCAN_VALUE || (call == LQT_CALL_SOLVE && keep_maps && nconsts == d->batch))) {
+    const GTree vt = split_tree(d->nx, d->T, d->batch);
+    void* a = take(es * B * ne_of(d->nx) * 64 * vt.m);
+    if (w) w->vpart[1] = a;
+    upper_stages(vt, true, false);
+  }
   // Method 2: the tree of node products and prefix states
   if (call == LQT_CALL_TRAJ_METHOD2) {
     for (int l = 1; l <= t.levels; ++l) {
@@ -709,9 +737,16 @@ LbRecs lb_for(const LbRecs& r, long T, int chunk) {
 
 // Value scan over elements (single pass; per-lane path).
 // cleared: the records' status words were already cleared (the solve clears both scans' at once).
-lqt_status run_value(const Ops* o, const KProb& kp, const Work& w, const void* elts, void* S,
+lqt_status run_value(const Ops* o, const KProb& kp, int dtype, const Work& w, const void* elts, void* S,
                      void* v, hipStream_t s, bool cleared = false) {
-  const int c = scan_chunk(kp.T, kScanMaxVChunk);
+  int c = scan_chunk(kp.T, kScanMaxVChunk);
+  if (w.vpart[1]) {
+    c = split_chunk(kp.T, kp.batch);
+    LQT_HIP(o->vred(kp, elts, w.vpart[1], w.vtup[2], c, s));
+    LQT_HIP(tile_nodes(kp, dtype, split_tree(kp.nx, kp.T, kp.batch), w, s));
+    LQT_HIP(o->vswp(kp, elts, w.vpart[1], w.vval[2], S, v, c, s));
+    return LQT_OK;
+  }
   if (!cleared) LQT_HIP(lb_clear(w.lbv, s));
   LQT_HIP(o->vscan(kp, elts, S, v, lb_for(w.lbv, kp.T, c), c, s));
   return LQT_OK;
@@ -898,7 +933,7 @@ lqt_status lqt_scan_value(const lqt_dims* dims, const void* elts, const void* Qf
     if (use_tile_scans(dims))
       LQT_HIP(tile_value(kp, tile_tree(dims), w, elts, S, v, stream));
     else
-      LQT_TRY(run_value(o, kp, w, elts, S, v, stream));
+      LQT_TRY(run_value(o, kp, dims->dtype, w, elts, S, v, stream));
   }
   const long nb = dims->batch, T1 = (long)dims->T + 1, nx = dims->nx;
   LQT_TRY(finite_check(dims, w, stream, {{S, nb * T1 * nx * nx, false}, {v, nb * T1 * nx, false}}));
@@ -959,13 +994,15 @@ lqt_status run_solve(const lqt_dims* dims, const KProb& kp, const Work& w, void*
   // the constants, and both scans' status words cleared in the same launch
   LQT_HIP(op->prep_clear(kprep, w.consts, w.lbv, w.lbt, stream));
   const bool lti = kp.lti && !kp.seg && w.lti;
+  KProb kb = kp;
+  kb.rev = w.vpart[1] != nullptr;
   if (lti) {
     LQT_HIP(op->lti_prep(kp, w.lti, stream));
-    LQT_HIP(op->lti_build(kp, w.lti, e, stream));
+    LQT_HIP(op->lti_build(kb, w.lti, e, stream));
   } else if (use_tile_build(dims)) {
     LQT_HIP(tile_build(kp, dims->dtype, e, stream));
   } else {
-    LQT_HIP(op->build(kp, e, stream));
+    LQT_HIP(op->build(kb, e, stream));
   }
   if (use_tile_scans(dims) && w.bmap && !kp.seg) {
     LQT_HIP(tile_scans(kp, tile_tree(dims), w, e, S, v, x, u, stream));
@@ -978,7 +1015,7 @@ lqt_status run_solve(const lqt_dims* dims, const KProb& kp, const Work& w, void*
                              lb_for(w.lbt, kp.T, queue_tchunk(cv)), cv, stream));
     return LQT_OK;
   }
-  LQT_TRY(run_value(op, kp, w, e, S, v, stream, true));
+  LQT_TRY(run_value(op, kp, dims->dtype, w, e, S, v, stream, true));
   LQT_TRY(run_traj(op, kp, w, e, S, v, x, u, stream, true));
   return LQT_OK;
 }

@@ -31,6 +31,7 @@ struct KProb {
   int nseg = 0;
   // Time-invariant path (lqt_dims.lti): per-problem shared element parts and response tables.
   int lti = 0;
+  int rev = 0;  // element build: the end of the horizon first
 };
 
 // Per-problem table of the time-invariant path (values of the call dtype): A - I [nx*nx],
@@ -201,6 +202,10 @@ struct Ops {
                            hipStream_t);
   hipError_t (*scan_queue)(const KProb&, const void* elts, void* S, void* v, void* x, void* u,
                              const LbRecs& lbv, const LbRecs& lbt, int cv, hipStream_t);
+  // the value scan in three launches: tile products and lane partials, (tile_nodes), sweep
+  hipError_t (*vred)(const KProb&, const void* elts, void* part, void* tiles, int chunk, hipStream_t);
+  hipError_t (*vswp)(const KProb&, const void* elts, const void* part, const void* vals, void* S,
+                     void* v, int chunk, hipStream_t);
 };
 
 // Adjoint kernels (lqt_adjoint.hip) of one (nx, nu, dtype) instantiation.
@@ -324,8 +329,10 @@ hipError_t wave_scans(const KProb& kp, int dtype, const GTree& t, const Work& w,
                       void* S, void* v, void* x, void* u, hipStream_t s);
 
 // Short horizons of the small sizes on the kernels of tile_kernels.hpp (lqt_tile.hip): the element
-// build at nx = 3, 4, and in FP64 at nx = 4 the value scan alone and both scans (block maps in w.bmap).
+// build at nx = 3, 4, and in FP64 at nx = 4 the value scan alone and both scans (block maps in w.bmap);
+// and for every nx <= 4 the value tree over given nodes (w.vtup[2] -> w.vval[2]).
 hipError_t tile_build(const KProb& kp, int dtype, void* elts, hipStream_t s);
+hipError_t tile_nodes(const KProb& kp, int dtype, const GTree& t, const Work& w, hipStream_t s);
 hipError_t tile_value(const KProb& kp, const GTree& t, const Work& w, const void* elts, void* S,
                       void* v, hipStream_t s);
 hipError_t tile_scans(const KProb& kp, const GTree& t, const Work& w, const void* elts, void* S,

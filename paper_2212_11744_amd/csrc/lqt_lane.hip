@@ -51,14 +51,17 @@ __device__ inline long gid() { return (long)blockIdx.x * blockDim.x + threadIdx.
 // 512 t + 8 l + r (lane l), which share row r of the tile, so each store of one value is a whole
 // 512-byte row instead of eight 64-byte segments.  (Placing the 8 rows of a tile on one XCD, with
 // wave w taking tile 8 (w / 64) + w % 8, measured no faster at 2^20 blocks: 0.300 ms both.)
-__device__ inline long tile_row_item() {
-  const long g = gid();
+__device__ inline long tile_row_item(long g) {
   return (g & ~511L) | ((g & 63) << 3) | ((g >> 6) & 7);
 }
 // Short horizons keep consecutive items per wave (neighbouring blocks share reference samples, and
 // a few waves are latency-bound): rows per wave from 8 tiles on.
 constexpr long kTileRowMin = 8L * kTile;
-__device__ inline long build_item(long n) { return n >= kTileRowMin ? tile_row_item() : gid(); }
+// rev: the last workgroups' items first.
+__device__ inline long build_item(long n, int rev = 0) {
+  const long b = rev ? gridDim.x - 1 - blockIdx.x : blockIdx.x, g = b * blockDim.x + threadIdx.x;
+  return n >= kTileRowMin ? tile_row_item(g) : g;
+}
 
 // ------------------------------------------------------------------------------------------
 // Element build (Theorem 8):
@@ -774,14 +777,15 @@ __global__ __launch_bounds__(kThreads) void k_build_lti(const KProb kp, const R*
   constexpr int kPer = (kStage + kThreads - 1) / kThreads;
   __shared__ R rs[kPer * kThreads];
   const int p = blockIdx.y;
-  const long k = gid();
+  const long bx = kp.rev ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
+  const long k = bx * kThreads + threadIdx.x;
   const int n = kp.n;
   const long T = kp.T;
   const R* tp = tab + (long)p * lti_count(N, n);
   const R* rbase = (const R*)kp.r + (long)p * (2L * n * T + 1) * N;
   Tup<N, R> out;
   if (n <= kLtiMaxStageSteps) {
-    const long k0 = (long)blockIdx.x * kThreads;
+    const long k0 = bx * kThreads;
     const long k1 = min(k0 + kThreads, T);
     const long cnt = (2L * n * (k1 - k0) + 1) * N;
     const R* src = rbase + 2L * n * k0 * N;
@@ -857,7 +861,7 @@ LQT_DEV void element_at(const KProb& kp, int p, long k, Tup<N, R>& out) {
 template <int N, int NU, class R, bool CONST_COEF>
 __global__ __launch_bounds__(kThreads) void k_build(const KProb kp, R* __restrict__ elts) {
   const int p = blockIdx.y;
-  const long k = build_item(kp.T);
+  const long k = build_item(kp.T, kp.rev);
   if (k >= kp.T) return;
   Tup<N, R> out;
   element_at<N, NU, R, CONST_COEF>(kp, p, k, out);
@@ -1300,6 +1304,12 @@ struct TrajAlg {
   }
 };
 
+// Waves per SIMD the registers of the single-pass scans are held to: two in FP32, where that costs
+// nx = 4 a few dozen spilled values (T = 2^20: value scan 187 -> 170 us, trajectory scan 146 ->
+// 131); in FP64 it would cost hundreds (302 -> 990 us).
+template <class R>
+constexpr int kScanWaves = sizeof(R) == 4 ? 2 : 1;
+
 // ------------------------------------------------------------------------------------------
 // Single-pass scans (lookback.hpp).  One wave per tile of 64 c blocks (c consecutive blocks per
 // lane: c = 8 covers one tile of the element layout with full 512-byte rows, c = 4 half a tile
@@ -1307,6 +1317,46 @@ struct TrajAlg {
 // tile's free end from the records of the tiles before it in the flow, carries that state to
 // every lane through the lane's exclusive product, and sweeps the lane's blocks.
 // ------------------------------------------------------------------------------------------
+// The sweep of a lane over its blocks [j0, j1), from the value st at the right end of the last.
+template <int N, class R, int CH>
+LQT_DEV void value_sweep(const KProb& kp, int p, const R* __restrict__ ep, long j0, long j1, int lane,
+                         typename ValAlg<N, R>::State& st, R* __restrict__ Sout,
+                         R* __restrict__ vout, R (&sE)[Lay<N>::NE][kThreads]) {
+  const long T = kp.T;
+  R* Sp = Sout + (long)p * (T + 1) * N * N;
+  R* vp = vout + (long)p * (T + 1) * N;
+  if (j1 == T && !kp.seg) {
+    S_store_full<N, R>(st.S, Sp + T * N * N);
+#pragma unroll
+    for (int q = 0; q < N; ++q) vp[T * N + q] = st.v[q];
+  }
+  // The lane's v rows share cache lines (S rows are a line each): where the lane's LDS column
+  // (free once E is back in registers) holds them, they are written together after the sweep,
+  // so that no line leaves the L2 half written.
+  constexpr bool kStageV = CH * N <= Lay<N>::NE;
+  Tup<N, R> nxt;
+  tup_load(nxt, ep, j1 - 1);
+  for (long k = j1 - 1; k >= j0; --k) {
+    Tup<N, R> a = nxt;
+    if (k - 1 >= j0) tup_load(nxt, ep, k - 1);
+    Aff<N, R> m;
+    fold(a, st.S, st.v, m);
+    S_store_full<N, R>(st.S, Sp + k * N * N);
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+      if (kStageV)
+        sE[(k - j0) * N + q][lane] = st.v[q];
+      else
+        vp[k * N + q] = st.v[q];
+    }
+  }
+  if (kStageV) {
+    for (long k = j0; k < j1; ++k)
+#pragma unroll
+      for (int q = 0; q < N; ++q) vp[k * N + q] = sE[(k - j0) * N + q][lane];
+  }
+}
+
 // Value scan (Theorem 6, Lemma 7, terminal element of Sec. IV-D).  The flow is backward in time:
 // place i takes tile G - 1 - i, so the first place holds the end of the horizon.  Tiles are 512
 // blocks, 8 per lane (one tile of the element layout): with four waves per CU at most (a lane
@@ -1344,47 +1394,69 @@ LQT_DEV void vscan_tile(const KProb& kp, int p, long i, const R* __restrict__ el
     if (lane != 63) Alg::apply(E, st0);  // the value at the right end of the lane's blocks
     st = st0;
   }
-  R* Sp = Sout + (long)p * (T + 1) * N * N;
-  R* vp = vout + (long)p * (T + 1) * N;
-  if (j1 == T && !kp.seg) {
-    S_store_full<N, R>(st.S, Sp + T * N * N);
-#pragma unroll
-    for (int q = 0; q < N; ++q) vp[T * N + q] = st.v[q];
-  }
-  // The lane's v rows share cache lines (S rows are a line each): where the lane's LDS column
-  // (free once E is back in registers) holds them, they are written together after the sweep,
-  // so that no line leaves the L2 half written.
-  constexpr bool kStageV = CH * N <= Lay<N>::NE;
-  Tup<N, R> nxt;
-  tup_load(nxt, ep, j1 - 1);
-  for (long k = j1 - 1; k >= j0; --k) {
-    Tup<N, R> a = nxt;
-    if (k - 1 >= j0) tup_load(nxt, ep, k - 1);
-    Aff<N, R> m;
-    fold(a, st.S, st.v, m);
-    S_store_full<N, R>(st.S, Sp + k * N * N);
-#pragma unroll
-    for (int q = 0; q < N; ++q) {
-      if (kStageV)
-        sE[(k - j0) * N + q][lane] = st.v[q];
-      else
-        vp[k * N + q] = st.v[q];
-    }
-  }
-  if (kStageV) {
-    for (long k = j0; k < j1; ++k)
-#pragma unroll
-      for (int q = 0; q < N; ++q) vp[k * N + q] = sE[(k - j0) * N + q][lane];
-  }
+  value_sweep<N, R, CH>(kp, p, ep, j0, j1, lane, st, Sout, vout, sE);
 }
 
 template <int N, class R, int CH>
-__global__ __launch_bounds__(kThreads) void k_vscan(const KProb kp, const R* __restrict__ elts,
+__global__ __launch_bounds__(kThreads, kScanWaves<R>) void k_vscan(const KProb kp, const R* __restrict__ elts,
                                                      R* __restrict__ Sout, R* __restrict__ vout,
                                                      const LbRecs lb) {
   __shared__ R sE[Lay<N>::NE][kThreads];
   const int p = blockIdx.y;
   vscan_tile<N, R, CH>(kp, p, lb_place(lb, p), elts, Sout, vout, lb, sE);
+}
+
+// The same scan in three launches: the products of the tiles and of each lane's right neighbours in
+// its tile, the tree over the tiles (tile_kernels.hpp), the sweep from the value at each tile's right
+// end.  The look-back of the single pass resolves a tile through up to twelve Lemma 7 combinations of
+// whole waves, about 37 of its 77 us at T = 2^16, nx = 4 FP64; the tree does it in 20, and without
+// the records' polling the two kernels stream: T = 2^20 132 + 141 us for 0.42 and 0.58 GB (the
+// single pass: 302), FP32 50 + 66 (187).  The sweep goes through the tiles backwards and the build
+// before it too, so that each launch starts where the one before it ended, in what the last-level
+// cache still holds.
+template <int N, class R, int CH>
+__global__ __launch_bounds__(kThreads) void k_vred(const KProb kp, const R* __restrict__ elts,
+                                                    R* __restrict__ part, R* __restrict__ tiles) {
+  using Alg = ValAlg<N, R>;
+  const int p = blockIdx.y, lane = threadIdx.x;
+  const long T = kp.T, tile = blockIdx.x, G = gridDim.x;
+  const R* ep = elts + (long)p * Lay<N>::NE * padt(T);
+  const long j0 = tile * (64L * CH) + (long)lane * CH;
+  const long j1 = min(j0 + CH, T);
+  const int active = (int)min((T - tile * 64L * CH + CH - 1) / CH, 64L);
+  Tup<N, R> P;
+  serial_product(ep, j0, j1, P);
+  wave_scan<Alg>(P, lane, tree_levels(active));
+  if (lane == 0) tup_store_rec<PlainAcc>(P, tiles, 1, ((long)p * G + tile) * Lay<N>::NE);
+  Tup<N, R> E;
+  wave_exclusive<Alg>(P, E, lane);
+  tup_store_rec<PlainAcc>(E, part + (long)p * Lay<N>::NE * G * 64, G * 64, tile * 64 + lane);
+}
+
+template <int N, class R, int CH>
+__global__ __launch_bounds__(kThreads) void k_vswp(const KProb kp, const R* __restrict__ elts,
+                                                    const R* __restrict__ part,
+                                                    const R* __restrict__ vals, R* __restrict__ Sout,
+                                                    R* __restrict__ vout) {
+  using Alg = ValAlg<N, R>;
+  __shared__ R sE[Lay<N>::NE][kThreads];
+  const int p = blockIdx.y, lane = threadIdx.x;
+  const long T = kp.T, G = gridDim.x, tile = G - 1 - blockIdx.x;
+  const long j0 = tile * (64L * CH) + (long)lane * CH;
+  const long j1 = min(j0 + CH, T);
+  if (j0 >= T) return;
+  const R* val = vals + ((long)p * G + tile) * (N * N + N);
+  typename Alg::State st;
+#pragma unroll
+  for (int a = 0; a < N; ++a) {
+#pragma unroll
+    for (int b = a; b < N; ++b) st.S[Sym<N>::at(a, b)] = val[a * N + b];
+    st.v[a] = val[N * N + a];
+  }
+  Tup<N, R> E;
+  tup_load_rec<PlainAcc>(E, part + (long)p * Lay<N>::NE * G * 64, G * 64, tile * 64 + lane);
+  if (lane != 63) Alg::apply(E, st);
+  value_sweep<N, R, CH>(kp, p, elts + (long)p * Lay<N>::NE * padt(T), j0, j1, lane, st, Sout, vout, sE);
 }
 
 // Trajectory (Method 1 of Sec. IV-E with the exact block maps, control law of Sec. II-B): the
@@ -1488,7 +1560,7 @@ LQT_DEV void tscan_tile(const KProb& kp, int p, long i, const R* __restrict__ el
 }
 
 template <int N, int NU, class R, int CH>
-__global__ __launch_bounds__(kThreads) void k_tscan(const KProb kp, const R* __restrict__ elts,
+__global__ __launch_bounds__(kThreads, kScanWaves<R>) void k_tscan(const KProb kp, const R* __restrict__ elts,
                                                      const R* __restrict__ Sg,
                                                      const R* __restrict__ vg,
                                                      R* __restrict__ xout, R* __restrict__ uout,
@@ -2116,6 +2188,41 @@ struct L {
     hipLaunchKernelGGL((k_vscan<N, R, CH>), dim3((unsigned)lb.G, kp.batch), dim3(kThreads), 0, s,
                        kp, (const R*)elts, (R*)S, (R*)v, lb);
   }
+  template <int CH>
+  static void vred_c(const KProb& kp, const void* elts, void* part, void* tiles, hipStream_t s) {
+    hipLaunchKernelGGL((k_vred<N, R, CH>), tiles_of<CH>(kp), dim3(kThreads), 0, s, kp,
+                       (const R*)elts, (R*)part, (R*)tiles);
+  }
+  template <int CH>
+  static void vswp_c(const KProb& kp, const void* elts, const void* part, const void* vals, void* S,
+                     void* v, hipStream_t s) {
+    hipLaunchKernelGGL((k_vswp<N, R, CH>), tiles_of<CH>(kp), dim3(kThreads), 0, s, kp,
+                       (const R*)elts, (const R*)part, (const R*)vals, (R*)S, (R*)v);
+  }
+  template <int CH>
+  static dim3 tiles_of(const KProb& kp) {
+    return dim3((unsigned)((kp.T + 64L * CH - 1) / (64L * CH)), kp.batch);
+  }
+  static hipError_t vred(const KProb& kp, const void* elts, void* part, void* tiles, int chunk,
+                         hipStream_t s) {
+    switch (chunk) {
+      case 2: vred_c<2>(kp, elts, part, tiles, s); break;
+      case 4: vred_c<4>(kp, elts, part, tiles, s); break;
+      case 8: vred_c<8>(kp, elts, part, tiles, s); break;
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
+  static hipError_t vswp(const KProb& kp, const void* elts, const void* part, const void* vals,
+                         void* S, void* v, int chunk, hipStream_t s) {
+    switch (chunk) {
+      case 2: vswp_c<2>(kp, elts, part, vals, S, v, s); break;
+      case 4: vswp_c<4>(kp, elts, part, vals, S, v, s); break;
+      case 8: vswp_c<8>(kp, elts, part, vals, S, v, s); break;
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
   static hipError_t vscan(const KProb& kp, const void* elts, void* S, void* v, const LbRecs& lb,
                           int chunk, hipStream_t s) {
     switch (chunk) {
@@ -2260,7 +2367,7 @@ struct L {
                           lti_prep,       lti_build,    build_fwd,
                           m2_up,   m2_top,         m2_down,      m2_bottom,
                           dense,   build_split,    build_ckpt,   prep_clear,
-                          scan_queue};
+                          scan_queue, vred,        vswp};
     return &o;
   }
 };

@@ -17,6 +17,21 @@ hipError_t tile_build(const KProb& kp, int dtype, void* elts, hipStream_t s) {
                       : tile::launch_build<tile::Q64<3, float>>(kp, elts, s);
   return hipErrorInvalidValue;
 }
+namespace {
+template <class Mem>
+hipError_t nodes_of(const KProb& kp, const GTree& t, const Work& w, hipStream_t s) {
+  switch (kp.nx) {
+    case 1: return tile::launch_value_tree<tile::Q64<1, Mem>>(kp, t, w, s);
+    case 2: return tile::launch_value_tree<tile::Q64<2, Mem>>(kp, t, w, s);
+    case 3: return tile::launch_value_tree<tile::Q64<3, Mem>>(kp, t, w, s);
+    case 4: return tile::launch_value_tree<tile::Q64<4, Mem>>(kp, t, w, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+}  // namespace
+hipError_t tile_nodes(const KProb& kp, int dtype, const GTree& t, const Work& w, hipStream_t s) {
+  return dtype == 0 ? nodes_of<double>(kp, t, w, s) : nodes_of<float>(kp, t, w, s);
+}
 hipError_t tile_value(const KProb& kp, const GTree& t, const Work& w, const void* elts, void* S,
                       void* v, hipStream_t s) {
   return tile::launch_value<Q4>(kp, t, w, elts, S, v, false, s);

@@ -32,18 +32,13 @@ constexpr int kGroupThreads = 64 * kGroupWaves<B>;
 // Arrays of the trees in the workspace (vtup, vval and tmap, tx): 1 sibling records of the bottom
 // stage's slots, 2 its groups, 3 + 2 j and 4 + 2 j those of upper stage j.
 //
-// Values of every boundary; with maps also the bottom groups' maps and, if the workspace has room
-// for them, every block's map.
+// Values at the right ends of the upper stages' nodes (vval[2]) from the nodes (vtup[2]).
 template <class B>
-hipError_t launch_value(const KProb& kp, const GTree& t, const Work& w, const void* elts, void* S,
-                        void* v, bool maps, hipStream_t s) {
+hipError_t launch_value_tree(const KProb& kp, const GTree& t, const Work& w, hipStream_t s) {
   using Mem = typename B::Mem;
   if (t.G != kGroup<B>) return hipErrorInvalidValue;
-  const int nb = kp.batch, run = bottom_run<B>(t.wc);
-  const dim3 b(kGroupThreads<B>), g0(spread_grid(t.m, run), nb);
-  const Stage s0 = bottom<B>(t);
-  hipLaunchKernelGGL((kt_vup<B>), g0, b, 0, s, s0, 1, run, (const Mem*)elts, (Mem*)w.vtup[1],
-                     (Mem*)w.vtup[2]);
+  const int nb = kp.batch;
+  const dim3 b(kGroupThreads<B>);
   for (int j = 0; j + 1 < t.up; ++j)
     hipLaunchKernelGGL((kt_vup<B>), dim3((unsigned)t.grp[j], nb), b, 0, s, upper(t, j), 0, 1,
                        (const Mem*)w.vtup[2 + 2 * j], (Mem*)w.vtup[3 + 2 * j],
@@ -58,6 +53,23 @@ hipError_t launch_value(const KProb& kp, const GTree& t, const Work& w, const vo
                          (const Mem*)w.vtup[2 + 2 * j], (const Mem*)w.vtup[3 + 2 * j],
                          (const Mem*)w.vval[4 + 2 * j], (Mem*)w.vval[2 + 2 * j]);
   }
+  return hipGetLastError();
+}
+
+// Values of every boundary; with maps also the bottom groups' maps and, if the workspace has room
+// for them, every block's map.
+template <class B>
+hipError_t launch_value(const KProb& kp, const GTree& t, const Work& w, const void* elts, void* S,
+                        void* v, bool maps, hipStream_t s) {
+  using Mem = typename B::Mem;
+  if (t.G != kGroup<B>) return hipErrorInvalidValue;
+  const int nb = kp.batch, run = bottom_run<B>(t.wc);
+  const dim3 b(kGroupThreads<B>), g0(spread_grid(t.m, run), nb);
+  const Stage s0 = bottom<B>(t);
+  hipLaunchKernelGGL((kt_vup<B>), g0, b, 0, s, s0, 1, run, (const Mem*)elts, (Mem*)w.vtup[1],
+                     (Mem*)w.vtup[2]);
+  const hipError_t e = launch_value_tree<B>(kp, t, w, s);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((kt_vbottom<B>), g0, b, 0, s, kp, s0, run, (const Mem*)elts,
                      (const Mem*)w.vtup[1], (const Mem*)w.vval[2], (Mem*)S, (Mem*)v,
                      (Mem*)w.tmap[1], (Mem*)(maps ? w.tmap[2] : nullptr),

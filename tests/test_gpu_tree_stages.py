@@ -62,3 +62,21 @@ def test_wave_sizes(nx, T, dtype):
                                         (4, 32769, torch.float64)])
 def test_build_rule(nx, T, dtype):
     _check([W.random_stable(nx + T, nx, 2, T, 1, tf=2.0)], dtype)
+
+
+# The value scan in three launches (nx = 3, 4; tiles of 64 x 2, 4 or 8 blocks): one block short of and
+# past its first horizon, whole and ragged tiles, and the changes of the blocks per lane; nx = 3 leaves
+# it at 32769 blocks.
+@pytest.mark.parametrize("nx,T,batch,dtype", [
+    (3, 512, 1, torch.float64), (3, 513, 1, torch.float64), (3, 640, 2, torch.float32),
+    (3, 16385, 1, torch.float64), (3, 32768, 1, torch.float32), (3, 32769, 1, torch.float64),
+    (4, 513, 1, torch.float32), (4, 1023, 3, torch.float32), (4, 16384, 1, torch.float32),
+    (4, 65537, 1, torch.float64), (4, 131073, 1, torch.float64), (4, 65537, 2, torch.float64)])
+def test_split_value_scan(nx, T, batch, dtype):
+    if batch == 1:
+        ps = [W.random_stable(nx + T, nx, 2, T, 1, tf=2.0)]
+    else:
+        ps = [W.random_stable(5, nx, 2, T, 1, tf=2.0, time_varying=False) for _ in range(batch)]
+        for b, p in enumerate(ps):
+            p.r, p.x0 = p.r * (1.0 + b), p.x0 - b
+    _check(ps, dtype)
