@@ -277,14 +277,25 @@ bool use_tile_scans(const lqt_dims* d) {
 // 40000 and slower beyond; nx = 1, 2, whose combinations are short: 46 vs 42 at nx = 2 and T = 17000.
 // Blocks per lane: the single pass's, of all problems, but at least 2 (a wave's scan over its lanes is
 // six combinations, so fewer blocks a lane only add waves of them: T = 100000 29 + 17 us with 4, 32 +
-// 22 with 2).
-int split_chunk(long T, long batch) {
-  return std::max(2, scan_chunk(T * batch, kScanMaxVChunk));
+// 22 with 2); with the elements formed in the same launch (tables) 4 up to one round of resident waves
+// (T = 200003: solve 177 us with 4, 181 with 8).
+int split_chunk(const lqt_dims* d, bool tables) {
+  const long blocks = (long)d->T * d->batch;
+  return tables && blocks <= 1L << 18 ? 4 : std::max(2, scan_chunk(blocks, kScanMaxVChunk));
 }
-GTree split_tree(int nx, long T, long batch) { return node_tree(nx, T, 64 * split_chunk(T, batch)); }
 bool use_split_scan(const lqt_dims* d) {
   if (use_wave(d) || d->nx < 3) return false;
   return d->nx == 4 ? d->T > 512 : d->T > 512 && d->T <= 1L << 15;
+}
+
+// The check of the grid and the first-order tables instead of the general build (k_uni_prep,
+// k_lti_red).  Check and tables take 20 us and the launches that find nothing to do 9, whatever T; at
+// T = 2^20, n = 4 they replace 441 us of build and reduction by 208 (solve 753 -> 595 us), and a grid of
+// uneven blocks pays 805 (the single pass: 787).  Below 2^19 blocks such a grid would lose more: 271 vs
+// 250 at 2^18, where the even one gains 250 -> 204.  FP32 block lengths are too coarse for it.
+bool use_uniform(const lqt_dims* d) {
+  return !d->lti && !d->F_sampled && !d->L_sampled && !d->has_c && d->dtype == LQT_F64 &&
+         (long)d->T * d->batch > 1L << 19;
 }
 
 }  // namespace
@@ -418,10 +429,16 @@ size_t layout(const lqt_dims* d, lqt_call call, char* base, Work* w, int wc, lon
   if (want_t) take_lb(w ? &w->lbt : nullptr, 64, nm_of(d->nx), d->nx);
   if (!tile && use_split_scan(d) &&
       (call == LQT_CALL_SCAN_VALUE || (call == LQT_CALL_SOLVE && keep_maps && nconsts == d->batch))) {
-    const GTree vt = split_tree(d->nx, d->T, d->batch);
+    const bool solve = call == LQT_CALL_SOLVE;
+    const int c = split_chunk(d, solve && (d->lti || use_uniform(d)));
+    const GTree vt = node_tree(d->nx, d->T, 64 * c);
     void* a = take(es * B * ne_of(d->nx) * 64 * vt.m);
-    if (w) w->vpart[1] = a;
+    if (w) w->vpart[1] = a, w->split = c;
     upper_stages(vt, true, false);
+    if (solve && use_uniform(d)) {
+      void* b = take(es * B * 2 * lti_count(d->nx, d->n_steps));
+      if (w) w->uni = b;
+    }
   }
   // Method 2: the tree of node products and prefix states
   if (call == LQT_CALL_TRAJ_METHOD2) {
@@ -738,12 +755,11 @@ LbRecs lb_for(const LbRecs& r, long T, int chunk) {
 // Value scan over elements (single pass; per-lane path).
 // cleared: the records' status words were already cleared (the solve clears both scans' at once).
 lqt_status run_value(const Ops* o, const KProb& kp, int dtype, const Work& w, const void* elts, void* S,
-                     void* v, hipStream_t s, bool cleared = false) {
-  int c = scan_chunk(kp.T, kScanMaxVChunk);
-  if (w.vpart[1]) {
-    c = split_chunk(kp.T, kp.batch);
-    LQT_HIP(o->vred(kp, elts, w.vpart[1], w.vtup[2], c, s));
-    LQT_HIP(tile_nodes(kp, dtype, split_tree(kp.nx, kp.T, kp.batch), w, s));
+                     void* v, hipStream_t s, bool cleared = false, bool reduced = false) {
+  const int c = w.split ? w.split : scan_chunk(kp.T, kScanMaxVChunk);
+  if (w.split) {
+    if (!reduced) LQT_HIP(o->vred(kp, nullptr, elts, w.vpart[1], w.vtup[2], c, s));
+    LQT_HIP(tile_nodes(kp, dtype, node_tree(kp.nx, kp.T, 64 * c), w, s));
     LQT_HIP(o->vswp(kp, elts, w.vpart[1], w.vval[2], S, v, c, s));
     return LQT_OK;
   }
@@ -995,8 +1011,20 @@ lqt_status run_solve(const lqt_dims* dims, const KProb& kp, const Work& w, void*
   LQT_HIP(op->prep_clear(kprep, w.consts, w.lbv, w.lbt, stream));
   const bool lti = kp.lti && !kp.seg && w.lti;
   KProb kb = kp;
-  kb.rev = w.vpart[1] != nullptr;
-  if (lti) {
+  kb.rev = w.split != 0;
+  bool reduced = false;
+  if (w.split && !kp.seg && !o.queue_chunk && (lti || w.uni)) {
+    const int c = w.split;
+    unsigned* bad = lti ? nullptr : (unsigned*)w.lbv.ctr;  // cleared with the status words
+    const void* tab = lti ? w.lti : w.uni;
+    LQT_HIP(lti ? op->lti_prep(kp, w.lti, stream) : op->uni_prep(kp, w.uni, bad, stream));
+    LQT_HIP(op->lti_red(kp, tab, bad, e, w.vpart[1], w.vtup[2], c, stream));
+    if (bad) {
+      LQT_HIP(op->build_rest(kp, bad, e, stream));
+      LQT_HIP(op->vred(kp, bad, e, w.vpart[1], w.vtup[2], c, stream));
+    }
+    reduced = true;
+  } else if (lti) {
     LQT_HIP(op->lti_prep(kp, w.lti, stream));
     LQT_HIP(op->lti_build(kb, w.lti, e, stream));
   } else if (use_tile_build(dims)) {
@@ -1015,7 +1043,7 @@ lqt_status run_solve(const lqt_dims* dims, const KProb& kp, const Work& w, void*
                              lb_for(w.lbt, kp.T, queue_tchunk(cv)), cv, stream));
     return LQT_OK;
   }
-  LQT_TRY(run_value(op, kp, dims->dtype, w, e, S, v, stream, true));
+  LQT_TRY(run_value(op, kp, dims->dtype, w, e, S, v, stream, true, reduced));
   LQT_TRY(run_traj(op, kp, w, e, S, v, x, u, stream, true));
   return LQT_OK;
 }

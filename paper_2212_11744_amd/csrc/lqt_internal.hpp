@@ -126,6 +126,8 @@ struct LbRecs {
 struct Work {
   void* consts = nullptr;
   LbRecs lbv, lbt;                   // single-pass value and trajectory scans (per-lane path)
+  int split = 0;        // blocks per lane of the value scan in three launches (0: single pass)
+  void* uni = nullptr;  // tables of uni_prep (2 lti_count values per problem)
   void* vtup[kMaxLevels + 1] = {};   // value tree: tuples at level l >= 1
   void* vval[kMaxLevels + 1] = {};   // value tree: (packed S, v) at right ends of level-l nodes
   void* vpart[kMaxLevels + 1] = {};  // value tree: lane partials of the wave trees above level l
@@ -203,9 +205,17 @@ struct Ops {
   hipError_t (*scan_queue)(const KProb&, const void* elts, void* S, void* v, void* x, void* u,
                              const LbRecs& lbv, const LbRecs& lbt, int cv, hipStream_t);
   // the value scan in three launches: tile products and lane partials, (tile_nodes), sweep
-  hipError_t (*vred)(const KProb&, const void* elts, void* part, void* tiles, int chunk, hipStream_t);
+  // (bad: only the problems marked there; nullptr: all)
+  hipError_t (*vred)(const KProb&, const unsigned* bad, const void* elts, void* part, void* tiles,
+                     int chunk, hipStream_t);
   hipError_t (*vswp)(const KProb&, const void* elts, const void* part, const void* vals, void* S,
                      void* v, int chunk, hipStream_t);
+  // time-invariant elements and their vred in one; with bad to first order in the blocks' lengths, for
+  // the problems uni_prep (tables, grid check) has not marked; build_rest: the elements of the others
+  hipError_t (*lti_red)(const KProb&, const void* tab, const unsigned* bad, void* elts, void* part,
+                        void* tiles, int chunk, hipStream_t);
+  hipError_t (*uni_prep)(const KProb&, void* tab, unsigned* bad, hipStream_t);
+  hipError_t (*build_rest)(const KProb&, const unsigned* bad, void* elts, hipStream_t);
 };
 
 // Adjoint kernels (lqt_adjoint.hip) of one (nx, nu, dtype) instantiation.

@@ -96,12 +96,15 @@ template <int N, class R>
 struct RMem {
   const R* r;
   LQT_DEV R operator()(long j, int i) const { return r[j * N + i]; }
+  LQT_DEV R step(R h) const { return h; }  // the RK4 step of a block whose own is h
 };
 template <class R>
 struct RImpulse {
   long j0;
   int i0;
+  R hs = R(0);  // another step than the block's
   LQT_DEV R operator()(long j, int i) const { return j == j0 && i == i0 ? R(1) : R(0); }
+  LQT_DEV R step(R h) const { return hs > R(0) ? hs : h; }
 };
 
 // nsteps < n stops at s = t_{k+1} - nsteps h: the tuple of V(., t_{k+1} - nsteps h; ., t_{k+1}).
@@ -155,7 +158,7 @@ LQT_DEV void build_block_rs(const KProb& kp, const Blk& bk, const RS& rs, Tup<N,
       for (int j = 0; j < NU; ++j) Wr[i][j] = cs[CS<N, NU>::W + i * NU + j];
   }
 
-  const R h = (t[1] - t[0]) / R(n);
+  const R h = rs.step((t[1] - t[0]) / R(n));
   R yA[N][N], yb[N], yC[NS], ye[N], yJ[NS];
 #pragma unroll
   for (int i = 0; i < N; ++i) {
@@ -732,8 +735,10 @@ __global__ __launch_bounds__(kThreads) void k_lti_prep(const KProb kp, R* __rest
 // b = sum_j V[j] r_j, eta = sum_j W[j] r_j over the block's samples r_0 .. r_2n (rp points at
 // r_0).  MAXJ > 0: the loop is unrolled to MAXJ samples (n_steps <= (MAXJ - 1) / 2) so that all
 // loads of the block are in flight together.
-template <int N, class R, int MAXJ>
-LQT_DEV void lti_sums(const R* rp, const R* tp, int n, Tup<N, R>& out) {
+// UNI: V + d Vd, W + d Wd instead, from a second table at td.
+template <int N, class R, int MAXJ, bool UNI = false>
+LQT_DEV void lti_sums(const R* rp, const R* tp, int n, Tup<N, R>& out, R d = R(0),
+                      const R* td = nullptr) {
 #pragma unroll
   for (int a = 0; a < N; ++a) {
     out.b[a] = R(0);
@@ -751,8 +756,14 @@ LQT_DEV void lti_sums(const R* rp, const R* tp, int n, Tup<N, R>& out) {
     for (int a = 0; a < N; ++a)
 #pragma unroll
       for (int i = 0; i < N; ++i) {
-        out.b[a] = fma(V[a * N + i], r[i], out.b[a]);
-        out.e[a] = fma(W[a * N + i], r[i], out.e[a]);
+        const long q = (long)j * N * N + a * N + i;
+        R va = V[a * N + i], wa = W[a * N + i];
+        if (UNI) {
+          va = fma(d, td[lti_off_V(N) + q], va);
+          wa = fma(d, td[lti_off_W(N, n) + q], wa);
+        }
+        out.b[a] = fma(va, r[i], out.b[a]);
+        out.e[a] = fma(wa, r[i], out.e[a]);
       }
   };
   if (MAXJ > 0) {
@@ -1415,10 +1426,12 @@ __global__ __launch_bounds__(kThreads, kScanWaves<R>) void k_vscan(const KProb k
 // before it too, so that each launch starts where the one before it ended, in what the last-level
 // cache still holds.
 template <int N, class R, int CH>
-__global__ __launch_bounds__(kThreads) void k_vred(const KProb kp, const R* __restrict__ elts,
+__global__ __launch_bounds__(kThreads) void k_vred(const KProb kp, const unsigned* __restrict__ bad,
+                                                    const R* __restrict__ elts,
                                                     R* __restrict__ part, R* __restrict__ tiles) {
   using Alg = ValAlg<N, R>;
   const int p = blockIdx.y, lane = threadIdx.x;
+  if (bad && !bad[p]) return;  // reduced with its build (k_lti_red)
   const long T = kp.T, tile = blockIdx.x, G = gridDim.x;
   const R* ep = elts + (long)p * Lay<N>::NE * padt(T);
   const long j0 = tile * (64L * CH) + (long)lane * CH;
@@ -1457,6 +1470,141 @@ __global__ __launch_bounds__(kThreads) void k_vswp(const KProb kp, const R* __re
   tup_load_rec<PlainAcc>(E, part + (long)p * Lay<N>::NE * G * 64, G * 64, tile * 64 + lane);
   if (lane != 63) Alg::apply(E, st);
   value_sweep<N, R, CH>(kp, p, elts + (long)p * Lay<N>::NE * padt(T), j0, j1, lane, st, Sout, vout, sE);
+}
+
+// ------------------------------------------------------------------------------------------
+// Constant F and L, no drift, blocks of equal length up to rounding (|h_k - h| <= 2^-27 h, h their
+// mean): the time-invariant path to first order in h_k - h.  Two tables per problem: the response
+// at h, and the change of it per 2^-20 h from a second integration at h (1 + 2^-20); what the
+// second order leaves out is below 2^-54.  A problem with another grid is marked in bad (cleared
+// before) and takes the general build.
+// ------------------------------------------------------------------------------------------
+constexpr double kUniTol = 0x1p-27, kUniStep = 0x1p-20;
+
+template <int N, int NU, class R>
+__global__ __launch_bounds__(kThreads) void k_uni_prep(const KProb kp, R* __restrict__ tab,
+                                                        unsigned* __restrict__ bad,
+                                                        int prep_blocks) {
+  const int p = blockIdx.y;
+  const long T = kp.T;
+  const R* t = (const R*)kp.t + (long)p * (T + 1);
+  const R h0 = (t[T] - t[0]) / R(T);
+  if ((int)blockIdx.x >= prep_blocks) {
+    const long k0 = (long)(blockIdx.x - prep_blocks) * 4 * kThreads + threadIdx.x;
+    R h[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const long k = min(k0 + q * kThreads, T - 1);
+      h[q] = t[k + 1] - t[k];
+    }
+    bool ok = true;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) ok = ok && fabs(h[q] - h0) <= h0 * R(kUniTol);
+    if (__ballot(!ok) != 0ull && threadIdx.x == 0) bad[p] = 1u;
+    return;
+  }
+  const int n = kp.n;
+  const long M = (2L * n + 1) * N, m = min(gid() >> 1, M - 1);
+  const bool second = gid() & 1;
+  const long j0 = m / N;
+  const int i0 = (int)(m % N);
+  const R h = second ? h0 * R(1 + kUniStep) : h0;
+  Tup<N, R> out;
+  const Blk bk{p, 0, 0, (long)p * (T + 1)};
+  build_block_rs<N, NU, R, true>(kp, bk, RImpulse<R>{j0, i0, h / R(n)}, out, n);
+  R* tp = tab + ((long)p * 2 + second) * lti_count(N, n);
+  auto put = [&](long q, R x, bool on) {
+    const R first = __shfl_xor(x, 1, 64);
+    if (on) tp[q] = second ? x - first : x;
+  };
+#pragma unroll
+  for (int a = 0; a < N; ++a) {
+    put(lti_off_V(N) + (j0 * N + a) * N + i0, out.b[a], true);
+    put(lti_off_W(N, n) + (j0 * N + a) * N + i0, out.e[a], true);
+#pragma unroll
+    for (int b = 0; b < N; ++b) put(a * N + b, out.A[a][b], m == 0);
+  }
+#pragma unroll
+  for (int q = 0; q < Sym<N>::size; ++q) {
+    put(N * N + q, out.C[q], m == 0);
+    put(N * N + Sym<N>::size + q, out.J[q], m == 0);
+  }
+}
+
+// Elements from the tables, and the reduction of k_vred over them while they are in registers: a
+// pass over the elements and a launch less.  Bound by memory, the samples read and the elements
+// written once.
+template <int N, class R, int CH, bool UNI>
+__global__ __launch_bounds__(kThreads) void k_lti_red(const KProb kp, const R* __restrict__ tab,
+                                                       const unsigned* __restrict__ bad,
+                                                       R* __restrict__ elts, R* __restrict__ part,
+                                                       R* __restrict__ tiles) {
+  using Alg = ValAlg<N, R>;
+  const int p = blockIdx.y, lane = threadIdx.x;
+  if (UNI && bad[p]) return;
+  const int n = kp.n;
+  const long T = kp.T, tile = blockIdx.x, G = gridDim.x;
+  R* ep = elts + (long)p * Lay<N>::NE * padt(T);
+  const long j0 = tile * (64L * CH) + (long)lane * CH;
+  const long j1 = min(j0 + CH, T);
+  const int active = (int)min((T - tile * 64L * CH + CH - 1) / CH, 64L);
+  const R* tp = tab + (long)p * (UNI ? 2 : 1) * lti_count(N, n);
+  const R* td = UNI ? tp + lti_count(N, n) : nullptr;
+  const R* t = (const R*)kp.t + (long)p * (T + 1);
+  const R* rbase = (const R*)kp.r + (long)p * (2L * n * T + 1) * N;
+  const R h0 = (t[T] - t[0]) / R(T), scale = R(1) / (h0 * R(kUniStep));
+  Tup<N, R> P;
+  tup_identity(P);
+#pragma unroll 1
+  for (int r = CH - 1; r >= 0; --r) {
+    const long k = j0 + r;
+    if (k >= T) continue;
+    Tup<N, R> x;
+    const R d = UNI ? ((t[k + 1] - t[k]) - h0) * scale : R(0);
+    if (n <= kLtiMaxStageSteps)
+      lti_sums<N, R, 2 * kLtiMaxStageSteps + 1, UNI>(rbase + 2L * n * k * N, tp, n, x, d, td);
+    else
+      lti_sums<N, R, 0, UNI>(rbase + 2L * n * k * N, tp, n, x, d, td);
+    auto at = [&](int q) { return UNI ? fma(d, td[q], tp[q]) : tp[q]; };
+#pragma unroll
+    for (int a = 0; a < N; ++a)
+#pragma unroll
+      for (int b = 0; b < N; ++b) x.A[a][b] = at(a * N + b);
+#pragma unroll
+    for (int q = 0; q < Sym<N>::size; ++q) {
+      x.C[q] = at(N * N + q);
+      x.J[q] = at(N * N + Sym<N>::size + q);
+    }
+    tup_store(x, ep, k);
+    if (k == j1 - 1)
+      P = x;
+    else
+      combine(x, P, P);
+  }
+  wave_scan<Alg>(P, lane, tree_levels(active));
+  if (lane == 0) tup_store_rec<PlainAcc>(P, tiles, 1, ((long)p * G + tile) * Lay<N>::NE);
+  Tup<N, R> E;
+  wave_exclusive<Alg>(P, E, lane);
+  tup_store_rec<PlainAcc>(E, part + (long)p * Lay<N>::NE * G * 64, G * 64, tile * 64 + lane);
+}
+
+// The general build of the problems marked bad, on as many waves as are resident at once: with no
+// problem marked it ends as soon as they have started.
+template <int N, int NU, class R>
+__global__ __launch_bounds__(kThreads) void k_build_rest(const KProb kp,
+                                                          const unsigned* __restrict__ bad,
+                                                          R* __restrict__ elts) {
+  const int p = blockIdx.y;
+  if (!bad[p]) return;
+  const long T = kp.T, nb = padt(T) / kThreads;
+#pragma unroll 1
+  for (long b = nb - 1 - blockIdx.x; b >= 0; b -= gridDim.x) {
+    const long k = tile_row_item(b * kThreads + threadIdx.x);
+    if (k >= T) continue;
+    Tup<N, R> out;
+    build_block<N, NU, R, true>(kp, blk_plain(kp, p, k), out);
+    tup_store(out, elts + (long)p * Lay<N>::NE * padt(T), k);
+  }
 }
 
 // Trajectory (Method 1 of Sec. IV-E with the exact block maps, control law of Sec. II-B): the
@@ -2189,9 +2337,44 @@ struct L {
                        kp, (const R*)elts, (R*)S, (R*)v, lb);
   }
   template <int CH>
-  static void vred_c(const KProb& kp, const void* elts, void* part, void* tiles, hipStream_t s) {
-    hipLaunchKernelGGL((k_vred<N, R, CH>), tiles_of<CH>(kp), dim3(kThreads), 0, s, kp,
+  static void vred_c(const KProb& kp, const unsigned* bad, const void* elts, void* part, void* tiles,
+                     hipStream_t s) {
+    hipLaunchKernelGGL((k_vred<N, R, CH>), tiles_of<CH>(kp), dim3(kThreads), 0, s, kp, bad,
                        (const R*)elts, (R*)part, (R*)tiles);
+  }
+  template <int CH>
+  static void lti_red_c(const KProb& kp, const void* tab, const unsigned* bad, void* elts, void* part,
+                        void* tiles, hipStream_t s) {
+    if (bad)
+      hipLaunchKernelGGL((k_lti_red<N, R, CH, true>), tiles_of<CH>(kp), dim3(kThreads), 0, s, kp,
+                         (const R*)tab, bad, (R*)elts, (R*)part, (R*)tiles);
+    else
+      hipLaunchKernelGGL((k_lti_red<N, R, CH, false>), tiles_of<CH>(kp), dim3(kThreads), 0, s, kp,
+                         (const R*)tab, bad, (R*)elts, (R*)part, (R*)tiles);
+  }
+  static hipError_t lti_red(const KProb& kp, const void* tab, const unsigned* bad, void* elts,
+                            void* part, void* tiles, int chunk, hipStream_t s) {
+    switch (chunk) {
+      case 2: lti_red_c<2>(kp, tab, bad, elts, part, tiles, s); break;
+      case 4: lti_red_c<4>(kp, tab, bad, elts, part, tiles, s); break;
+      case 8: lti_red_c<8>(kp, tab, bad, elts, part, tiles, s); break;
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
+  static hipError_t uni_prep(const KProb& kp, void* tab, unsigned* bad, hipStream_t s) {
+    const int pb = (int)((2 * (2L * kp.n + 1) * N + kThreads - 1) / kThreads);
+    // four block lengths a lane: the check ends before the tables do
+    const int check = (int)((kp.T + 4L * kThreads - 1) / (4 * kThreads));
+    hipLaunchKernelGGL((k_uni_prep<N, NU, R>), dim3((unsigned)(pb + check), kp.batch),
+                       dim3(kThreads), 0, s, kp, (R*)tab, bad, pb);
+    return hipGetLastError();
+  }
+  static hipError_t build_rest(const KProb& kp, const unsigned* bad, void* elts, hipStream_t s) {
+    const long nb = padt(kp.T) / kThreads;
+    hipLaunchKernelGGL((k_build_rest<N, NU, R>), dim3((unsigned)(nb < 1024 ? nb : 1024), kp.batch),
+                       dim3(kThreads), 0, s, kp, bad, (R*)elts);
+    return hipGetLastError();
   }
   template <int CH>
   static void vswp_c(const KProb& kp, const void* elts, const void* part, const void* vals, void* S,
@@ -2203,12 +2386,12 @@ struct L {
   static dim3 tiles_of(const KProb& kp) {
     return dim3((unsigned)((kp.T + 64L * CH - 1) / (64L * CH)), kp.batch);
   }
-  static hipError_t vred(const KProb& kp, const void* elts, void* part, void* tiles, int chunk,
-                         hipStream_t s) {
+  static hipError_t vred(const KProb& kp, const unsigned* bad, const void* elts, void* part,
+                         void* tiles, int chunk, hipStream_t s) {
     switch (chunk) {
-      case 2: vred_c<2>(kp, elts, part, tiles, s); break;
-      case 4: vred_c<4>(kp, elts, part, tiles, s); break;
-      case 8: vred_c<8>(kp, elts, part, tiles, s); break;
+      case 2: vred_c<2>(kp, bad, elts, part, tiles, s); break;
+      case 4: vred_c<4>(kp, bad, elts, part, tiles, s); break;
+      case 8: vred_c<8>(kp, bad, elts, part, tiles, s); break;
       default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -2367,7 +2550,7 @@ struct L {
                           lti_prep,       lti_build,    build_fwd,
                           m2_up,   m2_top,         m2_down,      m2_bottom,
                           dense,   build_split,    build_ckpt,   prep_clear,
-                          scan_queue, vred,        vswp};
+                          scan_queue, vred,        vswp,         lti_red, uni_prep, build_rest};
     return &o;
   }
 };

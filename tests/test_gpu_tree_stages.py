@@ -80,3 +80,41 @@ def test_split_value_scan(nx, T, batch, dtype):
         for b, p in enumerate(ps):
             p.r, p.x0 = p.r * (1.0 + b), p.x0 - b
     _check(ps, dtype)
+
+
+def _grid(T, uneven):
+    t = np.linspace(0.0, 10.0, T + 1)
+    if uneven is not None:  # one block longer by 1e-6 of its length
+        t[uneven + 1:] += 1e-6 * (t[1] - t[0])
+    return t
+
+
+# Constant F and L beyond 2^19 blocks (the elements from tables to first order in the blocks' lengths
+# where the grid is even to 2^-27, the general build elsewhere, problem by problem).
+@pytest.mark.parametrize("T,n,uneven", [(524289, 1, [None]), (524289, 5, [None]), (524301, 2, [0]),
+                                        (524301, 1, [524300]), (262145, 2, [None, 131000])])
+def test_even_grid(T, n, uneven):
+    _check([W.point_mass(3 + b, T, n, t_grid=_grid(T, u)) for b, u in enumerate(uneven)])
+
+
+def test_even_grid_nx3():
+    ps = [W.random_stable(8, 3, 2, 32768, 1, tf=2.0, time_varying=False) for _ in range(17)]
+    for b, p in enumerate(ps):
+        p.r = p.r * (1.0 + 0.1 * b)
+    _check(ps, check=(0, 16))
+
+
+@pytest.mark.parametrize("nx,T,n,batch", [(4, 70001, 5, 1), (4, 140001, 2, 1), (4, 300007, 1, 1),
+                                          (3, 1025, 4, 2)])
+def test_time_invariant_reduction(nx, T, n, batch):
+    ps = [W.random_stable(8, nx, 2, T, n, tf=2.0, time_varying=False) for _ in range(batch)]
+    for b, p in enumerate(ps):
+        p.r = p.r * (1.0 + 0.1 * b)
+    dp = lqt.DeviceProblem.from_problems(ps)
+    dp.lti = True  # even to rounding, which is more than 1e-12 of such short blocks
+    out = lqt.solve(dp)
+    for b, p in enumerate(ps):
+        ref = O.solve(p)
+        for k in ("S", "v", "x", "u"):
+            e = relerr(out[k][b].cpu().numpy(), ref[k])
+            assert e < TOL[torch.float64], f"problem {b} {k}: {e:.3e}"
