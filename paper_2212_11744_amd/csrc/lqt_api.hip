@@ -271,10 +271,11 @@ bool use_tile_scans(const lqt_dims* d) {
 }
 
 // The value scan of the per-lane path in three launches (k_vred, the tree over its tiles, k_vswp)
-// instead of a single pass.  Measured in a solve or alone (us): nx = 4 FP64
-// scan 84 vs 101 at T = 150000, 189 vs 233 at 600000; nx = 4 FP32 solve 62 vs 62 at 600, 58 vs 71 at
-// 4000, 282 vs 344 at 600000; nx = 3 solve 45.8 vs 49.2 at 2000, 67 vs 71 at 20000, 79.3 vs 79.3 at
-// 40000 and slower beyond; nx = 1, 2, whose combinations are short: 46 vs 42 at nx = 2 and T = 17000.
+// instead of a single pass.  Measured in a solve or alone (us): nx = 4 FP64 scan 84 vs 101 at
+// T = 150000, 189 vs 233 at 600000; nx = 4 FP32 scan 28 vs 33 at 600 (32 vs 29 at 300), 36 vs 41 at
+// 4000, solve 282 vs 344 at 600000; nx = 3 scan 22.4 vs 20.9 at 600, 27.2 vs 27.9 at 8000, 31 vs 37 at
+// 20000, 33 vs 37 at 28000, solve 79.3 vs 79.3 at 40000 and slower beyond; nx = 1, 2, whose
+// combinations are short: solve 46 vs 42 at nx = 2 and T = 17000.
 // Blocks per lane: the single pass's, of all problems, but at least 2 (a wave's scan over its lanes is
 // six combinations, so fewer blocks a lane only add waves of them: T = 100000 29 + 17 us with 4, 32 +
 // 22 with 2); with the elements formed in the same launch (tables) 4 up to one round of resident waves
@@ -285,7 +286,7 @@ int split_chunk(const lqt_dims* d, bool tables) {
 }
 bool use_split_scan(const lqt_dims* d) {
   if (use_wave(d) || d->nx < 3) return false;
-  return d->nx == 4 ? d->T > 512 : d->T > 512 && d->T <= 1L << 15;
+  return d->nx == 4 ? d->T > 512 : d->T > 1L << 13 && d->T <= 1L << 15;
 }
 
 // The check of the grid and the first-order tables instead of the general build (k_uni_prep,

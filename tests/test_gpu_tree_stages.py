@@ -65,8 +65,8 @@ def test_build_rule(nx, T, dtype):
 
 
 # The value scan in three launches (nx = 3, 4; tiles of 64 x 2, 4 or 8 blocks): one block short of and
-# past its first horizon, whole and ragged tiles, and the changes of the blocks per lane; nx = 3 leaves
-# it at 32769 blocks.
+# past its first horizon (nx = 4; nx = 3 takes it from 8193 to 32768 blocks, see test_build_rule), whole
+# and ragged tiles, and the changes of the blocks per lane.
 @pytest.mark.parametrize("nx,T,batch,dtype", [
     (3, 512, 1, torch.float64), (3, 513, 1, torch.float64), (3, 640, 2, torch.float32),
     (3, 16385, 1, torch.float64), (3, 32768, 1, torch.float32), (3, 32769, 1, torch.float64),
