@@ -14,6 +14,7 @@
 #pragma once
 
 #include "tile.hpp"
+#include "tree_pairs.hpp"
 
 namespace lqt {
 namespace tile {
@@ -360,18 +361,10 @@ TDEV Tup<B> t_serial(const Here<B>& h, const Stage& st, bool src_elts, const typ
   return acc;
 }
 
-// Pair q of a round of distance s: places 2 s q and 2 s q + s of a group of cnt slots.  A node
-// without a pair takes the first one's operands and stores nothing.
+// This node's pair in a round of distance s (tree_pairs.hpp).
 template <class B>
-struct Pair {
-  int r;
-  bool any, on;  // a pair in the wave, in the node
-  TDEV Pair(const Here<B>& h, int s) {
-    r = 2 * s * (h.w * B::NODES + B::node());
-    any = 2 * s * h.w * B::NODES + s < h.cnt;
-    on = r + s < h.cnt;
-    if (!on) r = 0;
-  }
+struct Pair : PairPlaces {
+  TDEV Pair(const Here<B>& h, int s) : PairPlaces(pair_places(h.w, B::node(), B::NODES, s, h.cnt)) {}
 };
 
 // Group product of the slots' products.  Slot loc sits at place cnt - 1 - loc of ex (the last slot
