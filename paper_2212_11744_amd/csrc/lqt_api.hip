@@ -124,11 +124,11 @@ void upper_stages(GTree& t) {
 }
 }  // namespace
 
-GTree group_tree(int nx, long T, int wc) {
+GTree group_tree(int nx, long T, int wc, bool shorten) {
   GTree t;
   t.G = group_slots(nx);
   // a horizon of one group: as few blocks in a row as that allows
-  while (wc > 1 && T <= wc / 2 * t.G) wc /= 2;
+  while (shorten && wc > 1 && T <= wc / 2 * t.G) wc /= 2;
   t.wc = wc;
   t.T = T;
   t.n1 = (T + wc - 1) / wc;
@@ -354,11 +354,16 @@ size_t layout(const lqt_dims* d, lqt_call call, char* base, Work* w, int wc, lon
     if (w) w->vval[l] = a, w->tx[l] = b;
   };
   auto upper_stages = [&](const GTree& t, bool val, bool traj) {
-    nodes(2, t.m, val, traj);
+    if (t.up > 0) nodes(2, t.m, val, traj);
     for (int j = 0; j < t.up; ++j) {
-      // the last stage of a tree from fewer nodes may have more slots, up to a group
       const bool root = j + 1 == t.up;
-      slots(3 + 2 * j, root ? std::min((long)t.G, t.src[j]) : t.slot[j], val, traj);
+      if (!keep_maps && root && t.c[j] == 1) {
+        // one node a slot: the root has read its nodes before it writes its slots' records
+        if (w) w->vtup[3 + 2 * j] = w->vtup[2 + 2 * j], w->tmap[3 + 2 * j] = w->tmap[2 + 2 * j];
+        break;
+      }
+      // the last stage of a tree from fewer nodes (a larger wc) may have more slots, up to a group
+      slots(3 + 2 * j, root && keep_maps ? std::min((long)t.G, t.src[j]) : t.slot[j], val, traj);
       if (!root) nodes(4 + 2 * j, t.grp[j], val, traj);
     }
   };
@@ -381,7 +386,7 @@ size_t layout(const lqt_dims* d, lqt_call call, char* base, Work* w, int wc, lon
   if (use_wave(d) || tile) {
     const GTree t = !use_wave(d)                       ? tile_tree(d)
                     : call == LQT_CALL_FORWARD_TRAJ ? node_tree(d->nx, d->T, wc)
-                                                    : group_tree(d->nx, d->T, wc);
+                                                    : group_tree(d->nx, d->T, wc, keep_maps);
     if (want_v) slots(1, t.n1, want_v, want_t);
     if (call == LQT_CALL_SOLVE && !keep_maps) {
       void* a = take(es * B * d->nx * t.n1);
@@ -1003,8 +1008,9 @@ lqt_status run_solve(const lqt_dims* dims, const KProb& kp, const Work& w, void*
       LQT_HIP(wave_lti(kp, dims->dtype, w.lti, e, stream));
     else
       LQT_HIP(wave_build(kp, dims->dtype, e, stream));
-    LQT_HIP(wave_scans(kp, dims->dtype, group_tree(dims->nx, dims->T, o.wave_chunk), w, e, S, v, x, u,
-                       stream));
+    LQT_HIP(wave_scans(kp, dims->dtype,
+                       group_tree(dims->nx, dims->T, o.wave_chunk, w.bmap != nullptr), w, e, S, v, x,
+                       u, stream));
     return LQT_OK;
   }
   const Ops* op = lane_ops(dims->nx, dims->nu, dims->dtype);

@@ -296,8 +296,10 @@ struct GTree {
   int c[kMaxStages] = {};
   long src[kMaxStages] = {}, slot[kMaxStages] = {}, grp[kMaxStages] = {};
 };
-GTree group_tree(int nx, long T, int wc);   // from the blocks
-GTree node_tree(int nx, long T, int wc);    // from nodes of wc blocks, which no stage here forms
+// From the blocks.  shorten: fewer than wc blocks per slot where the horizon then still is one group,
+// for more slots at work; without (no room for block maps) the tree arrays stay a wc-th of the blocks.
+GTree group_tree(int nx, long T, int wc, bool shorten = true);
+GTree node_tree(int nx, long T, int wc);  // from nodes of wc blocks, which no stage here forms
 // Launchers of one wave-path instantiation (state size, dtype).
 struct WaveFns {
   hipError_t (*build)(const KProb&, void* elts, hipStream_t);

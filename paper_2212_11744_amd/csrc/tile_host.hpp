@@ -30,7 +30,7 @@ template <class B>
 constexpr int kGroupThreads = 64 * kGroupWaves<B>;
 
 // Arrays of the trees in the workspace (vtup, vval and tmap, tx): 1 sibling records of the bottom
-// stage's slots, 2 its groups, 3 + 2 j and 4 + 2 j those of upper stage j.
+// stage's slots, 2 its groups (if there are several), 3 + 2 j and 4 + 2 j those of upper stage j.
 //
 // Values at the right ends of the upper stages' nodes (vval[2]) from the nodes (vtup[2]).
 template <class B>
@@ -72,7 +72,7 @@ hipError_t launch_value(const KProb& kp, const GTree& t, const Work& w, const vo
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((kt_vbottom<B>), g0, b, 0, s, kp, s0, run, (const Mem*)elts,
                      (const Mem*)w.vtup[1], (const Mem*)w.vval[2], (Mem*)S, (Mem*)v,
-                     (Mem*)w.tmap[1], (Mem*)(maps ? w.tmap[2] : nullptr),
+                     (Mem*)(maps ? w.tmap[1] : nullptr), (Mem*)(maps ? w.tmap[2] : nullptr),
                      (Mem*)(maps ? w.bmap : nullptr));
   return hipGetLastError();
 }

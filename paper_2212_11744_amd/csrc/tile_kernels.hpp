@@ -472,7 +472,8 @@ TDEV void t_vspread(const Here<B>& h, const Stage& st, const typename B::Mem* sr
   }
 }
 
-// Reduction of a stage: the groups' products and their slots' sibling records.
+// Reduction of a stage: the groups' products and their slots' sibling records (of a single group the
+// records alone).
 template <class B>
 __global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_vup(const Stage st, int src_elts, int run,
                                                            const typename B::Mem* __restrict__ src,
@@ -488,8 +489,9 @@ __global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_vup(const Stage st,
     const Tup<B> acc = t_serial<B>(h, st, src_elts, src, scr);
     if (h.live) dump<B>(acc, ex[h.cnt - 1 - h.loc]);
   }
-  t_vup<B>(h, ex, sib + ((long)h.p * st.n_slot + g * kGroup<B>)*NE, false, scr);
-  if (h.w == 0)
+  const bool root = st.n_grp == 1;
+  t_vup<B>(h, ex, sib + ((long)h.p * st.n_slot + g * kGroup<B>)*NE, root, scr);
+  if (h.w == 0 && !root)
     tstore_t<B>(B::node() == 0, undump<B, false>(ex[0]), rec(grp, NE, (long)h.p * st.n_grp + g));
 }
 
@@ -760,8 +762,8 @@ __global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_tdown(
   t_tspread<B>(h, st, src, xs, x_out);
 }
 
-// The bottom stage down: values of every block, and with grp the group's map (msib: its slots'
-// sibling maps).
+// The bottom stage down: values of every block, and with msib the sibling maps of the slots and, of
+// several groups, each group's map (grp).
 template <class B>
 __global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_vbottom(
     const KProb kp, const Stage st, int run, const typename B::Mem* __restrict__ elts,
@@ -777,11 +779,12 @@ __global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_vbottom(
   typename B::R* scr = scr_all[h.w];
   t_vtop<B>(kp, h, st.n_grp == 1, val_in + ((long)h.p * st.n_grp + h.g) * kVR<B::N>, val);
   t_vdown<B>(h, val, sib + ((long)h.p * st.n_slot + g * kGroup<B>)*kNE<B::N>, scr);
-  const Map<B> acc = t_vbottom<B>(kp, h, st.c, elts, val, Sout, vout, bmaps, grp != nullptr, scr);
-  if (!grp) return;
+  const Map<B> acc = t_vbottom<B>(kp, h, st.c, elts, val, Sout, vout, bmaps, msib != nullptr, scr);
+  if (!msib) return;
   if (h.live) vdump<B>(acc.P, acc.q, val[h.loc]);
-  t_tup<B>(h, val, msib + ((long)h.p * st.n_slot + g * kGroup<B>)*VR, st.n_grp == 1);
-  if (h.w == 0) t_tgroup<B>(val, grp + ((long)h.p * st.n_grp + g) * VR);
+  const bool root = st.n_grp == 1;
+  t_tup<B>(h, val, msib + ((long)h.p * st.n_slot + g * kGroup<B>)*VR, root);
+  if (h.w == 0 && !root) t_tgroup<B>(val, grp + ((long)h.p * st.n_grp + g) * VR);
 }
 
 // x_k and u_k = -R^{-1} L(t_k)^T (S_k x_k - v_k) of every block of a slot, from the block maps the
