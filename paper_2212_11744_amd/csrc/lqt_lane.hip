@@ -1473,13 +1473,16 @@ __global__ __launch_bounds__(kThreads) void k_vswp(const KProb kp, const R* __re
 }
 
 // ------------------------------------------------------------------------------------------
-// Constant F and L, no drift, blocks of equal length up to rounding (|h_k - h| <= 2^-27 h, h their
-// mean): the time-invariant path to first order in h_k - h.  Two tables per problem: the response
-// at h, and the change of it per 2^-20 h from a second integration at h (1 + 2^-20); what the
-// second order leaves out is below 2^-54.  A problem with another grid is marked in bad (cleared
-// before) and takes the general build.
+// Constant F and L, no drift, blocks of equal length up to rounding (|h_k - h| <= 2^-29 h, h their
+// mean): the time-invariant path to first order in h_k - h.  Two tables per problem: the response f
+// at h, and the change of it per 2^-20 h, half the difference of the responses at h (1 + 2^-20) and
+// h (1 - 2^-20).  Of an entry that goes as h^m, delta = (h_k - h) / h: the second order leaves out
+// delta^2 m (m - 1) / 2 and the difference quotient delta 2^-40 m (m - 1)(m - 2) / 6 of it, below
+// 2^-53 for m <= 7 (C of four integrators in a row) and below m 2^-53, what the rounding of h_k does
+// to it, for m <= 64.  (A one-sided quotient would leave out delta 2^-20 m (m - 1) / 2.)  A problem
+// with another grid is marked in bad (cleared before) and takes the general build.
 // ------------------------------------------------------------------------------------------
-constexpr double kUniTol = 0x1p-27, kUniStep = 0x1p-20;
+constexpr double kUniTol = 0x1p-29, kUniStep = 0x1p-20;
 
 template <int N, int NU, class R>
 __global__ __launch_bounds__(kThreads) void k_uni_prep(const KProb kp, R* __restrict__ tab,
@@ -1504,18 +1507,19 @@ __global__ __launch_bounds__(kThreads) void k_uni_prep(const KProb kp, R* __rest
     return;
   }
   const int n = kp.n;
-  const long M = (2L * n + 1) * N, m = min(gid() >> 1, M - 1);
-  const bool second = gid() & 1;
+  // four lanes per impulse: the responses at h, h (1 + 2^-20), h (1 - 2^-20), and h again
+  const long M = (2L * n + 1) * N, m = min(gid() >> 2, M - 1);
+  const int part = gid() & 3;
   const long j0 = m / N;
   const int i0 = (int)(m % N);
-  const R h = second ? h0 * R(1 + kUniStep) : h0;
+  const R h = part == 1 ? h0 * R(1 + kUniStep) : part == 2 ? h0 * R(1 - kUniStep) : h0;
   Tup<N, R> out;
   const Blk bk{p, 0, 0, (long)p * (T + 1)};
   build_block_rs<N, NU, R, true>(kp, bk, RImpulse<R>{j0, i0, h / R(n)}, out, n);
-  R* tp = tab + ((long)p * 2 + second) * lti_count(N, n);
+  R* tp = tab + ((long)p * 2 + (part == 1)) * lti_count(N, n);
   auto put = [&](long q, R x, bool on) {
-    const R first = __shfl_xor(x, 1, 64);
-    if (on) tp[q] = second ? x - first : x;
+    const R below = __shfl_xor(x, 3, 64);
+    if (on && part < 2) tp[q] = part == 1 ? R(0.5) * (x - below) : x;
   };
 #pragma unroll
   for (int a = 0; a < N; ++a) {
@@ -2363,7 +2367,7 @@ struct L {
     return hipGetLastError();
   }
   static hipError_t uni_prep(const KProb& kp, void* tab, unsigned* bad, hipStream_t s) {
-    const int pb = (int)((2 * (2L * kp.n + 1) * N + kThreads - 1) / kThreads);
+    const int pb = (int)((4 * (2L * kp.n + 1) * N + kThreads - 1) / kThreads);
     // four block lengths a lane: the check ends before the tables do
     const int check = (int)((kp.T + 4L * kThreads - 1) / (4 * kThreads));
     hipLaunchKernelGGL((k_uni_prep<N, NU, R>), dim3((unsigned)(pb + check), kp.batch),

@@ -1,0 +1,39 @@
+"""Elements of a solve over nearly even grids (constant F and L, beyond 2^19 blocks in FP64), where they
+come from tables to first order in the blocks' lengths as long as those are even to 2^-29, against
+lqt_build_elements, which integrates every block.
+
+The grids are stretched smoothly by `amp` of a block's length: on both sides of the limit, and at 0.8 of
+2^-27.  Every entry of the elements has to agree to 32 eps of its largest value over the horizon: each
+build rounds some ten operations per entry and step, and the tables leave out less than an eps.
+Without the first order the entries would be off by 1 to 7 times amp."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2212_11744_amd import lqt
+from paper_2212_11744_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _grid(T, amp, phase):
+    k = np.arange(T)
+    h = (10.0 / T) * (1.0 + amp * np.sin(2 * np.pi * k / T + phase))
+    return np.concatenate([[0.0], np.cumsum(h.astype(np.longdouble))]).astype(np.float64)
+
+
+@pytest.mark.parametrize("T,n,batch", [(524289, 1, 1), (524289, 5, 1), (262147, 2, 2)])
+@pytest.mark.parametrize("amp", [1.5e-9, 2.2e-9, 6e-9])
+def test_elements_of_nearly_even_grids(T, n, batch, amp):
+    ps = [W.point_mass(3 + b, T, n, t_grid=_grid(T, amp, b)) for b in range(batch)]
+    dp = lqt.DeviceProblem.from_problems(ps)
+    ref = lqt.build_elements(dp)
+    got = lqt.solve(dp, keep_elements=True)["elts"]
+    k = torch.arange(T, device="cuda")
+    tile, col = k // 512, 64 * (k % 8) + (k % 512) // 8
+    eps = torch.finfo(torch.float64).eps
+    for b in range(batch):
+        for q in range(lqt.element_count(4)):
+            r, g = ref[b][tile, q, col], got[b][tile, q, col]
+            e = float((g - r).abs().max())
+            assert e <= 32 * eps * float(r.abs().max()), f"problem {b} value {q}: {e:.3e}"
