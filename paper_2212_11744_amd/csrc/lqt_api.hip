@@ -290,13 +290,13 @@ bool use_split_scan(const lqt_dims* d) {
 }
 
 // The check of the grid and the first-order tables instead of the general build (k_uni_prep,
-// k_lti_red).  Check and tables take 20 us and the launches that find nothing to do 9, whatever T; at
-// T = 2^20, n = 4 they replace 441 us of build and reduction by 208 (solve 753 -> 595 us), and a grid of
-// uneven blocks pays 805 (the single pass: 787).  Below 2^19 blocks such a grid would lose more: 271 vs
-// 250 at 2^18, where the even one gains 250 -> 204.  FP32 block lengths are too coarse for it.
+// k_lti_red), for calls of more than 2^19 blocks.  The tables cost 4 (2 n + 1) nx block integrations per
+// problem, the build they replace T: they have to be at most a sixteenth of it, or a batch of short
+// problems would integrate as much as it saves (T = 600, n = 75: 2416 blocks in place of 600).  FP32
+// block lengths are too coarse for it.
 bool use_uniform(const lqt_dims* d) {
   return !d->lti && !d->F_sampled && !d->L_sampled && !d->has_c && d->dtype == LQT_F64 &&
-         (long)d->T * d->batch > 1L << 19;
+         (long)d->T * d->batch > 1L << 19 && d->T >= 16 * 4 * (2L * d->n_steps + 1) * d->nx;
 }
 
 }  // namespace
