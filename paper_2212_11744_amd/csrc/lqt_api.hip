@@ -292,8 +292,11 @@ bool use_split_scan(const lqt_dims* d) {
 // The check of the grid and the first-order tables instead of the general build (k_uni_prep,
 // k_lti_red), for calls of more than 2^19 blocks.  The tables cost 4 (2 n + 1) nx block integrations per
 // problem, the build they replace T: they have to be at most a sixteenth of it, or a batch of short
-// problems would integrate as much as it saves (T = 600, n = 75: 2416 blocks in place of 600).  FP32
-// block lengths are too coarse for it.
+// problems would integrate as much as it saves (T = 600, n = 75: 2416 blocks in place of 600).
+// Solves of one problem (us; even, uneven, uneven by one block that the probes miss; the general
+// build and the single-pass scan): T = 2^20, n = 4: 599, 752, 770; 778.  n = 10: 759, 1094, 1129; 1130.
+// T = 2^19 + 1, n = 4: 329, 400, 419; 430: below, a grid of the third kind would lose.  FP32 block
+// lengths are too coarse for it.
 bool use_uniform(const lqt_dims* d) {
   return !d->lti && !d->F_sampled && !d->L_sampled && !d->has_c && d->dtype == LQT_F64 &&
          (long)d->T * d->batch > 1L << 19 && d->T >= 16 * 4 * (2L * d->n_steps + 1) * d->nx;

@@ -1483,6 +1483,7 @@ __global__ __launch_bounds__(kThreads) void k_vswp(const KProb kp, const R* __re
 // with another grid is marked in bad (cleared before) and takes the general build.
 // ------------------------------------------------------------------------------------------
 constexpr double kUniTol = 0x1p-29, kUniStep = 0x1p-20;
+constexpr int kUniProbes = 4;  // blocks a lane looks at before the tables
 
 template <int N, int NU, class R>
 __global__ __launch_bounds__(kThreads) void k_uni_prep(const KProb kp, R* __restrict__ tab,
@@ -1504,6 +1505,18 @@ __global__ __launch_bounds__(kThreads) void k_uni_prep(const KProb kp, R* __rest
 #pragma unroll
     for (int q = 0; q < 4; ++q) ok = ok && fabs(h[q] - h0) <= h0 * R(kUniTol);
     if (__ballot(!ok) != 0ull && threadIdx.x == 0) bad[p] = 1u;
+    return;
+  }
+  // blocks spread over the horizon first, the same for every wave: all but the rarest uneven grids show
+  // here (one odd block among T moves the mean, and so all others), and their tables are left out
+  bool even = true;
+#pragma unroll
+  for (int q = 0; q < kUniProbes; ++q) {
+    const long k = (q * kThreads + threadIdx.x) * (T - 1) / (kUniProbes * kThreads - 1);
+    even = even && fabs((t[k + 1] - t[k]) - h0) <= h0 * R(kUniTol);
+  }
+  if (__ballot(!even) != 0ull) {
+    if (threadIdx.x == 0) bad[p] = 1u;
     return;
   }
   const int n = kp.n;
@@ -1592,23 +1605,22 @@ __global__ __launch_bounds__(kThreads) void k_lti_red(const KProb kp, const R* _
   tup_store_rec<PlainAcc>(E, part + (long)p * Lay<N>::NE * G * 64, G * 64, tile * 64 + lane);
 }
 
-// The general build of the problems marked bad, on as many waves as are resident at once: with no
-// problem marked it ends as soon as they have started.
+// The general build of the problems marked bad, one item per lane as in k_build.  (A loop over items on
+// the resident waves was slower, 80 scalar registers instead of 112: constants that are uniform over
+// a wave were vector loads again after its first store.  Uneven T = 2^20, n = 4 / 10: solve 773 /
+// 1166 us, so 752 / 1093; with nothing to do it ends 1.4 us later.)
 template <int N, int NU, class R>
 __global__ __launch_bounds__(kThreads) void k_build_rest(const KProb kp,
                                                           const unsigned* __restrict__ bad,
                                                           R* __restrict__ elts) {
   const int p = blockIdx.y;
   if (!bad[p]) return;
-  const long T = kp.T, nb = padt(T) / kThreads;
-#pragma unroll 1
-  for (long b = nb - 1 - blockIdx.x; b >= 0; b -= gridDim.x) {
-    const long k = tile_row_item(b * kThreads + threadIdx.x);
-    if (k >= T) continue;
-    Tup<N, R> out;
-    build_block<N, NU, R, true>(kp, blk_plain(kp, p, k), out);
-    tup_store(out, elts + (long)p * Lay<N>::NE * padt(T), k);
-  }
+  const long T = kp.T;
+  const long k = build_item(T, true);
+  if (k >= T) return;
+  Tup<N, R> out;
+  build_block<N, NU, R, true>(kp, blk_plain(kp, p, k), out);
+  tup_store(out, elts + (long)p * Lay<N>::NE * padt(T), k);
 }
 
 // Trajectory (Method 1 of Sec. IV-E with the exact block maps, control law of Sec. II-B): the
@@ -2375,9 +2387,8 @@ struct L {
     return hipGetLastError();
   }
   static hipError_t build_rest(const KProb& kp, const unsigned* bad, void* elts, hipStream_t s) {
-    const long nb = padt(kp.T) / kThreads;
-    hipLaunchKernelGGL((k_build_rest<N, NU, R>), dim3((unsigned)(nb < 1024 ? nb : 1024), kp.batch),
-                       dim3(kThreads), 0, s, kp, bad, (R*)elts);
+    hipLaunchKernelGGL((k_build_rest<N, NU, R>), grid_tile_rows(kp.T, kp.batch), dim3(kThreads), 0, s,
+                       kp, bad, (R*)elts);
     return hipGetLastError();
   }
   template <int CH>

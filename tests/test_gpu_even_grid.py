@@ -22,18 +22,44 @@ def _grid(T, amp, phase):
     return np.concatenate([[0.0], np.cumsum(h.astype(np.longdouble))]).astype(np.float64)
 
 
-@pytest.mark.parametrize("T,n,batch", [(524289, 1, 1), (524289, 5, 1), (262147, 2, 2)])
-@pytest.mark.parametrize("amp", [1.5e-9, 2.2e-9, 6e-9])
-def test_elements_of_nearly_even_grids(T, n, batch, amp):
-    ps = [W.point_mass(3 + b, T, n, t_grid=_grid(T, amp, b)) for b in range(batch)]
+def _compare_elements(ps):
     dp = lqt.DeviceProblem.from_problems(ps)
     ref = lqt.build_elements(dp)
     got = lqt.solve(dp, keep_elements=True)["elts"]
-    k = torch.arange(T, device="cuda")
+    k = torch.arange(dp.T, device="cuda")
     tile, col = k // 512, 64 * (k % 8) + (k % 512) // 8
     eps = torch.finfo(torch.float64).eps
-    for b in range(batch):
+    for b in range(dp.batch):
         for q in range(lqt.element_count(4)):
             r, g = ref[b][tile, q, col], got[b][tile, q, col]
             e = float((g - r).abs().max())
             assert e <= 32 * eps * float(r.abs().max()), f"problem {b} value {q}: {e:.3e}"
+
+
+@pytest.mark.parametrize("T,n,batch", [(524289, 1, 1), (524289, 5, 1), (262147, 2, 2)])
+@pytest.mark.parametrize("amp", [1.5e-9, 2.2e-9, 6e-9])
+def test_elements_of_nearly_even_grids(T, n, batch, amp):
+    ps = [W.point_mass(3 + b, T, n, t_grid=_grid(T, amp, b)) for b in range(batch)]
+    _compare_elements(ps)
+
+
+def _uneven(T, kind):
+    h = np.full(T, 10.0 / T)
+    if kind == "all":
+        h *= 1.0 + 0.3 * np.sin(np.arange(T))
+    elif kind == "two lengths":
+        h[T // 3:] *= 1.01
+    elif kind == "last":
+        h[-1] *= 0.5
+    elif kind.startswith("block"):  # one block, by 1e-6 of its length, which the mean hides
+        h[int(kind.split()[1])] *= 1.0 + 1e-6
+    return np.concatenate([[0.0], np.cumsum(h.astype(np.longdouble))]).astype(np.float64)
+
+
+@pytest.mark.parametrize("T,kinds", [
+    (524289, ["all"]), (524289, ["two lengths"]), (524289, ["last"]), (524289, ["block 0"]),
+    (524289, ["block 524288"]), (524289, ["block 777"]), (262147, ["none", "block 1000"]),
+    (262147, ["all", "none"])])
+def test_elements_of_uneven_grids(T, kinds):
+    """Problem by problem: marked at once by the spread blocks, or by the check of every block."""
+    _compare_elements([W.point_mass(3 + b, T, 2, t_grid=_uneven(T, kd)) for b, kd in enumerate(kinds)])
