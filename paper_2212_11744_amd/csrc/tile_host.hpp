@@ -10,9 +10,9 @@ namespace tile {
 template <class B>
 hipError_t launch_build(const KProb& kp, void* elts, hipStream_t s) {
   using Mem = typename B::Mem;
-  // waves 8 g + r take the blocks 8 B::NODES g + 8 s + r
-  const unsigned groups = (unsigned)((kp.T + 8L * B::NODES - 1) / (8L * B::NODES));
-  const dim3 g(8 * groups, kp.batch);
+  // waves 8 g + r take the blocks 8 B::NODES g + 8 s + r; none without a block
+  const long whole = kp.T / (8L * B::NODES), rest = kp.T % (8L * B::NODES);
+  const dim3 g((unsigned)(8 * whole + (rest < 8 ? rest : 8)), kp.batch);
   if (!kp.F_sampled && !kp.L_sampled && !kp.has_c)
     hipLaunchKernelGGL((kt_build<B, true>), g, dim3(64), 0, s, kp, (Mem*)elts);
   else
@@ -40,7 +40,7 @@ hipError_t launch_value_tree(const KProb& kp, const GTree& t, const Work& w, hip
   const int nb = kp.batch;
   const dim3 b(kGroupThreads<B>);
   for (int j = 0; j + 1 < t.up; ++j)
-    hipLaunchKernelGGL((kt_vup<B>), dim3((unsigned)t.grp[j], nb), b, 0, s, upper(t, j), 0, 1,
+    hipLaunchKernelGGL((kt_vup<B>), dim3((unsigned)(t.grp[j] * nb)), b, 0, s, upper(t, j), 0, nb, 1,
                        (const Mem*)w.vtup[2 + 2 * j], (Mem*)w.vtup[3 + 2 * j],
                        (Mem*)w.vtup[4 + 2 * j]);
   for (int j = t.up - 1; j >= 0; --j) {
@@ -63,14 +63,15 @@ hipError_t launch_value(const KProb& kp, const GTree& t, const Work& w, const vo
                         void* v, bool maps, hipStream_t s) {
   using Mem = typename B::Mem;
   if (t.G != kGroup<B>) return hipErrorInvalidValue;
-  const int nb = kp.batch, run = bottom_run<B>(t.wc);
-  const dim3 b(kGroupThreads<B>), g0(spread_grid(t.m, run), nb);
+  const int nb = kp.batch;
+  const SpreadGrid g0(t.m * nb, bottom_run<B>(t.wc));
+  const dim3 b(kGroupThreads<B>);
   const Stage s0 = bottom<B>(t);
-  hipLaunchKernelGGL((kt_vup<B>), g0, b, 0, s, s0, 1, run, (const Mem*)elts, (Mem*)w.vtup[1],
-                     (Mem*)w.vtup[2]);
+  hipLaunchKernelGGL((kt_vup<B>), dim3(g0.grid), b, 0, s, s0, 1, nb, g0.run, (const Mem*)elts,
+                     (Mem*)w.vtup[1], (Mem*)w.vtup[2]);
   const hipError_t e = launch_value_tree<B>(kp, t, w, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((kt_vbottom<B>), g0, b, 0, s, kp, s0, run, (const Mem*)elts,
+  hipLaunchKernelGGL((kt_vbottom<B>), dim3(g0.grid), b, 0, s, kp, s0, g0.run, (const Mem*)elts,
                      (const Mem*)w.vtup[1], (const Mem*)w.vval[2], (Mem*)S, (Mem*)v,
                      (Mem*)(maps ? w.tmap[1] : nullptr), (Mem*)(maps ? w.tmap[2] : nullptr),
                      (Mem*)(maps ? w.bmap : nullptr));

@@ -33,16 +33,18 @@ TDEV Ref<R> elt_ref(R* elts, int p, long k, long T) {
   return {elts + ((p * nt + k / kEltT) * kNE<N>)*kEltT + ((k & 7) << 6) + ((k & 511) >> 3), kEltT};
 }
 
-// Workgroups of one launch are dealt to the eight XCDs in turn (workgroup w to XCD w % 8), each with
-// its own L2.  Workgroup w takes group `spread(w, run)`: runs of `run` consecutive groups, whose
-// element columns share 128-byte lines, go to one XCD.  The grid is a multiple of 8 run.
-TDEV long spread(long w, int run) {
-  const long blk = 8L * run;
-  return (w / blk) * blk + (w % 8) * run + (w % blk) / 8;
-}
-inline unsigned spread_grid(long groups, int run) {
-  return (unsigned)((groups + 8L * run - 1) / (8L * run) * (8L * run));
-}
+// Problem and group of a workgroup of a launch over the groups of all problems (tree_pairs.hpp).
+struct Place {
+  int p;
+  long g;
+  bool live;
+  TDEV Place(long n_grp, int batch, int run) {
+    const unsigned w = (unsigned)(run > 1 ? spread(blockIdx.x, run) : (long)blockIdx.x);
+    p = (int)(w / (unsigned)n_grp);
+    g = w - (unsigned)p * (unsigned)n_grp;
+    live = p < batch;
+  }
+};
 // Waves and slots of a group, and the run length of the bottom stage: 16 (FP64) or 32 (FP32)
 // element columns to a line, a column per 8 blocks, wc blocks per slot.
 // One wave a SIMD (the steps of a group are serial, and two waves of matrix instructions on a SIMD
@@ -475,15 +477,17 @@ TDEV void t_vspread(const Here<B>& h, const Stage& st, const typename B::Mem* sr
 // Reduction of a stage: the groups' products and their slots' sibling records (of a single group the
 // records alone).
 template <class B>
-__global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_vup(const Stage st, int src_elts, int run,
+__global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_vup(const Stage st, int src_elts, int batch,
+                                                           int run,
                                                            const typename B::Mem* __restrict__ src,
                                                            typename B::Mem* __restrict__ sib,
                                                            typename B::Mem* __restrict__ grp) {
   constexpr int NE = kNE<B::N>;
   __shared__ typename B::R ex[kGroup<B>][kDumpT<B>], scr_all[kGroupWaves<B>][kInvScr<B>];
-  const long g = run > 1 ? spread(blockIdx.x, run) : (long)blockIdx.x;
-  if (g >= st.n_grp) return;
-  const Here<B> h(st, g, blockIdx.y);
+  const Place at(st.n_grp, batch, run);
+  if (!at.live) return;
+  const long g = at.g;
+  const Here<B> h(st, g, at.p);
   typename B::R* scr = scr_all[h.w];
   if (h.w * B::NODES < h.cnt) {
     const Tup<B> acc = t_serial<B>(h, st, src_elts, src, scr);
@@ -773,9 +777,10 @@ __global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_vbottom(
     typename B::Mem* __restrict__ bmaps) {
   constexpr int VR = kVR<B::N>;
   __shared__ typename B::R val[kGroup<B>][kDumpV<B>], scr_all[kGroupWaves<B>][kInvScr<B>];
-  const long g = run > 1 ? spread(blockIdx.x, run) : (long)blockIdx.x;
-  if (g >= st.n_grp) return;
-  const Here<B> h(st, g, blockIdx.y);
+  const Place at(st.n_grp, kp.batch, run);
+  if (!at.live) return;
+  const long g = at.g;
+  const Here<B> h(st, g, at.p);
   typename B::R* scr = scr_all[h.w];
   t_vtop<B>(kp, h, st.n_grp == 1, val_in + ((long)h.p * st.n_grp + h.g) * kVR<B::N>, val);
   t_vdown<B>(h, val, sib + ((long)h.p * st.n_slot + g * kGroup<B>)*kNE<B::N>, scr);
