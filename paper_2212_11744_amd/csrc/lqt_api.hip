@@ -127,8 +127,8 @@ void upper_stages(GTree& t) {
 GTree group_tree(int nx, long T, int wc, bool shorten) {
   GTree t;
   t.G = group_slots(nx);
-  // a horizon of one group: as few blocks in a row as that allows
-  while (shorten && wc > 1 && T <= wc / 2 * t.G) wc /= 2;
+  // a horizon of one group (one slot): as few blocks in a row as that allows
+  while (wc > 1 && T <= wc / 2 * (shorten ? t.G : 1)) wc /= 2;
   t.wc = wc;
   t.T = T;
   t.n1 = (T + wc - 1) / wc;
@@ -244,6 +244,14 @@ bool use_wave(const lqt_dims* d) { return lane_ops(d->nx, d->nu, d->dtype) == nu
 // wave than its workspace was laid out for: the level-1 tree arrays hold ceil(T / chunk) records.
 constexpr int kWaveChunk = 4;
 
+// Tree of the wave path's scans.  A horizon of one group gets more, shorter slots while every problem has
+// a CU of its own; more problems than that are bound by their steps, which the rounds over the slots
+// add to (1024 problems of 4 blocks at nx = 16: value scan 202 us with slots of one block, 91 with 4).
+constexpr long kCUs = 256;
+GTree wave_group_tree(const lqt_dims* d, int wc, bool maps) {
+  return group_tree(d->nx, d->T, wc, maps && d->batch <= kCUs);
+}
+
 WTree wtree_for(const lqt_dims* d) { return wave_tree(d->T, kWaveChunk); }
 
 // Where the small sizes take the kernels of lqt_tile.hip: four lanes times four to a block or node
@@ -252,22 +260,24 @@ WTree wtree_for(const lqt_dims* d) { return wave_tree(d->T, kWaveChunk); }
 // 21 at 32000, 37 vs 23 at 2^16 (n = 10: 6.5 vs 38 at 64, 22 vs 41 at 16000); nx = 4 FP32 7.0 vs
 // 14.6 at 8000, 20 vs 16 at 32000; nx = 3 8.6 vs 12.4 at 8000, 14 vs 13 at 16000; nx = 2 4.7 vs 4.3
 // at 64 and slower beyond.
+// Those limits are waves' worth: from the fifth block on a problem takes waves that it does not fill
+// (batch 248, T = 33, nx = 3: 2232 waves against 248; solve 34.3 vs 33.0).
 bool use_tile_build(const lqt_dims* d) {
   if (use_wave(d) || d->nx < 3) return false;
+  const long limit = d->nx == 4 && d->dtype == LQT_F64 ? 1L << 15 : 1L << 13;
   const long blocks = (long)d->T * d->batch;
-  return blocks <= (d->nx == 4 && d->dtype == LQT_F64 ? 1L << 15 : 1L << 13);
+  return blocks <= limit && (d->T <= 4 || 4 * tile_build_waves(d->T) * d->batch <= limit);
 }
 // Scans, nx = 4 FP64, as long as every group has a CU of its own.  Against the single-pass scans of
 // the per-lane path, in a solve (us): 27 vs 76 at T = 64 and n = 10, 98 vs 131 at T = 2^16, the most
 // that 256 groups take.  FP32 (whose per-lane arithmetic is four times as fast) and nx <= 3
 // (smaller systems, the same number of steps) are at best even: 23 vs 27 in FP32 at T = 64, 23 vs
 // 23 at nx = 3, 73 vs 50 at nx = 3 and T = 16000.
-constexpr long kTileGroups = 256;
 constexpr int kTileChunk = 8;  // blocks per slot
 GTree tile_tree(const lqt_dims* d) { return group_tree(d->nx, d->T, kTileChunk); }
 bool use_tile_scans(const lqt_dims* d) {
   return !use_wave(d) && d->nx == 4 && d->dtype == LQT_F64 &&
-         tile_tree(d).m * d->batch <= kTileGroups;
+         tile_tree(d).m * d->batch <= kCUs;
 }
 
 // The value scan of the per-lane path in three launches (k_vred, the tree over its tiles, k_vswp)
@@ -389,7 +399,7 @@ size_t layout(const lqt_dims* d, lqt_call call, char* base, Work* w, int wc, lon
   if (use_wave(d) || tile) {
     const GTree t = !use_wave(d)                       ? tile_tree(d)
                     : call == LQT_CALL_FORWARD_TRAJ ? node_tree(d->nx, d->T, wc)
-                                                    : group_tree(d->nx, d->T, wc, keep_maps);
+                                                    : wave_group_tree(d, wc, keep_maps);
     if (want_v) slots(1, t.n1, want_v, want_t);
     if (call == LQT_CALL_SOLVE && !keep_maps) {
       void* a = take(es * B * d->nx * t.n1);
@@ -951,8 +961,7 @@ lqt_status lqt_scan_value(const lqt_dims* dims, const void* elts, const void* Qf
   p.rf = rf;
   KProb kp = make_kprob(dims, &p, w.consts);
   if (use_wave(dims)) {
-    LQT_HIP(wave_value(kp, dims->dtype, group_tree(dims->nx, dims->T, kWaveChunk), w, elts, S, v,
-                       stream));
+    LQT_HIP(wave_value(kp, dims->dtype, wave_group_tree(dims, kWaveChunk, true), w, elts, S, v, stream));
   } else {
     const Ops* o = lane_ops(dims->nx, dims->nu, dims->dtype);
     if (use_tile_scans(dims))
@@ -1011,9 +1020,8 @@ lqt_status run_solve(const lqt_dims* dims, const KProb& kp, const Work& w, void*
       LQT_HIP(wave_lti(kp, dims->dtype, w.lti, e, stream));
     else
       LQT_HIP(wave_build(kp, dims->dtype, e, stream));
-    LQT_HIP(wave_scans(kp, dims->dtype,
-                       group_tree(dims->nx, dims->T, o.wave_chunk, w.bmap != nullptr), w, e, S, v, x,
-                       u, stream));
+    LQT_HIP(wave_scans(kp, dims->dtype, wave_group_tree(dims, o.wave_chunk, w.bmap != nullptr), w, e, S,
+                       v, x, u, stream));
     return LQT_OK;
   }
   const Ops* op = lane_ops(dims->nx, dims->nu, dims->dtype);

@@ -340,6 +340,13 @@ hipError_t wave_traj(const KProb& kp, int dtype, const GTree& t, const Work& w, 
 hipError_t wave_scans(const KProb& kp, int dtype, const GTree& t, const Work& w, const void* elts,
                       void* S, void* v, void* x, void* u, hipStream_t s);
 
+// Waves per problem of the element build of tile_kernels.hpp, `nodes` blocks each: waves 8 g + r take the blocks 8 nodes g + 8 s + r
+// (fewer than 8 nodes blocks: in order), and there is none without a block.
+inline long tile_build_waves(long T, int nodes = 4) {
+  const long whole = T / (8L * nodes), rest = T % (8L * nodes);
+  return 8 * whole + (whole == 0 ? (rest + nodes - 1) / nodes : rest < 8 ? rest : 8);
+}
+
 // Short horizons of the small sizes on the kernels of tile_kernels.hpp (lqt_tile.hip): the element
 // build at nx = 3, 4, and in FP64 at nx = 4 the value scan alone and both scans (block maps in w.bmap);
 // and for every nx <= 4 the value tree over given nodes (w.vtup[2] -> w.vval[2]).

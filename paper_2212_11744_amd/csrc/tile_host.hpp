@@ -10,9 +10,7 @@ namespace tile {
 template <class B>
 hipError_t launch_build(const KProb& kp, void* elts, hipStream_t s) {
   using Mem = typename B::Mem;
-  // waves 8 g + r take the blocks 8 B::NODES g + 8 s + r; none without a block
-  const long whole = kp.T / (8L * B::NODES), rest = kp.T % (8L * B::NODES);
-  const dim3 g((unsigned)(8 * whole + (rest < 8 ? rest : 8)), kp.batch);
+  const dim3 g((unsigned)tile_build_waves(kp.T, B::NODES), kp.batch);
   if (!kp.F_sampled && !kp.L_sampled && !kp.has_c)
     hipLaunchKernelGGL((kt_build<B, true>), g, dim3(64), 0, s, kp, (Mem*)elts);
   else
@@ -26,8 +24,18 @@ template <class B>
 Stage bottom(const GTree& t) {
   return stage(t.wc, t.T, t.n1, t.m);
 }
+// Threads of a stage's workgroups, and their LDS with a dump of DUMP values per slot (and the scratch
+// of the pivoted inverse).
 template <class B>
-constexpr int kGroupThreads = 64 * kGroupWaves<B>;
+dim3 threads(const Stage& st) {
+  const long slots = st.n_grp == 1 ? st.n_slot : kGroup<B>;
+  return dim3((unsigned)(64 * ((slots + B::NODES - 1) / B::NODES)));
+}
+template <class B, int DUMP, bool SCR = true>
+unsigned lds(const Stage& st) {
+  const unsigned waves = threads<B>(st).x / 64;
+  return (unsigned)sizeof(typename B::R) * waves * (B::NODES * DUMP + (SCR ? kInvScr<B> : 0));
+}
 
 // Arrays of the trees in the workspace (vtup, vval and tmap, tx): 1 sibling records of the bottom
 // stage's slots, 2 its groups (if there are several), 3 + 2 j and 4 + 2 j those of upper stage j.
@@ -38,20 +46,23 @@ hipError_t launch_value_tree(const KProb& kp, const GTree& t, const Work& w, hip
   using Mem = typename B::Mem;
   if (t.G != kGroup<B>) return hipErrorInvalidValue;
   const int nb = kp.batch;
-  const dim3 b(kGroupThreads<B>);
-  for (int j = 0; j + 1 < t.up; ++j)
-    hipLaunchKernelGGL((kt_vup<B>), dim3((unsigned)(t.grp[j] * nb)), b, 0, s, upper(t, j), 0, nb, 1,
-                       (const Mem*)w.vtup[2 + 2 * j], (Mem*)w.vtup[3 + 2 * j],
-                       (Mem*)w.vtup[4 + 2 * j]);
+  for (int j = 0; j + 1 < t.up; ++j) {
+    const Stage st = upper(t, j);
+    hipLaunchKernelGGL((kt_vup<B>), dim3((unsigned)(t.grp[j] * nb)), threads<B>(st),
+                       (lds<B, kDumpT<B>>(st)), s, st, 0, nb, 1, (const Mem*)w.vtup[2 + 2 * j],
+                       (Mem*)w.vtup[3 + 2 * j], (Mem*)w.vtup[4 + 2 * j]);
+  }
   for (int j = t.up - 1; j >= 0; --j) {
+    const Stage st = upper(t, j);
     if (j == t.up - 1)
-      hipLaunchKernelGGL((kt_vroot<B>), dim3(1, nb), b, 0, s, kp, upper(t, j),
-                         (const Mem*)w.vtup[2 + 2 * j], (Mem*)w.vtup[3 + 2 * j],
+      hipLaunchKernelGGL((kt_vroot<B>), dim3(1, nb), threads<B>(st), (lds<B, kDumpT<B>>(st)), s, kp,
+                         st, (const Mem*)w.vtup[2 + 2 * j], (Mem*)w.vtup[3 + 2 * j],
                          (Mem*)w.vval[2 + 2 * j]);
     else
-      hipLaunchKernelGGL((kt_vdown<B>), dim3((unsigned)t.grp[j], nb), b, 0, s, kp, upper(t, j),
-                         (const Mem*)w.vtup[2 + 2 * j], (const Mem*)w.vtup[3 + 2 * j],
-                         (const Mem*)w.vval[4 + 2 * j], (Mem*)w.vval[2 + 2 * j]);
+      hipLaunchKernelGGL((kt_vdown<B>), dim3((unsigned)t.grp[j], nb), threads<B>(st),
+                         (lds<B, kDumpV<B>>(st)), s, kp, st, (const Mem*)w.vtup[2 + 2 * j],
+                         (const Mem*)w.vtup[3 + 2 * j], (const Mem*)w.vval[4 + 2 * j],
+                         (Mem*)w.vval[2 + 2 * j]);
   }
   return hipGetLastError();
 }
@@ -65,16 +76,16 @@ hipError_t launch_value(const KProb& kp, const GTree& t, const Work& w, const vo
   if (t.G != kGroup<B>) return hipErrorInvalidValue;
   const int nb = kp.batch;
   const SpreadGrid g0(t.m * nb, bottom_run<B>(t.wc));
-  const dim3 b(kGroupThreads<B>);
   const Stage s0 = bottom<B>(t);
-  hipLaunchKernelGGL((kt_vup<B>), dim3(g0.grid), b, 0, s, s0, 1, nb, g0.run, (const Mem*)elts,
-                     (Mem*)w.vtup[1], (Mem*)w.vtup[2]);
+  if (t.n1 > 1)  // a single slot has no siblings
+    hipLaunchKernelGGL((kt_vup<B>), dim3(g0.grid), threads<B>(s0), (lds<B, kDumpT<B>>(s0)), s, s0, 1,
+                       nb, g0.run, (const Mem*)elts, (Mem*)w.vtup[1], (Mem*)w.vtup[2]);
   const hipError_t e = launch_value_tree<B>(kp, t, w, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((kt_vbottom<B>), dim3(g0.grid), b, 0, s, kp, s0, g0.run, (const Mem*)elts,
-                     (const Mem*)w.vtup[1], (const Mem*)w.vval[2], (Mem*)S, (Mem*)v,
-                     (Mem*)(maps ? w.tmap[1] : nullptr), (Mem*)(maps ? w.tmap[2] : nullptr),
-                     (Mem*)(maps ? w.bmap : nullptr));
+  hipLaunchKernelGGL((kt_vbottom<B>), dim3(g0.grid), threads<B>(s0), (lds<B, kDumpV<B>>(s0)), s, kp, s0,
+                     g0.run, (const Mem*)elts, (const Mem*)w.vtup[1], (const Mem*)w.vval[2], (Mem*)S,
+                     (Mem*)v, (Mem*)(maps ? w.tmap[1] : nullptr),
+                     (Mem*)(maps ? w.tmap[2] : nullptr), (Mem*)(maps ? w.bmap : nullptr));
   return hipGetLastError();
 }
 
@@ -84,20 +95,24 @@ hipError_t launch_traj_tree(const KProb& kp, const GTree& t, const Work& w, hipS
   using Mem = typename B::Mem;
   if (t.G != kGroup<B>) return hipErrorInvalidValue;
   const int nb = kp.batch;
-  const dim3 b(kGroupThreads<B>);
-  for (int j = 0; j + 1 < t.up; ++j)
-    hipLaunchKernelGGL((kt_tup<B>), dim3((unsigned)t.grp[j], nb), b, 0, s, upper(t, j),
-                       (const Mem*)w.tmap[2 + 2 * j], (Mem*)w.tmap[3 + 2 * j],
-                       (Mem*)w.tmap[4 + 2 * j]);
+  for (int j = 0; j + 1 < t.up; ++j) {
+    const Stage st = upper(t, j);
+    hipLaunchKernelGGL((kt_tup<B>), dim3((unsigned)t.grp[j], nb), threads<B>(st),
+                       (lds<B, kDumpV<B>, false>(st)), s, st, (const Mem*)w.tmap[2 + 2 * j],
+                       (Mem*)w.tmap[3 + 2 * j], (Mem*)w.tmap[4 + 2 * j]);
+  }
   for (int j = t.up - 1; j >= 0; --j) {
+    const Stage st = upper(t, j);
     if (j == t.up - 1)
-      hipLaunchKernelGGL((kt_troot<B>), dim3(1, nb), b, 0, s, kp, upper(t, j),
+      hipLaunchKernelGGL((kt_troot<B>), dim3(1, nb), threads<B>(st),
+                         (lds<B, kDumpV<B> + kDumpX<B>, false>(st)), s, kp, st,
                          (const Mem*)w.tmap[2 + 2 * j], (Mem*)w.tmap[3 + 2 * j],
                          (Mem*)w.tx[2 + 2 * j]);
     else
-      hipLaunchKernelGGL((kt_tdown<B>), dim3((unsigned)t.grp[j], nb), b, 0, s, kp, upper(t, j),
-                         (const Mem*)w.tmap[2 + 2 * j], (const Mem*)w.tmap[3 + 2 * j],
-                         (const Mem*)w.tx[4 + 2 * j], (Mem*)w.tx[2 + 2 * j]);
+      hipLaunchKernelGGL((kt_tdown<B>), dim3((unsigned)t.grp[j], nb), threads<B>(st),
+                         (lds<B, kDumpX<B>, false>(st)), s, kp, st, (const Mem*)w.tmap[2 + 2 * j],
+                         (const Mem*)w.tmap[3 + 2 * j], (const Mem*)w.tx[4 + 2 * j],
+                         (Mem*)w.tx[2 + 2 * j]);
   }
   return hipGetLastError();
 }
@@ -106,9 +121,11 @@ template <class B>
 hipError_t launch_tbottom(const KProb& kp, const GTree& t, const Work& w, const void* S,
                           const void* v, void* x, void* u, hipStream_t s) {
   using Mem = typename B::Mem;
-  hipLaunchKernelGGL((kt_tbottom<B>), dim3((unsigned)t.m, kp.batch), dim3(kGroupThreads<B>), 0, s, kp,
-                     bottom<B>(t), (const Mem*)S, (const Mem*)v, (const Mem*)w.tmap[1],
-                     (const Mem*)w.tx[2], (Mem*)x, (Mem*)u, (const Mem*)w.bmap);
+  const Stage st = bottom<B>(t);
+  hipLaunchKernelGGL((kt_tbottom<B>), dim3((unsigned)t.m, kp.batch), threads<B>(st),
+                     (lds<B, kDumpX<B>, false>(st)), s, kp, st, (const Mem*)S, (const Mem*)v,
+                     (const Mem*)w.tmap[1], (const Mem*)w.tx[2], (Mem*)x, (Mem*)u,
+                     (const Mem*)w.bmap);
   return hipGetLastError();
 }
 
@@ -116,9 +133,10 @@ hipError_t launch_tbottom(const KProb& kp, const GTree& t, const Work& w, const 
 template <class B>
 hipError_t launch_slot_states(const KProb& kp, const GTree& t, const Work& w, hipStream_t s) {
   using Mem = typename B::Mem;
-  hipLaunchKernelGGL((kt_tdown<B>), dim3((unsigned)t.m, kp.batch), dim3(kGroupThreads<B>), 0, s, kp,
-                     stage(1, t.n1, t.n1, t.m), (const Mem*)nullptr, (const Mem*)w.tmap[1],
-                     (const Mem*)w.tx[2], (Mem*)w.tx[1]);
+  const Stage st = stage(1, t.n1, t.n1, t.m);
+  hipLaunchKernelGGL((kt_tdown<B>), dim3((unsigned)t.m, kp.batch), threads<B>(st),
+                     (lds<B, kDumpX<B>, false>(st)), s, kp, st, (const Mem*)nullptr,
+                     (const Mem*)w.tmap[1], (const Mem*)w.tx[2], (Mem*)w.tx[1]);
   return hipGetLastError();
 }
 
@@ -129,8 +147,9 @@ hipError_t launch_scans(const KProb& kp, const GTree& t, const Work& w, const vo
   using Mem = typename B::Mem;
   if (t.m == 1 && t.up == 0) {
     if (t.G != kGroup<B>) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((kt_small<B>), dim3(1, kp.batch), dim3(kGroupThreads<B>), 0, s, kp, bottom<B>(t),
-                       (const Mem*)elts, (Mem*)w.vtup[1], (Mem*)w.tmap[1], (Mem*)S, (Mem*)v,
+    const Stage st = bottom<B>(t);
+    hipLaunchKernelGGL((kt_small<B>), dim3(1, kp.batch), threads<B>(st), (lds<B, kDumpT<B>>(st)), s, kp,
+                       st, (const Mem*)elts, (Mem*)w.vtup[1], (Mem*)w.tmap[1], (Mem*)S, (Mem*)v,
                        (Mem*)x, (Mem*)u, (Mem*)w.bmap);
     return hipGetLastError();
   }

@@ -64,7 +64,8 @@ constexpr int bottom_run(int wc) {
 //   dAd/ds = (I + Ad) K,  db/ds = -(I + Ad)(G eta + c),  dC/ds = -((I + Ad) Lc)((I + Ad) Lc)^T,
 //   deta/ds = K^T eta + J c - Q r,  dJ/ds = -Q + J K - F^T J,
 // A held transposed.  The blocks of a wave are 8 apart (k % 8 fixed), so its stores of one value
-// fill whole sectors of the element layout, and the waves that complete a line run on one XCD.
+// fill whole sectors of the element layout, and the waves that complete a line run on one XCD; a
+// horizon too short for that is taken in order, which fills its waves.
 // Per stage and node group: 3 products with K, one each for K and the C part (two small ones), 3
 // matrix-vector products: bound by the FP64 (FP32) rate of the matrix instruction.
 // ------------------------------------------------------------------------------------------
@@ -76,7 +77,9 @@ __global__ __launch_bounds__(64, 2) void kt_build(const KProb kp, typename B::Me
   constexpr int N = B::N;
   const int nu = kp.nu, nn = kp.n;
   const long T = kp.T;
-  const long k0 = (long)(blockIdx.x >> 3) * (8 * B::NODES) + 8 * B::node() + (blockIdx.x & 7);
+  const long w = blockIdx.x;
+  const long k0 = T < 8 * B::NODES ? w * B::NODES + B::node()
+                                   : (w >> 3) * (8 * B::NODES) + 8 * B::node() + (w & 7);
   const bool live = k0 < T;
   const long k = live ? k0 : T - 1;
   int p = blockIdx.y;
@@ -283,6 +286,19 @@ template <class B>
 constexpr int kDumpV = (B::MR + B::VR) * B::LANES;  // values and maps
 template <class B>
 constexpr int kDumpX = B::VR * B::LANES;
+// The LDS of a launch: a dump per slot that the workgroup's waves hold, then the waves' scratch of the
+// pivoted inverse.  Sized by the host, with as many waves as a single small group needs (a full group's
+// 41 KB would let three workgroups of one busy wave each onto a CU).
+extern __shared__ double lds_raw[];
+TDEV int lds_waves() { return (int)(blockDim.x >> 6); }
+template <class B, int DUMP>
+TDEV auto lds_slots() {
+  return (typename B::R(*)[DUMP])lds_raw;
+}
+template <class B, int DUMP>
+TDEV typename B::R* lds_scratch(int w) {
+  return (typename B::R*)lds_raw + lds_waves() * B::NODES * DUMP + w * kInvScr<B>;
+}
 template <class B, int CNT>
 TDEV void put(const typename B::R (&x)[CNT], typename B::R* g) {
 #pragma unroll
@@ -483,12 +499,12 @@ __global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_vup(const Stage st,
                                                            typename B::Mem* __restrict__ sib,
                                                            typename B::Mem* __restrict__ grp) {
   constexpr int NE = kNE<B::N>;
-  __shared__ typename B::R ex[kGroup<B>][kDumpT<B>], scr_all[kGroupWaves<B>][kInvScr<B>];
+  auto ex = lds_slots<B, kDumpT<B>>();
   const Place at(st.n_grp, batch, run);
   if (!at.live) return;
   const long g = at.g;
   const Here<B> h(st, g, at.p);
-  typename B::R* scr = scr_all[h.w];
+  typename B::R* scr = lds_scratch<B, kDumpT<B>>(h.w);
   if (h.w * B::NODES < h.cnt) {
     const Tup<B> acc = t_serial<B>(h, st, src_elts, src, scr);
     if (h.live) dump<B>(acc, ex[h.cnt - 1 - h.loc]);
@@ -506,9 +522,9 @@ __global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_vroot(const KProb k
                                                              typename B::Mem* sib,
                                                              typename B::Mem* __restrict__ val_out) {
   constexpr int NE = kNE<B::N>;
-  __shared__ typename B::R ex[kGroup<B>][kDumpT<B>], scr_all[kGroupWaves<B>][kInvScr<B>];
+  auto ex = lds_slots<B, kDumpT<B>>();
   const Here<B> h(st, 0, blockIdx.y);
-  typename B::R* scr = scr_all[h.w];
+  typename B::R* scr = lds_scratch<B, kDumpT<B>>(h.w);
   if (h.w * B::NODES < h.cnt) {
     const Tup<B> acc = t_serial<B>(h, st, false, src, scr);
     if (h.live) dump<B>(acc, ex[h.cnt - 1 - h.loc]);
@@ -527,9 +543,9 @@ __global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_vdown(
     const KProb kp, const Stage st, const typename B::Mem* __restrict__ src,
     const typename B::Mem* __restrict__ sib, const typename B::Mem* __restrict__ val_in,
     typename B::Mem* __restrict__ val_out) {
-  __shared__ typename B::R val[kGroup<B>][kDumpV<B>], scr_all[kGroupWaves<B>][kInvScr<B>];
+  auto val = lds_slots<B, kDumpV<B>>();
   const Here<B> h(st, blockIdx.x, blockIdx.y);
-  typename B::R* scr = scr_all[h.w];
+  typename B::R* scr = lds_scratch<B, kDumpV<B>>(h.w);
   t_vtop<B>(kp, h, st.n_grp == 1, val_in + ((long)h.p * st.n_grp + h.g) * kVR<B::N>, val);
   t_vdown<B>(h, val, sib + ((long)h.p * st.n_slot + h.g * kGroup<B>)*kNE<B::N>, scr);
   t_vspread<B>(h, st, src, val, val_out, scr);
@@ -731,7 +747,7 @@ __global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_tup(const Stage st,
                                                            typename B::Mem* __restrict__ sib,
                                                            typename B::Mem* __restrict__ grp) {
   constexpr int VR = kVR<B::N>;
-  __shared__ typename B::R ex[kGroup<B>][kDumpV<B>];
+  auto ex = lds_slots<B, kDumpV<B>>();
   const Here<B> h(st, blockIdx.x, blockIdx.y);
   t_tserial<B>(h, st, src, ex);
   t_tup<B>(h, ex, sib + ((long)h.p * st.n_slot + h.g * kGroup<B>)*VR, false);
@@ -744,7 +760,8 @@ __global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_troot(const KProb k
                                                              typename B::Mem* sib,
                                                              typename B::Mem* __restrict__ x_out) {
   constexpr int VR = kVR<B::N>;
-  __shared__ typename B::R ex[kGroup<B>][kDumpV<B>], xs[kGroup<B>][kDumpX<B>];
+  auto ex = lds_slots<B, kDumpV<B>>();
+  auto xs = (typename B::R(*)[kDumpX<B>])ex[lds_waves() * B::NODES];  // after the maps
   const Here<B> h(st, 0, blockIdx.y);
   typename B::Mem* sb = sib + (long)h.p * st.n_slot * VR;
   t_tserial<B>(h, st, src, ex);
@@ -759,7 +776,7 @@ __global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_tdown(
     const KProb kp, const Stage st, const typename B::Mem* __restrict__ src,
     const typename B::Mem* __restrict__ sib, const typename B::Mem* __restrict__ x_in,
     typename B::Mem* __restrict__ x_out) {
-  __shared__ typename B::R xs[kGroup<B>][kDumpX<B>];
+  auto xs = lds_slots<B, kDumpX<B>>();
   const Here<B> h(st, blockIdx.x, blockIdx.y);
   t_ttop<B>(kp, h, st.n_grp == 1, x_in + ((long)h.p * st.n_grp + h.g) * B::N, xs);
   t_tdown<B>(h, xs, sib + ((long)h.p * st.n_slot + h.g * kGroup<B>)*kVR<B::N>);
@@ -776,12 +793,12 @@ __global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_vbottom(
     typename B::Mem* __restrict__ msib, typename B::Mem* __restrict__ grp,
     typename B::Mem* __restrict__ bmaps) {
   constexpr int VR = kVR<B::N>;
-  __shared__ typename B::R val[kGroup<B>][kDumpV<B>], scr_all[kGroupWaves<B>][kInvScr<B>];
+  auto val = lds_slots<B, kDumpV<B>>();
   const Place at(st.n_grp, kp.batch, run);
   if (!at.live) return;
   const long g = at.g;
   const Here<B> h(st, g, at.p);
-  typename B::R* scr = scr_all[h.w];
+  typename B::R* scr = lds_scratch<B, kDumpV<B>>(h.w);
   t_vtop<B>(kp, h, st.n_grp == 1, val_in + ((long)h.p * st.n_grp + h.g) * kVR<B::N>, val);
   t_vdown<B>(h, val, sib + ((long)h.p * st.n_slot + g * kGroup<B>)*kNE<B::N>, scr);
   const Map<B> acc = t_vbottom<B>(kp, h, st.c, elts, val, Sout, vout, bmaps, msib != nullptr, scr);
@@ -888,7 +905,7 @@ __global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_tbottom(
     const typename B::Mem* __restrict__ vg, const typename B::Mem* __restrict__ msib,
     const typename B::Mem* __restrict__ x_in, typename B::Mem* __restrict__ xout,
     typename B::Mem* __restrict__ uout, const typename B::Mem* __restrict__ bmaps) {
-  __shared__ typename B::R xs[kGroup<B>][kDumpX<B>];
+  auto xs = lds_slots<B, kDumpX<B>>();
   const Here<B> h(st, blockIdx.x, blockIdx.y);
   t_ttop<B>(kp, h, st.n_grp == 1, x_in + ((long)h.p * st.n_grp + h.g) * B::N, xs);
   t_tdown<B>(h, xs, msib + ((long)h.p * st.n_slot + h.g * kGroup<B>)*kVR<B::N>);
@@ -902,9 +919,9 @@ __global__ __launch_bounds__(64 * kGroupWaves<B>, 2) void kt_small(
     typename B::Mem* msib, typename B::Mem* Sout, typename B::Mem* vout,
     typename B::Mem* __restrict__ xout, typename B::Mem* __restrict__ uout, typename B::Mem* bmaps) {
   constexpr int NE = kNE<B::N>, VR = kVR<B::N>;
-  __shared__ typename B::R ex[kGroup<B>][kDumpT<B>], scr_all[kGroupWaves<B>][kInvScr<B>];
+  auto ex = lds_slots<B, kDumpT<B>>();
   const Here<B> h(st, 0, blockIdx.y);
-  typename B::R* scr = scr_all[h.w];
+  typename B::R* scr = lds_scratch<B, kDumpT<B>>(h.w);
   typename B::Mem* sb = sib + (long)h.p * st.n_slot * NE;
   typename B::Mem* mb = msib + (long)h.p * st.n_slot * VR;
   const bool any = h.w * B::NODES < h.cnt;
