@@ -57,9 +57,10 @@ __device__ inline long tile_row_item(long g) {
 // Short horizons keep consecutive items per wave (neighbouring blocks share reference samples, and
 // a few waves are latency-bound): rows per wave from 8 tiles on.
 constexpr long kTileRowMin = 8L * kTile;
-// rev: the last workgroups' items first.
-__device__ inline long build_item(long n, int rev = 0) {
-  const long b = rev ? gridDim.x - 1 - blockIdx.x : blockIdx.x, g = b * blockDim.x + threadIdx.x;
+// REV: the last workgroups' items first.
+template <bool REV = false>
+__device__ inline long build_item(long n) {
+  const long b = REV ? gridDim.x - 1 - blockIdx.x : blockIdx.x, g = b * blockDim.x + threadIdx.x;
   return n >= kTileRowMin ? tile_row_item(g) : g;
 }
 
@@ -869,10 +870,10 @@ LQT_DEV void element_at(const KProb& kp, int p, long k, Tup<N, R>& out) {
     build_block<N, NU, R, CONST_COEF>(kp, blk_ragged(kp, i, k), out);
 }
 
-template <int N, int NU, class R, bool CONST_COEF>
+template <int N, int NU, class R, bool CONST_COEF, bool REV>
 __global__ __launch_bounds__(kThreads) void k_build(const KProb kp, R* __restrict__ elts) {
   const int p = blockIdx.y;
-  const long k = build_item(kp.T, kp.rev);
+  const long k = build_item<REV>(kp.T);
   if (k >= kp.T) return;
   Tup<N, R> out;
   element_at<N, NU, R, CONST_COEF>(kp, p, k, out);
@@ -1315,11 +1316,14 @@ struct TrajAlg {
   }
 };
 
-// Waves per SIMD the registers of the single-pass scans are held to: two in FP32, where that costs
-// nx = 4 a few dozen spilled values (T = 2^20: value scan 187 -> 170 us, trajectory scan 146 ->
-// 131); in FP64 it would cost hundreds (302 -> 990 us).
-template <class R>
-constexpr int kScanWaves = sizeof(R) == 4 ? 2 : 1;
+// The single-pass scans at nx = 4 in FP32 with their registers held to two waves a SIMD (W = 2), for a few
+// dozen spilled values, where there are more tiles than SIMDs (T = 2^20: value scan 187 -> 170 us,
+// trajectory scan 146 -> 131; 8192 problems of one block: value scan 92 -> 65); with fewer, a second
+// wave a SIMD only brings the spills (512 problems of 64 blocks: 25 -> 28).  In FP64 it would cost hundreds
+// of values (302 -> 990), and smaller sizes fit without.
+template <int N, class R>
+constexpr bool kTwoWaves = N == 4 && sizeof(R) == 4;
+constexpr long kSimds = 1024;
 
 // ------------------------------------------------------------------------------------------
 // Single-pass scans (lookback.hpp).  One wave per tile of 64 c blocks (c consecutive blocks per
@@ -1328,12 +1332,58 @@ constexpr int kScanWaves = sizeof(R) == 4 ? 2 : 1;
 // tile's free end from the records of the tiles before it in the flow, carries that state to
 // every lane through the lane's exclusive product, and sweeps the lane's blocks.
 // ------------------------------------------------------------------------------------------
-// The sweep of a lane over its blocks [j0, j1), from the value st at the right end of the last.
-template <int N, class R, int CH>
-LQT_DEV void value_sweep(const KProb& kp, int p, const R* __restrict__ ep, long j0, long j1, int lane,
-                         typename ValAlg<N, R>::State& st, R* __restrict__ Sout,
-                         R* __restrict__ vout, R (&sE)[Lay<N>::NE][kThreads]) {
+// Value scan (Theorem 6, Lemma 7, terminal element of Sec. IV-D).  The flow is backward in time:
+// place i takes tile G - 1 - i, so the first place holds the end of the horizon.  Tiles are 512
+// blocks, 8 per lane (one tile of the element layout): with four waves per CU at most (a lane
+// holds two tuples and a Lemma 7 combination), a horizon of 2^20 blocks then needs two rounds of
+// resident waves instead of four, and the per-tile costs that do not grow with the tile (the
+// lane scan of the wave and the look-back) are spread over twice the blocks.
+// Value tile of place i of problem p (the kernel body).  SPLIT: the products of each lane's right
+// neighbours in part and the value at the tile's right end in vals instead of the reduction and the
+// look-back (the sweep is not a function of its own: the single pass lost 3 to 5 % to its code then).
+template <int N, class R, int CH, bool SPLIT = false>
+LQT_DEV void vscan_tile(const KProb& kp, int p, long i, const R* __restrict__ elts,
+                        R* __restrict__ Sout, R* __restrict__ vout, const LbRecs& lb,
+                        R (&sE)[Lay<N>::NE][kThreads], const R* __restrict__ part = nullptr,
+                        const R* __restrict__ vals = nullptr) {
+  using Alg = ValAlg<N, R>;
+  const int lane = threadIdx.x;
   const long T = kp.T;
+  const long tile = lb.G - 1 - i;
+  const R* ep = elts + (long)p * Lay<N>::NE * padt(T);
+  const long j0 = tile * (64L * CH) + (long)lane * CH;
+  const long j1 = min(j0 + CH, T);
+  // lanes holding blocks (fewer than 64 only in the tile at the end of a short horizon)
+  const int active = (int)min((T - tile * 64L * CH + CH - 1) / CH, 64L);
+  typename Alg::State st;
+  if constexpr (SPLIT) {
+    if (j0 >= T) return;
+    const R* val = vals + ((long)p * lb.G + tile) * (N * N + N);
+#pragma unroll
+    for (int a = 0; a < N; ++a) {
+#pragma unroll
+      for (int b = a; b < N; ++b) st.S[Sym<N>::at(a, b)] = val[a * N + b];
+      st.v[a] = val[N * N + a];
+    }
+    Tup<N, R> E;
+    tup_load_rec<PlainAcc>(E, part + (long)p * Lay<N>::NE * lb.G * 64, lb.G * 64, tile * 64 + lane);
+    if (lane != 63) Alg::apply(E, st);
+  } else {
+    // The lane's exclusive product waits in LDS during the look-back (registers are short: the
+    // look-back combines tuples of its own).
+    Tup<N, R> P;
+    serial_product(ep, j0, j1, P);
+    wave_scan<Alg>(P, lane, tree_levels(active));  // lane m: product of lanes m ..; lane 0: tile
+    Tup<N, R> E;
+    wave_exclusive<Alg>(P, E, lane);
+    tup_store_rec<PlainAcc>(E, &sE[0][0], kThreads, lane);
+    typename Alg::State st0;
+    lb_resolve<Alg, R>(kp, (const R*)nullptr, p, lb, i, P, lane, st0);
+    if (j0 >= T) return;
+    tup_load_rec<PlainAcc>(E, &sE[0][0], kThreads, lane);
+    if (lane != 63) Alg::apply(E, st0);  // the value at the right end of the lane's blocks
+    st = st0;
+  }
   R* Sp = Sout + (long)p * (T + 1) * N * N;
   R* vp = vout + (long)p * (T + 1) * N;
   if (j1 == T && !kp.seg) {
@@ -1368,50 +1418,10 @@ LQT_DEV void value_sweep(const KProb& kp, int p, const R* __restrict__ ep, long 
   }
 }
 
-// Value scan (Theorem 6, Lemma 7, terminal element of Sec. IV-D).  The flow is backward in time:
-// place i takes tile G - 1 - i, so the first place holds the end of the horizon.  Tiles are 512
-// blocks, 8 per lane (one tile of the element layout): with four waves per CU at most (a lane
-// holds two tuples and a Lemma 7 combination), a horizon of 2^20 blocks then needs two rounds of
-// resident waves instead of four, and the per-tile costs that do not grow with the tile (the
-// lane scan of the wave and the look-back) are spread over twice the blocks.
-// Value tile of place i of problem p (the kernel body).
-template <int N, class R, int CH>
-LQT_DEV void vscan_tile(const KProb& kp, int p, long i, const R* __restrict__ elts,
-                        R* __restrict__ Sout, R* __restrict__ vout, const LbRecs& lb,
-                        R (&sE)[Lay<N>::NE][kThreads]) {
-  using Alg = ValAlg<N, R>;
-  const int lane = threadIdx.x;
-  const long T = kp.T;
-  const long tile = lb.G - 1 - i;
-  const R* ep = elts + (long)p * Lay<N>::NE * padt(T);
-  const long j0 = tile * (64L * CH) + (long)lane * CH;
-  const long j1 = min(j0 + CH, T);
-  // lanes holding blocks (fewer than 64 only in the tile at the end of a short horizon)
-  const int active = (int)min((T - tile * 64L * CH + CH - 1) / CH, 64L);
-  typename Alg::State st;
-  // The lane's exclusive product waits in LDS during the look-back (registers are short: the
-  // look-back combines tuples of its own).
-  {
-    Tup<N, R> P;
-    serial_product(ep, j0, j1, P);
-    wave_scan<Alg>(P, lane, tree_levels(active));  // lane m: product of lanes m ..; lane 0: tile
-    Tup<N, R> E;
-    wave_exclusive<Alg>(P, E, lane);
-    tup_store_rec<PlainAcc>(E, &sE[0][0], kThreads, lane);
-    typename Alg::State st0;
-    lb_resolve<Alg, R>(kp, (const R*)nullptr, p, lb, i, P, lane, st0);
-    if (j0 >= T) return;
-    tup_load_rec<PlainAcc>(E, &sE[0][0], kThreads, lane);
-    if (lane != 63) Alg::apply(E, st0);  // the value at the right end of the lane's blocks
-    st = st0;
-  }
-  value_sweep<N, R, CH>(kp, p, ep, j0, j1, lane, st, Sout, vout, sE);
-}
-
-template <int N, class R, int CH>
-__global__ __launch_bounds__(kThreads, kScanWaves<R>) void k_vscan(const KProb kp, const R* __restrict__ elts,
-                                                     R* __restrict__ Sout, R* __restrict__ vout,
-                                                     const LbRecs lb) {
+template <int N, class R, int CH, int W>
+__global__ __launch_bounds__(kThreads, W) void k_vscan(const KProb kp, const R* __restrict__ elts,
+                                                        R* __restrict__ Sout, R* __restrict__ vout,
+                                                        const LbRecs lb) {
   __shared__ R sE[Lay<N>::NE][kThreads];
   const int p = blockIdx.y;
   vscan_tile<N, R, CH>(kp, p, lb_place(lb, p), elts, Sout, vout, lb, sE);
@@ -1451,25 +1461,10 @@ __global__ __launch_bounds__(kThreads) void k_vswp(const KProb kp, const R* __re
                                                     const R* __restrict__ part,
                                                     const R* __restrict__ vals, R* __restrict__ Sout,
                                                     R* __restrict__ vout) {
-  using Alg = ValAlg<N, R>;
   __shared__ R sE[Lay<N>::NE][kThreads];
-  const int p = blockIdx.y, lane = threadIdx.x;
-  const long T = kp.T, G = gridDim.x, tile = G - 1 - blockIdx.x;
-  const long j0 = tile * (64L * CH) + (long)lane * CH;
-  const long j1 = min(j0 + CH, T);
-  if (j0 >= T) return;
-  const R* val = vals + ((long)p * G + tile) * (N * N + N);
-  typename Alg::State st;
-#pragma unroll
-  for (int a = 0; a < N; ++a) {
-#pragma unroll
-    for (int b = a; b < N; ++b) st.S[Sym<N>::at(a, b)] = val[a * N + b];
-    st.v[a] = val[N * N + a];
-  }
-  Tup<N, R> E;
-  tup_load_rec<PlainAcc>(E, part + (long)p * Lay<N>::NE * G * 64, G * 64, tile * 64 + lane);
-  if (lane != 63) Alg::apply(E, st);
-  value_sweep<N, R, CH>(kp, p, elts + (long)p * Lay<N>::NE * padt(T), j0, j1, lane, st, Sout, vout, sE);
+  LbRecs lb;
+  lb.G = gridDim.x;
+  vscan_tile<N, R, CH, true>(kp, blockIdx.y, blockIdx.x, elts, Sout, vout, lb, sE, part, vals);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1616,7 +1611,7 @@ __global__ __launch_bounds__(kThreads) void k_build_rest(const KProb kp,
   const int p = blockIdx.y;
   if (!bad[p]) return;
   const long T = kp.T;
-  const long k = build_item(T, true);
+  const long k = build_item<true>(T);
   if (k >= T) return;
   Tup<N, R> out;
   build_block<N, NU, R, true>(kp, blk_plain(kp, p, k), out);
@@ -1723,12 +1718,12 @@ LQT_DEV void tscan_tile(const KProb& kp, int p, long i, const R* __restrict__ el
   }
 }
 
-template <int N, int NU, class R, int CH>
-__global__ __launch_bounds__(kThreads, kScanWaves<R>) void k_tscan(const KProb kp, const R* __restrict__ elts,
-                                                     const R* __restrict__ Sg,
-                                                     const R* __restrict__ vg,
-                                                     R* __restrict__ xout, R* __restrict__ uout,
-                                                     const LbRecs lb) {
+template <int N, int NU, class R, int CH, int W>
+__global__ __launch_bounds__(kThreads, W) void k_tscan(const KProb kp, const R* __restrict__ elts,
+                                                        const R* __restrict__ Sg,
+                                                        const R* __restrict__ vg,
+                                                        R* __restrict__ xout, R* __restrict__ uout,
+                                                        const LbRecs lb) {
   const int p = blockIdx.y;
   tscan_tile<N, NU, R, CH, PlainAcc>(kp, p, lb_place(lb, p), elts, Sg, vg, xout, uout, lb);
 }
@@ -2330,14 +2325,22 @@ inline dim3 grid_waves(long waves, int batch) { return dim3((unsigned)waves, (un
 
 template <int N, int NU, class R>
 struct L {
+  template <bool CC>
+  static void build_c(const KProb& kp, void* elts, hipStream_t s) {
+    const dim3 g = grid_tile_rows(kp.T, kp.batch);
+    if constexpr (N >= 3) {  // a template rather than a flag: that cost batches of single blocks 3 %
+      if (kp.rev) {
+        hipLaunchKernelGGL((k_build<N, NU, R, CC, true>), g, dim3(kThreads), 0, s, kp, (R*)elts);
+        return;
+      }
+    }
+    hipLaunchKernelGGL((k_build<N, NU, R, CC, false>), g, dim3(kThreads), 0, s, kp, (R*)elts);
+  }
   static hipError_t build(const KProb& kp, void* elts, hipStream_t s) {
-    const bool cc = !kp.F_sampled && !kp.L_sampled && !kp.has_c;
-    if (cc)
-      hipLaunchKernelGGL((k_build<N, NU, R, true>), grid_tile_rows(kp.T, kp.batch), dim3(kThreads),
-                         0, s, kp, (R*)elts);
+    if (!kp.F_sampled && !kp.L_sampled && !kp.has_c)
+      build_c<true>(kp, elts, s);
     else
-      hipLaunchKernelGGL((k_build<N, NU, R, false>), grid_tile_rows(kp.T, kp.batch), dim3(kThreads),
-                         0, s, kp, (R*)elts);
+      build_c<false>(kp, elts, s);
     return hipGetLastError();
   }
   static hipError_t vreduce0(const KProb& kp, const void* elts, void* dst, long n1,
@@ -2349,8 +2352,16 @@ struct L {
   template <int CH>
   static void vscan_c(const KProb& kp, const void* elts, void* S, void* v, const LbRecs& lb,
                       hipStream_t s) {
-    hipLaunchKernelGGL((k_vscan<N, R, CH>), dim3((unsigned)lb.G, kp.batch), dim3(kThreads), 0, s,
-                       kp, (const R*)elts, (R*)S, (R*)v, lb);
+    const dim3 g((unsigned)lb.G, kp.batch);
+    if constexpr (kTwoWaves<N, R>) {
+      if ((long)lb.G * kp.batch > kSimds) {
+        hipLaunchKernelGGL((k_vscan<N, R, CH, 2>), g, dim3(kThreads), 0, s, kp, (const R*)elts, (R*)S,
+                           (R*)v, lb);
+        return;
+      }
+    }
+    hipLaunchKernelGGL((k_vscan<N, R, CH, 1>), g, dim3(kThreads), 0, s, kp, (const R*)elts, (R*)S,
+                       (R*)v, lb);
   }
   template <int CH>
   static void vred_c(const KProb& kp, const unsigned* bad, const void* elts, void* part, void* tiles,
@@ -2435,8 +2446,16 @@ struct L {
   template <int CH>
   static void tscan_c(const KProb& kp, const void* elts, const void* S, const void* v, void* x,
                       void* u, const LbRecs& lb, hipStream_t s) {
-    hipLaunchKernelGGL((k_tscan<N, NU, R, CH>), dim3((unsigned)lb.G, kp.batch), dim3(kThreads), 0,
-                       s, kp, (const R*)elts, (const R*)S, (const R*)v, (R*)x, (R*)u, lb);
+    const dim3 g((unsigned)lb.G, kp.batch);
+    if constexpr (kTwoWaves<N, R> && CH == kScanMaxTChunk) {  // fewer blocks a lane fit without
+      if ((long)lb.G * kp.batch > kSimds) {
+        hipLaunchKernelGGL((k_tscan<N, NU, R, CH, 2>), g, dim3(kThreads), 0, s, kp, (const R*)elts,
+                           (const R*)S, (const R*)v, (R*)x, (R*)u, lb);
+        return;
+      }
+    }
+    hipLaunchKernelGGL((k_tscan<N, NU, R, CH, 1>), g, dim3(kThreads), 0, s, kp, (const R*)elts,
+                       (const R*)S, (const R*)v, (R*)x, (R*)u, lb);
   }
   static hipError_t tscan(const KProb& kp, const void* elts, const void* S, const void* v,
                           void* x, void* u, const LbRecs& lb, int chunk, hipStream_t s) {
