@@ -299,6 +299,15 @@ bool use_split_scan(const lqt_dims* d) {
   return d->nx == 4 ? d->T > 512 : d->T > 1L << 13 && d->T <= 1L << 15;
 }
 
+// The elements of the time-invariant path formed and reduced in one launch (k_lti_red) instead of
+// k_build_lti and k_vred.  In FP32 a short horizon has too few waves for it, each of which forms its
+// blocks one after the other: nx = 4 solves of one problem (us, in one launch / as two / with the
+// single-pass scan) 68.8 / 62.5 / 64.0 at T = 600, 77.3 / 72.7 / 79.2 at 5000, 90 / 92 / 102 at 30000.
+// In FP64 one launch is never the slower (71.0 / 77.9 single-pass at 600, 77.0 / 98.5 at 5000).
+bool use_lti_red(const lqt_dims* d) {
+  return d->lti && (d->dtype == LQT_F64 || (long)d->T * d->batch > 1L << 15);
+}
+
 // The check of the grid and the first-order tables instead of the general build (k_uni_prep,
 // k_lti_red), for calls of more than 2^19 blocks.  The tables cost 4 (2 n + 1) nx block integrations per
 // problem, the build they replace T: they have to be at most a sixteenth of it, or a batch of short
@@ -449,7 +458,7 @@ size_t layout(const lqt_dims* d, lqt_call call, char* base, Work* w, int wc, lon
   if (!tile && use_split_scan(d) &&
       (call == LQT_CALL_SCAN_VALUE || (call == LQT_CALL_SOLVE && keep_maps && nconsts == d->batch))) {
     const bool solve = call == LQT_CALL_SOLVE;
-    const int c = split_chunk(d, solve && (d->lti || use_uniform(d)));
+    const int c = split_chunk(d, solve && (use_lti_red(d) || use_uniform(d)));
     const GTree vt = node_tree(d->nx, d->T, 64 * c);
     void* a = take(es * B * ne_of(d->nx) * 64 * vt.m);
     if (w) w->vpart[1] = a, w->split = c;
@@ -1031,7 +1040,7 @@ lqt_status run_solve(const lqt_dims* dims, const KProb& kp, const Work& w, void*
   KProb kb = kp;
   kb.rev = w.split != 0;
   bool reduced = false;
-  if (w.split && !kp.seg && !o.queue_chunk && (lti || w.uni)) {
+  if (w.split && !kp.seg && !o.queue_chunk && (lti ? use_lti_red(dims) : w.uni != nullptr)) {
     const int c = w.split;
     unsigned* bad = lti ? nullptr : (unsigned*)w.lbv.ctr;  // cleared with the status words
     const void* tab = lti ? w.lti : w.uni;
