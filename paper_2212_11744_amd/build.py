@@ -26,6 +26,9 @@ SOURCES = ["lqt_api.hip", "lqt_prep.hip", "lqt_lane.hip", "lqt_tile.hip", "lqt_a
 # template instantiations, so the shards compile in parallel.  Must match kLaneShards and
 # kWaveShards in csrc/lqt_internal.hpp (a mismatch fails at link time).
 SHARDS = {"lqt_lane.hip": 4, "lqt_wave.hip": 8}
+# Objects of kernels are named lqt_lane.* and lqt_wave.*: the test of the sanitized host code links
+# these beside the units it compiles itself.  lqt_tile.hip serves the sizes of lqt_lane.hip.
+KERNEL_OBJECTS = {"lqt_tile.hip": "lqt_lane.tile.o"}
 
 
 def units() -> list:
@@ -35,7 +38,7 @@ def units() -> list:
         stem = os.path.splitext(src)[0]
         n = SHARDS.get(src)
         if n is None:
-            out.append((src, None, os.path.join(OBJ_DIR, stem + ".o")))
+            out.append((src, None, os.path.join(OBJ_DIR, KERNEL_OBJECTS.get(src, stem + ".o"))))
         else:
             out.extend((src, i, os.path.join(OBJ_DIR, f"{stem}.{i}.o")) for i in range(n))
     return out
