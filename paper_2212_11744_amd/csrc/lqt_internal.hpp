@@ -349,7 +349,7 @@ inline long tile_build_waves(long T, int nodes = 4) {
 
 // Short horizons of the small sizes on the kernels of tile_kernels.hpp (lqt_tile.hip): the element
 // build at nx = 3, 4, and in FP64 at nx = 4 the value scan alone and both scans (block maps in w.bmap);
-// and for every nx <= 4 the value tree over given nodes (w.vtup[2] -> w.vval[2]).
+// and for both sizes the value tree over given nodes (w.vtup[2] -> w.vval[2]).
 hipError_t tile_build(const KProb& kp, int dtype, void* elts, hipStream_t s);
 hipError_t tile_nodes(const KProb& kp, int dtype, const GTree& t, const Work& w, hipStream_t s);
 hipError_t tile_value(const KProb& kp, const GTree& t, const Work& w, const void* elts, void* S,

@@ -2363,44 +2363,71 @@ struct L {
     hipLaunchKernelGGL((k_vscan<N, R, CH, 1>), g, dim3(kThreads), 0, s, kp, (const R*)elts, (R*)S,
                        (R*)v, lb);
   }
+  // The three-launch value scan is for nx = 3 and 4 only, with 2, 4 or 8 blocks per lane; elements from
+  // tables are reduced with 4 or 8, on even grids (FP64, more than 2^19 blocks) with 8.
+  static constexpr bool kSplit = N >= 3, kUni = kSplit && sizeof(R) == 8;
+  template <int CH>
+  static dim3 tiles_of(const KProb& kp) {
+    return dim3((unsigned)((kp.T + 64L * CH - 1) / (64L * CH)), kp.batch);
+  }
   template <int CH>
   static void vred_c(const KProb& kp, const unsigned* bad, const void* elts, void* part, void* tiles,
                      hipStream_t s) {
     hipLaunchKernelGGL((k_vred<N, R, CH>), tiles_of<CH>(kp), dim3(kThreads), 0, s, kp, bad,
                        (const R*)elts, (R*)part, (R*)tiles);
   }
-  template <int CH>
+  static hipError_t vred(const KProb& kp, const unsigned* bad, const void* elts, void* part,
+                         void* tiles, int chunk, hipStream_t s) {
+    if constexpr (kSplit) {
+      switch (chunk) {
+        case 2: vred_c<2>(kp, bad, elts, part, tiles, s); return hipGetLastError();
+        case 4: vred_c<4>(kp, bad, elts, part, tiles, s); return hipGetLastError();
+        case 8: vred_c<8>(kp, bad, elts, part, tiles, s); return hipGetLastError();
+      }
+    }
+    return hipErrorInvalidValue;
+  }
+  template <int CH, bool UNI>
   static void lti_red_c(const KProb& kp, const void* tab, const unsigned* bad, void* elts, void* part,
                         void* tiles, hipStream_t s) {
-    if (bad)
-      hipLaunchKernelGGL((k_lti_red<N, R, CH, true>), tiles_of<CH>(kp), dim3(kThreads), 0, s, kp,
-                         (const R*)tab, bad, (R*)elts, (R*)part, (R*)tiles);
-    else
-      hipLaunchKernelGGL((k_lti_red<N, R, CH, false>), tiles_of<CH>(kp), dim3(kThreads), 0, s, kp,
-                         (const R*)tab, bad, (R*)elts, (R*)part, (R*)tiles);
+    hipLaunchKernelGGL((k_lti_red<N, R, CH, UNI>), tiles_of<CH>(kp), dim3(kThreads), 0, s, kp,
+                       (const R*)tab, bad, (R*)elts, (R*)part, (R*)tiles);
   }
   static hipError_t lti_red(const KProb& kp, const void* tab, const unsigned* bad, void* elts,
                             void* part, void* tiles, int chunk, hipStream_t s) {
-    switch (chunk) {
-      case 2: lti_red_c<2>(kp, tab, bad, elts, part, tiles, s); break;
-      case 4: lti_red_c<4>(kp, tab, bad, elts, part, tiles, s); break;
-      case 8: lti_red_c<8>(kp, tab, bad, elts, part, tiles, s); break;
-      default: return hipErrorInvalidValue;
+    if constexpr (kUni) {
+      if (bad) {
+        if (chunk != 8) return hipErrorInvalidValue;
+        lti_red_c<8, true>(kp, tab, bad, elts, part, tiles, s);
+        return hipGetLastError();
+      }
     }
-    return hipGetLastError();
+    if constexpr (kSplit) {
+      switch (bad ? 0 : chunk) {
+        case 4: lti_red_c<4, false>(kp, tab, nullptr, elts, part, tiles, s); return hipGetLastError();
+        case 8: lti_red_c<8, false>(kp, tab, nullptr, elts, part, tiles, s); return hipGetLastError();
+      }
+    }
+    return hipErrorInvalidValue;
   }
   static hipError_t uni_prep(const KProb& kp, void* tab, unsigned* bad, hipStream_t s) {
-    const int pb = (int)((4 * (2L * kp.n + 1) * N + kThreads - 1) / kThreads);
-    // four block lengths a lane: the check ends before the tables do
-    const int check = (int)((kp.T + 4L * kThreads - 1) / (4 * kThreads));
-    hipLaunchKernelGGL((k_uni_prep<N, NU, R>), dim3((unsigned)(pb + check), kp.batch),
-                       dim3(kThreads), 0, s, kp, (R*)tab, bad, pb);
-    return hipGetLastError();
+    if constexpr (kUni) {
+      const int pb = (int)((4 * (2L * kp.n + 1) * N + kThreads - 1) / kThreads);
+      // four block lengths a lane: the check ends before the tables do
+      const int check = (int)((kp.T + 4L * kThreads - 1) / (4 * kThreads));
+      hipLaunchKernelGGL((k_uni_prep<N, NU, R>), dim3((unsigned)(pb + check), kp.batch),
+                         dim3(kThreads), 0, s, kp, (R*)tab, bad, pb);
+      return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
   }
   static hipError_t build_rest(const KProb& kp, const unsigned* bad, void* elts, hipStream_t s) {
-    hipLaunchKernelGGL((k_build_rest<N, NU, R>), grid_tile_rows(kp.T, kp.batch), dim3(kThreads), 0, s,
-                       kp, bad, (R*)elts);
-    return hipGetLastError();
+    if constexpr (kUni) {
+      hipLaunchKernelGGL((k_build_rest<N, NU, R>), grid_tile_rows(kp.T, kp.batch), dim3(kThreads), 0, s,
+                         kp, bad, (R*)elts);
+      return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
   }
   template <int CH>
   static void vswp_c(const KProb& kp, const void* elts, const void* part, const void* vals, void* S,
@@ -2408,29 +2435,16 @@ struct L {
     hipLaunchKernelGGL((k_vswp<N, R, CH>), tiles_of<CH>(kp), dim3(kThreads), 0, s, kp,
                        (const R*)elts, (const R*)part, (const R*)vals, (R*)S, (R*)v);
   }
-  template <int CH>
-  static dim3 tiles_of(const KProb& kp) {
-    return dim3((unsigned)((kp.T + 64L * CH - 1) / (64L * CH)), kp.batch);
-  }
-  static hipError_t vred(const KProb& kp, const unsigned* bad, const void* elts, void* part,
-                         void* tiles, int chunk, hipStream_t s) {
-    switch (chunk) {
-      case 2: vred_c<2>(kp, bad, elts, part, tiles, s); break;
-      case 4: vred_c<4>(kp, bad, elts, part, tiles, s); break;
-      case 8: vred_c<8>(kp, bad, elts, part, tiles, s); break;
-      default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-  }
   static hipError_t vswp(const KProb& kp, const void* elts, const void* part, const void* vals,
                          void* S, void* v, int chunk, hipStream_t s) {
-    switch (chunk) {
-      case 2: vswp_c<2>(kp, elts, part, vals, S, v, s); break;
-      case 4: vswp_c<4>(kp, elts, part, vals, S, v, s); break;
-      case 8: vswp_c<8>(kp, elts, part, vals, S, v, s); break;
-      default: return hipErrorInvalidValue;
+    if constexpr (kSplit) {
+      switch (chunk) {
+        case 2: vswp_c<2>(kp, elts, part, vals, S, v, s); return hipGetLastError();
+        case 4: vswp_c<4>(kp, elts, part, vals, S, v, s); return hipGetLastError();
+        case 8: vswp_c<8>(kp, elts, part, vals, S, v, s); return hipGetLastError();
+      }
     }
-    return hipGetLastError();
+    return hipErrorInvalidValue;
   }
   static hipError_t vscan(const KProb& kp, const void* elts, void* S, void* v, const LbRecs& lb,
                           int chunk, hipStream_t s) {

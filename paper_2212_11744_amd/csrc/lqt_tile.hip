@@ -21,8 +21,6 @@ namespace {
 template <class Mem>
 hipError_t nodes_of(const KProb& kp, const GTree& t, const Work& w, hipStream_t s) {
   switch (kp.nx) {
-    case 1: return tile::launch_value_tree<tile::Q64<1, Mem>>(kp, t, w, s);
-    case 2: return tile::launch_value_tree<tile::Q64<2, Mem>>(kp, t, w, s);
     case 3: return tile::launch_value_tree<tile::Q64<3, Mem>>(kp, t, w, s);
     case 4: return tile::launch_value_tree<tile::Q64<4, Mem>>(kp, t, w, s);
     default: return hipErrorInvalidValue;
