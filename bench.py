@@ -209,7 +209,9 @@ def main(argv=None):
         "config": {"workload": f"point-mass LQT tracking, nx=4 nu=2, T={T} blocks x {n} RK4 steps on [0,10], "
                                f"single problem, elements + value scan + trajectory scan",
                    "T": T, "nx": 4, "nu": 2, "n_steps": n, "batch": 1, "parallelism": "single GPU"},
-        "roofline": {"bound": "alu", "kernel": "k_build (element build)", "achieved": achieved,
+        "roofline": {"bound": "alu",
+                     "kernel": "k_build (lqt_build_elements; the solve above forms the elements of this "
+                               "even grid from tables instead)", "achieved": achieved,
                      "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak, "traffic": traffic,
                      "flops_per_launch": flops, "launch_ms": ms_build,
                      "flops_per_block": build_flops_per_block(4, 2, n),

@@ -211,8 +211,9 @@ lqt_status lqt_dense_output(const lqt_dims *dims, const lqt_problem *prob, const
                             const void *v, const void *x, void *Sd, void *vd, void *xd, void *ud,
                             void *ws, size_t ws_bytes, hipStream_t stream);
 
-/* All three stages in one call (prep, element build, value scan, trajectory scan; the same
- * kernels and results as the stage calls).  elts may be NULL (then the elements live in the
+/* All three stages in one call (prep, element build, value scan, trajectory scan).  Results equal
+ * those of the stage calls up to rounding: where a stage's result need not leave the device's
+ * registers or a grid is even, the call takes kernels of its own.  elts may be NULL (then the elements live in the
  * workspace); S, v, x must be non-NULL; u may be NULL. */
 lqt_status lqt_solve(const lqt_dims *dims, const lqt_problem *prob, void *elts, void *S, void *v,
                      void *x, void *u, void *ws, size_t ws_bytes, hipStream_t stream);
@@ -276,8 +277,8 @@ lqt_status lqt_backward(const lqt_dims *dims, const lqt_problem *prob, const voi
  * constants, elements, and then for nx <= 4 the clearing of status words and one launch for both
  * scans, whose waves take tiles (value tiles in the value scan's order, then trajectory tiles)
  * from a work queue; a wave only waits for work taken before its own, so every wait ends; for
- * nx >= 5 a launch per level of the two scan trees.  The number of launches does not depend on
- * the number of problems.
+ * nx >= 5 a few launches per stage of the two scan trees, whose number grows with the logarithm of
+ * the rows.  The number of launches does not depend on how the rows divide into problems.
  * ------------------------------------------------------------------------------------------- */
 typedef struct lqt_ragged {
   int32_t nx, nu, n_steps, dtype; /* as in lqt_dims                                             */

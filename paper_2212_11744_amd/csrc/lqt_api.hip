@@ -233,7 +233,7 @@ namespace {
 Tree tree_for(const lqt_dims* d) { return plan_tree(d->T); }
 
 // Kernel family of a call: the per-lane path (one tuple per lane, registers) where it is
-// instantiated (nu <= nx <= 4), otherwise the wavefront-per-tuple path (LDS, any nx <= 16).
+// instantiated (nu <= nx <= 4), otherwise the wave path (lqt_wave.hip).
 bool use_wave(const lqt_dims* d) { return lane_ops(d->nx, d->nu, d->dtype) == nullptr; }
 
 // Blocks per wave at the bottom level of the wave path's trees for single solves and stage calls
@@ -269,10 +269,11 @@ bool use_tile_build(const lqt_dims* d) {
   return blocks <= limit && (d->T <= 4 || 4 * tile_build_waves(d->T) * d->batch <= limit);
 }
 // Scans, nx = 4 FP64, as long as every group has a CU of its own.  Against the single-pass scans of
-// the per-lane path, in a solve (us): 27 vs 76 at T = 64 and n = 10, 98 vs 131 at T = 2^16, the most
-// that 256 groups take.  FP32 (whose per-lane arithmetic is four times as fast) and nx <= 3
-// (smaller systems, the same number of steps) are at best even: 23 vs 27 in FP32 at T = 64, 23 vs
-// 23 at nx = 3, 73 vs 50 at nx = 3 and T = 16000.
+// the per-lane path, in a solve (us): 27 vs 76 at T = 64 and n = 10, 98 vs 133 at T = 2^16, the most
+// that 256 groups take; 37 vs 61 for 256 problems of 64 blocks, 78 vs 101 for 128 of 512.  Against the
+// three launches below, value scan alone: 51 at 2^16 vs 59 one block further.  FP32 (whose per-lane
+// arithmetic is four times as fast) and nx <= 3 (smaller systems, the same number of steps) are at
+// best even: 23 vs 27 in FP32 at T = 64, 23 vs 23 at nx = 3, 73 vs 50 at nx = 3 and T = 16000.
 constexpr int kTileChunk = 8;  // blocks per slot
 GTree tile_tree(const lqt_dims* d) { return group_tree(d->nx, d->T, kTileChunk); }
 bool use_tile_scans(const lqt_dims* d) {
@@ -283,9 +284,11 @@ bool use_tile_scans(const lqt_dims* d) {
 // The value scan of the per-lane path in three launches (k_vred, the tree over its tiles, k_vswp)
 // instead of a single pass.  Measured in a solve or alone (us): nx = 4 FP64 scan 84 vs 101 at
 // T = 150000, 189 vs 233 at 600000; nx = 4 FP32 scan 28 vs 33 at 600 (32 vs 29 at 300), 36 vs 41 at
-// 4000, solve 282 vs 344 at 600000; nx = 3 scan 22.4 vs 20.9 at 600, 27.2 vs 27.9 at 8000, 31 vs 37 at
-// 20000, 33 vs 37 at 28000, solve 79.3 vs 79.3 at 40000 and slower beyond; nx = 1, 2, whose
-// combinations are short: solve 46 vs 42 at nx = 2 and T = 17000.
+// 4000, solve 282 vs 344 at 600000; 1000 problems of 600 blocks 568 vs 710 (FP32 297 vs 456).  nx = 3
+// scan 22.4 vs 20.9 at 600, 27.2 vs 27.9 at 8000, 31 vs 37 at 20000, 33 vs 37 at 28000, solve 79.3 vs
+// 79.3 at 40000 and slower beyond; FP32 solve 52.3 vs 54.6 at 8193, 58.1 vs 59.4 at 20000, 63.6 vs 63.2
+// at 32768.  Batches of such horizons gain as one does (8 problems of 32768: 177 vs 186, FP32 142 vs
+// 150).  nx = 1, 2, whose combinations are short: solve 46 vs 42 at nx = 2 and T = 17000.
 // Blocks per lane: the single pass's, of all problems, but at least 2 (a wave's scan over its lanes is
 // six combinations, so fewer blocks a lane only add waves of them: T = 100000 29 + 17 us with 4, 32 +
 // 22 with 2); with the elements formed in the same launch (tables) 4 up to one round of resident waves

@@ -268,11 +268,13 @@ const Ops* lane_ops_shard(int nx, int nu, int dtype);
 // Instantiations for 1 <= nu <= nx <= 4 (one tuple per lane); nullptr if not available.
 const Ops* lane_ops(int nx, int nu, int dtype);
 
-// Wavefront-per-tuple path (lqt_wave.hip) for any nx <= 16: one wavefront per block or tree
-// node, matrices in LDS.  Its trees (Method 2) reduce wcs[l] nodes per wave at level l: n[0] = T,
-// n[l + 1] = ceil(n[l] / wcs[l]) while n[l] > wcs[l] (wcs[0] = wc, above kWaveUpperChunk).  Tree
-// nodes are records ([batch][n[l]][record]): tuples (NE values, element order), values (S full, v:
-// nx^2 + nx), maps (P = Psi - I, q: nx^2 + nx), states (nx).
+// Wave path (lqt_wave.hip) for 5 <= nx <= 16: Theorem 8 elements, value scan and Method 1 trajectory on
+// the kernels of tile_kernels.hpp (matrices in registers, GTree below); Theorem 9 and split-block
+// elements, Method 2, values inside the blocks and the time-invariant tables on one wavefront per
+// block or tree node, matrices in LDS.  The trees of the latter (Method 2) reduce wcs[l] nodes per wave
+// at level l: n[0] = T, n[l + 1] = ceil(n[l] / wcs[l]) while n[l] > wcs[l] (wcs[0] = wc, above
+// kWaveUpperChunk).  Tree nodes are records ([batch][n[l]][record]): tuples (NE values, element
+// order), values (S full, v: nx^2 + nx), maps (P = Psi - I, q: nx^2 + nx), states (nx).
 struct WTree {
   int levels = 0;
   int wc = 8;                     // blocks per wave at the bottom (= wcs[0])

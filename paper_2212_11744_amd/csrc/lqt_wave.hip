@@ -1,15 +1,15 @@
-// Wavefront-per-tuple path for 5 <= nx <= 16 (runtime sizes): one wavefront owns one block (or
-// one tree node) and keeps its matrices in LDS; the 64 lanes split the entries of every matrix
-// product and elimination step.  The arithmetic is that of the per-lane path (A stored as A - I,
-// pivoted Gauss-Jordan solves, the combination rule of Lemma 7, the fold of Theorem 6, the
-// closed-loop block maps of Sec. IV-E); only the distribution over lanes differs.
+// Wave path for 5 <= nx <= 16.  Element build, value scan and Method 1 trajectory are those of
+// tile_kernels.hpp, with the matrices in registers.  The kernels here are one wavefront per block or tree
+// node with its matrices in LDS, the 64 lanes splitting the entries of every matrix product and
+// elimination step: Theorem 9 and split-block elements, the time-invariant tables, Method 2, values
+// inside the blocks, and the trajectory's block maps where none were kept.  Their arithmetic is that
+// of the per-lane path (A stored as A - I, pivoted Gauss-Jordan solves, the combination rule of Lemma
+// 7, the fold of Theorem 6, the closed-loop block maps of Sec. IV-E).
 //
 // Elements use the tiled layout of the C ABI; tree nodes are records ([batch][n][NQ]) with the
 // element's value order: A - I (nx*nx, row-major), b, C (upper triangle, row by row), eta, J.
-// The element build, the value scan and the Method 1 trajectory are those of tile_kernels.hpp, with
-// the matrices in registers; here are the trajectory's block maps where none were kept, and Method 2:
-// every wave reduces wcs[l] consecutive nodes of level l serially (the bottom chunk chosen at run
-// time, upper levels kWaveUpperChunk); level l + 1 has ceil(n_l / wcs[l]) nodes while n_l > wcs[l];
+// Method 2: every wave reduces wcs[l] consecutive nodes of level l serially (the bottom chunk chosen at
+// run time, upper levels kWaveUpperChunk); level l + 1 has ceil(n_l / wcs[l]) nodes while n_l > wcs[l];
 // the top (<= wcs[L] nodes) is swept by one wave.
 #include <cstring>
 

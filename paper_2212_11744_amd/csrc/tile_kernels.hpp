@@ -1,7 +1,8 @@
-// Kernels of the solve for 5 <= nx <= 16 on the register-resident matrices of tile.hpp: element
-// build (Theorem 8), value scan and trajectory scan.  A wave works on B::NODES blocks or tree nodes
-// side by side and exchanges nothing with other waves; LDS holds only the scratch of the rare
-// pivoted inverse.
+// Kernels on the register-resident matrices of tile.hpp: element build (Theorem 8), value scan and
+// trajectory scan of 5 <= nx <= 16 and of short horizons at nx = 3, 4, and the value tree over the tiles of
+// the per-lane path's three-launch scan.  A wave works on B::NODES blocks or tree nodes side by side.
+// The build exchanges nothing with other waves; the trees exchange dumps of registers in LDS, beside the
+// scratch of the rare pivoted inverse.
 //
 // Trees: a slot of a wave takes c consecutive nodes of a level one after the other, and the slots of
 // a workgroup (a group) are combined pairwise in LDS, so that a stage of the tree reduces c G
