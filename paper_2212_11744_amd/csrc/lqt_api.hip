@@ -236,12 +236,11 @@ Tree tree_for(const lqt_dims* d) { return plan_tree(d->T); }
 // instantiated (nu <= nx <= 4), otherwise the wave path (lqt_wave.hip).
 bool use_wave(const lqt_dims* d) { return lane_ops(d->nx, d->nu, d->dtype) == nullptr; }
 
-// Blocks per wave at the bottom level of the wave path's trees for single solves and stage calls
-// (upper levels: kWaveUpperChunk), also the chunk the workspace is laid out for.  Measured on
-// single solves: 4 vs 8 gives nx = 16 at T = 2^14 1.55 vs 1.61 ms and at 2^12 0.68 vs 0.74 ms,
-// nx = 8 and 12 within 1 %; 16 is slower for all three, and so are binary trees (2 per wave at
-// every level: nx = 16 1.61 ms, nx = 8 at 2^16 1.30 vs 1.23 ms, nx = 12 2.02 vs 1.92 ms).  A solve must not use fewer blocks per
-// wave than its workspace was laid out for: the level-1 tree arrays hold ceil(T / chunk) records.
+// Blocks per slot of the bottom stage of the wave path's trees (per wave of Method 2's bottom level) for
+// single solves and stage calls, also the chunk the workspace is laid out for: a solve must not use
+// fewer, since the arrays of the bottom stage hold ceil(T / chunk) records.  Solves of one problem (us, 4 / 8):
+// nx = 16 227 / 238 at T = 2^12, 548 / 515 at 2^14; nx = 12 424 / 406 at 2^14; nx = 8 152 / 167 at 2^14,
+// 364 / 336 at 2^16; nx = 7 103 / 114 at 3001; nx = 5 177 / 172 at 20000.
 constexpr int kWaveChunk = 4;
 
 // Tree of the wave path's scans.  A horizon of one group gets more, shorter slots while every problem has

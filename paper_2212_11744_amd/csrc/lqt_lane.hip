@@ -1431,7 +1431,7 @@ __global__ __launch_bounds__(kThreads, W) void k_vscan(const KProb kp, const R* 
 // its tile, the tree over the tiles (tile_kernels.hpp), the sweep from the value at each tile's right
 // end.  The look-back of the single pass resolves a tile through up to twelve Lemma 7 combinations of
 // whole waves, about 37 of its 77 us at T = 2^16, nx = 4 FP64; the tree does it in 20, and without
-// the records' polling the two kernels stream: T = 2^20 132 + 141 us for 0.42 and 0.58 GB (the
+// the records' polling the two kernels stream: T = 2^20 125 + 127 us for 0.42 and 0.58 GB (the
 // single pass: 302), FP32 50 + 66 (187).  The sweep goes through the tiles backwards and the build
 // before it too, so that each launch starts where the one before it ended, in what the last-level
 // cache still holds.
